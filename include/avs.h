@@ -253,9 +253,9 @@ avs_status avs_dia_adapt(avs_dia *dia, double C1, double C2, const double *probe
 avs_status avs_dia_remap(avs_dia *dia);
 void avs_dia_destroy(avs_dia *dia);
 
-/* Bytes of the device region avs_step_implicit needs for the right-hand
- * side of the micro system: one VDF buffer (components x cells x leaf
- * capacity x element size). */
+/* Bytes of the device region avs_step_implicit needs for the increment of
+ * the micro system: one VDF buffer (components x cells x leaf capacity x
+ * element size). */
 avs_status avs_implicit_bytes(const avs_ctx *ctx, size_t *bytes);
 
 /* Advance nsteps implicit steps (IUGKS, Sec. 2.3.1-2.3.2) with the context's

@@ -90,7 +90,8 @@ struct avs_ctx {
   double *cc, *crit_part, *Mk, *probe_cc, *probe_prim;
   int8_t *raw, *eff;
   int *cnt, *off, *pkind, *psrc, *pchild, *bad;
-  double *rA, *irhs, *idiag, *dW;                // implicit predictor: r per face, rhs, diagonal, increment
+  double *rA, *irhs, *idiag, *prow, *pst;        // implicit predictor: r per face, rhs, 1/diagonal, slot records, state rows
+  int* pnb;                                      // and the sweeps' neighbour table
   int64_t leaf_gen = 0;                          // bumped whenever the leaf set changes
   int* col_cells;                                // cells in colour-major order
   std::vector<int> col_off;                      // colour c holds col_cells[col_off[c] .. col_off[c+1])
@@ -284,7 +285,9 @@ void carve(avs_ctx& x, Carver& c) {
   x.rA = c.take<double>(nf + 1);
   x.irhs = c.take<double>(nc * N);
   x.idiag = c.take<double>(nc);
-  x.dW = c.take<double>(nc * N);
+  x.prow = c.take<double>(nc * mf * (D + 2 + N));
+  x.pst = c.take<double>(nc * (2 * N + 2));
+  x.pnb = c.take<int>(nc * mf);
   x.col_cells = c.take<int>(nc);
   if (D == 2) {
     x.feat = c.take<uint16_t>(cap * mlp::NINP);
@@ -510,6 +513,47 @@ avs_status launch_step(avs_ctx* ctx, bool last_residual) {
   return AVS_OK;
 }
 
+// The turns of nsweep symmetric colour sweeps (colours 0 .. n-1, then n-1
+// .. 0), consecutive turns of one colour taken together: calls
+// turn(colour, reps, last) with reps the number of turns and last set on
+// every colour's final visit (the downward half of the last sweep).
+template <typename F>
+avs_status colour_turns(int ncol, int nsweep, F&& turn) {
+  const int per = 2 * ncol, n = per * nsweep;
+  for (int t = 0; t < n;) {
+    const int p = t % per, c = p < ncol ? p : per - 1 - p;
+    int e = t + 1;
+    while (e < n) {
+      const int q = e % per;
+      if ((q < ncol ? q : per - 1 - q) != c) break;
+      ++e;
+    }
+    if (avs_status st = turn(c, e - t, e - 1 >= n - ncol)) return st;
+    t = e;
+  }
+  return AVS_OK;
+}
+
+// Predictor: records, n_macro symmetric sweeps, the implicit flux over F.
+template <int D, bool ROT>
+avs_status run_predictor(avs_ctx* ctx, int n_macro, double Z, const double* W, const double* rf, double* rec, int* nb,
+                         double* rhs, double* inv, double* st, double* F, int* bad) {
+  k_pred_setup<D, ROT><<<(unsigned)((ctx->nc + BLOCK - 1) / BLOCK), BLOCK, 0, ctx->stream>>>(
+      ctx->geo, ctx->col_cells, F, rf, W, rec, nb, rhs, inv, st);
+  CKL();
+  const avs_status s = colour_turns((int)ctx->col_off.size() - 1, n_macro, [&](int c, int reps, bool) -> avs_status {
+    const int t0 = ctx->col_off[c], cnt = ctx->col_off[c + 1] - t0;
+    k_pred_turn<D, ROT><<<(unsigned)((cnt + PRED_BLOCK - 1) / PRED_BLOCK), PRED_BLOCK, 0, ctx->stream>>>(
+        ctx->geo, ctx->gas, Z, ctx->dt, ctx->col_cells, t0, cnt, reps, W, rec, nb, rhs, inv, st, bad);
+    CKL();
+    return AVS_OK;
+  });
+  if (s) return s;
+  k_pred_flux<D, ROT><<<(unsigned)((ctx->nf + BLOCK - 1) / BLOCK), BLOCK, 0, ctx->stream>>>(ctx->geo, W, st, rf, F);
+  CKL();
+  return AVS_OK;
+}
+
 // One implicit step (IUGKS): interfaces as in the explicit step, then the
 // PRSGS predictor (n_macro symmetric sweeps, colours up then down), W^{n+1}
 // in flux form with the implicit flux of the predicted increment, the
@@ -517,12 +561,15 @@ avs_status launch_step(avs_ctx* ctx, bool last_residual) {
 // n_micro symmetric sweeps of the upwind micro system into the second VDF
 // buffer, phi^{n+1} = phi^n + dphi, and the moments of phi^{n+1}.
 template <int D, typename T>
-avs_status launch_step_implicit(avs_ctx* ctx, int n_macro, int n_micro, T* res, bool last_residual) {
+avs_status launch_step_implicit(avs_ctx* ctx, int n_macro, int n_micro, T* dphi, bool last_residual) {
   constexpr int MAXF = Cfg<D>::MAXF;
   const Leaves L = ctx->leaves(ctx->lcur);
   const int nu = ctx->vg.numax;
   const T* vin = (const T*)ctx->vdf[ctx->cur];
-  T* dphi = (T*)ctx->vdf[ctx->cur ^ 1];
+  // the micro right-hand side lives in the next state's buffer and the
+  // increment in the caller's region: a cell's last visit writes phi^{n+1}
+  // over its own right-hand side, which no other cell reads
+  T* res = (T*)ctx->vdf[ctx->cur ^ 1];
   const int ncol = (int)ctx->col_off.size() - 1;
   const unsigned gc = (unsigned)((ctx->nc + BLOCK - 1) / BLOCK);
   if (avs_status st = launch_interfaces<D, T>(ctx)) return st;
@@ -531,19 +578,9 @@ avs_status launch_step_implicit(avs_ctx* ctx, int n_macro, int n_micro, T* res, 
     k_imp_rface<D><<<(unsigned)((ctx->nf + BLOCK - 1) / BLOCK), BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, ctx->h, ctx->W,
                                                                                        ctx->fpar, ctx->rA);
     CKL();
-    k_imp_rhs<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->F, ctx->rA, ctx->irhs, ctx->idiag, ctx->dW);
-    CKL();
-    for (int sw = 0; sw < n_macro; ++sw)
-      for (int t = 0; t < 2 * ncol; ++t) {
-        const int c = t < ncol ? t : 2 * ncol - 1 - t;
-        const int cnt = ctx->col_off[c + 1] - ctx->col_off[c];
-        k_imp_macro<D><<<(unsigned)((cnt + BLOCK - 1) / BLOCK), BLOCK, 0, ctx->stream>>>(
-            ctx->geo, ctx->gas, ctx->col_cells + ctx->col_off[c], cnt, ctx->W, ctx->rA, ctx->irhs, ctx->idiag, ctx->dW);
-        CKL();
-      }
-    k_imp_fhat<D><<<(unsigned)((ctx->nf + BLOCK - 1) / BLOCK), BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, ctx->W,
-                                                                                      ctx->dW, ctx->rA, ctx->F);
-    CKL();
+    if (avs_status sp = run_predictor<D, false>(ctx, n_macro, 0.0, ctx->W, ctx->rA, ctx->prow, ctx->pnb, ctx->irhs,
+                                                ctx->idiag, ctx->pst, ctx->F, ctx->bad))
+      return sp;
     k_macro<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, ctx->dt, ctx->F, ctx->W, ctx->Wn, ctx->q, ctx->tpar,
                                               ctx->bad);
     CKL();
@@ -562,18 +599,22 @@ avs_status launch_step_implicit(avs_ctx* ctx, int n_macro, int n_micro, T* res, 
   }
   {
     ProfScope ps(ctx, K_IMP_MICRO);
-    k_imp_zero<T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->P, ctx->nc, L, dphi);
-    CKL();
-    for (int sw = 0; sw < n_micro; ++sw)
-      for (int t = 0; t < 2 * ncol; ++t) {
-        const int c = t < ncol ? t : 2 * ncol - 1 - t;
-        const int cnt = ctx->col_off[c + 1] - ctx->col_off[c];
-        k_imp_micro<D, T><<<(unsigned)cnt, BLOCK, 0, ctx->stream>>>(ctx->geo, L, ctx->col_cells + ctx->col_off[c], res,
-                                                                     dphi, ctx->tpar, NPAR, P_A);
-        CKL();
-      }
-    k_imp_finish<T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->P, ctx->nc, L, vin, dphi);
-    CKL();
+    if (n_micro == 0) {
+      k_imp_copy<T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->P, ctx->nc, L, vin, res);
+      CKL();
+    } else {
+      k_imp_zero<T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->P, ctx->nc, L, dphi);
+      CKL();
+    }
+    const avs_status sm = colour_turns(ncol, n_micro, [&](int c, int reps, bool last) -> avs_status {
+      const int cnt = ctx->col_off[c + 1] - ctx->col_off[c];
+      k_imp_micro<D, T><<<(unsigned)cnt, BLOCK, 0, ctx->stream>>>(ctx->geo, L, ctx->col_cells + ctx->col_off[c], res,
+                                                                   dphi, ctx->tpar, NPAR, P_A, reps,
+                                                                   last ? vin : nullptr, last ? res : nullptr);
+      CKL();
+      return AVS_OK;
+    });
+    if (sm) return sm;
   }
   if (last_residual) {
     ProfScope ps(ctx, K_RESIDUAL);
@@ -1449,7 +1490,8 @@ struct avs_dia {
   DiaGas gp{};
   double *v[2] = {nullptr, nullptr}, *fv = nullptr, *W[2] = {nullptr, nullptr};
   double *q = nullptr, *F = nullptr, *tp = nullptr, *lam = nullptr;
-  double *rf = nullptr, *irhs = nullptr, *idiag = nullptr, *dW = nullptr;   // implicit predictor
+  double *rf = nullptr, *irhs = nullptr, *idiag = nullptr, *prow = nullptr, *pst = nullptr;   // implicit predictor
+  int* pnb = nullptr;
   int* bad = nullptr;
   int cur = 0;
   int64_t gen = 0;
@@ -1478,11 +1520,13 @@ size_t dia_layout(const avs_ctx* c, int64_t max_leaves, avs_dia* d, char* base) 
   double* rf = cv.take<double>(nf + 1);
   double* irhs = cv.take<double>(nc * NW);
   double* idiag = cv.take<double>(nc);
-  double* dW = cv.take<double>(nc * NW);
+  double* prow = cv.take<double>(nc * (size_t)c->maxf * (D + 2 + NW));
+  double* pst = cv.take<double>(nc * (2 * NW + 2));
+  int* pnb = cv.take<int>(nc * (size_t)c->maxf);
   int* bad = cv.take<int>(4);
   if (d) {
     d->fv = fv; d->W[0] = W0; d->W[1] = W1; d->q = q; d->F = F; d->tp = tp; d->lam = lam; d->bad = bad;
-    d->rf = rf; d->irhs = irhs; d->idiag = idiag; d->dW = dW;
+    d->rf = rf; d->irhs = irhs; d->idiag = idiag; d->prow = prow; d->pst = pst; d->pnb = pnb;
   }
   return cv.off;
 }
@@ -1552,7 +1596,7 @@ template <int D>
 avs_status dia_steps_implicit(avs_dia* d, int nsteps, int n_macro, int n_micro) {
   avs_ctx* ctx = d->ctx;
   const Leaves L = ctx->leaves(ctx->lcur);
-  const unsigned gc = (unsigned)((ctx->nc + BLOCK - 1) / BLOCK), gf = (unsigned)((ctx->nf + BLOCK - 1) / BLOCK);
+  const unsigned gc = (unsigned)((ctx->nc + BLOCK - 1) / BLOCK);
   const size_t shm = dia_shm(ctx);
   const int ncol = (int)ctx->col_off.size() - 1;
   for (int st = 0; st < nsteps; ++st) {
@@ -1563,19 +1607,9 @@ avs_status dia_steps_implicit(avs_dia* d, int nsteps, int n_macro, int n_micro) 
     k_dg_face<D><<<ctx->nf, BLOCK, shm, ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->gas, d->gp, ctx->h, d->fv, d->F,
                                                        d->bad, d->W[c], d->rf);
     CKL();
-    k_imp_rhs<D, D + 3><<<gc, BLOCK, 0, ctx->stream>>>(ctx->geo, d->F, d->rf, d->irhs, d->idiag, d->dW);
-    CKL();
-    for (int sw = 0; sw < n_macro; ++sw)
-      for (int t = 0; t < 2 * ncol; ++t) {
-        const int cc = t < ncol ? t : 2 * ncol - 1 - t;
-        const int cnt = ctx->col_off[cc + 1] - ctx->col_off[cc];
-        k_dgi_macro<D><<<(unsigned)((cnt + BLOCK - 1) / BLOCK), BLOCK, 0, ctx->stream>>>(
-            ctx->geo, ctx->gas, d->gp, ctx->dt, ctx->col_cells + ctx->col_off[cc], cnt, d->W[c], d->rf, d->irhs,
-            d->idiag, d->dW, d->bad);
-        CKL();
-      }
-    k_dgi_fhat<D><<<gf, BLOCK, 0, ctx->stream>>>(ctx->geo, d->gp, d->W[c], d->dW, d->rf, d->F);
-    CKL();
+    if (avs_status sp = run_predictor<D, true>(ctx, n_macro, d->gp.Z, d->W[c], d->rf, d->prow, d->pnb, d->irhs,
+                                               d->idiag, d->pst, d->F, d->bad))
+      return sp;
     k_dg_macro<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, d->gp, ctx->dt, d->F, d->W[c], d->W[c ^ 1], d->q,
                                                  d->tp, d->bad);
     CKL();
@@ -1589,18 +1623,16 @@ avs_status dia_steps_implicit(avs_dia* d, int nsteps, int n_macro, int n_micro) 
     CKL();
     k_imp_zero<double><<<ctx->nc, BLOCK, 0, ctx->stream>>>(3, ctx->nc, L, dphi);
     CKL();
-    for (int sw = 0; sw < n_micro; ++sw)
-      for (int t = 0; t < 2 * ncol; ++t) {
-        const int cc = t < ncol ? t : 2 * ncol - 1 - t;
-        const int cnt = ctx->col_off[cc + 1] - ctx->col_off[cc];
-        // the backward half of the last sweep visits every cell for the last
-        // time and writes phi^{n+1} over its right-hand side
-        const bool last = sw == n_micro - 1 && t >= ncol;
-        k_imp_micro<D, double, 3><<<(unsigned)cnt, BLOCK, 0, ctx->stream>>>(
-            ctx->geo, L, ctx->col_cells + ctx->col_off[cc], res, dphi, d->tp, Dg<D>::NT, Dg<D>::IDT,
-            last ? d->v[c] : nullptr, last ? d->v[c ^ 1] : nullptr);
-        CKL();
-      }
+    // a cell's last visit writes phi^{n+1} over its right-hand side
+    const avs_status sp = colour_turns(ncol, n_micro, [&](int cc, int reps, bool last) -> avs_status {
+      const int cnt = ctx->col_off[cc + 1] - ctx->col_off[cc];
+      k_imp_micro<D, double, 3><<<(unsigned)cnt, BLOCK, 0, ctx->stream>>>(
+          ctx->geo, L, ctx->col_cells + ctx->col_off[cc], res, dphi, d->tp, Dg<D>::NT, Dg<D>::IDT, reps,
+          last ? d->v[c] : nullptr, last ? d->v[c ^ 1] : nullptr);
+      CKL();
+      return AVS_OK;
+    });
+    if (sp) return sp;
     if (n_micro == 0) {
       k_dgi_finish<<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->nc, L, d->v[c], dphi, d->v[c ^ 1]);
       CKL();

@@ -7,6 +7,7 @@
 // launch updates a whole colour and the result is the sequential
 // Gauss-Seidel sweep in colour-major cell order.  Interface VDFs, fluxes,
 // the target and the closure are those of the explicit step.
+// The predictor is shared with the diatomic gas.
 // Part of the library's single translation unit, after avs_kernels.hip.
 
 namespace avs {
@@ -46,168 +47,335 @@ __global__ void k_imp_rface(Geo g, GasP gas, double h, const double* __restrict_
   rf[f] = fabs(un) + sqrt(5.0 / 3.0 * RT) + 2.0 * nu_over_dl;
 }
 
-// Right-hand side -sum_f sigma A F_f^n, diagonal V/dt + 1/2 sum_f A r, and
-// dW = 0.
-template <int D, int N = D + 2>
-__global__ void k_imp_rhs(Geo g, const double* __restrict__ F, const double* __restrict__ rf, double* __restrict__ rhs,
-                          double* __restrict__ diag, double* __restrict__ dW) {
-  constexpr int MAXF = Cfg<D>::MAXF;
-  const int i = blockIdx.x * BLOCK + threadIdx.x;
-  if (i >= g.nc) return;
-  const int ns = g.nslot[i];
-  double acc[N], ar = 0.0;
-  for (int m = 0; m < N; ++m) acc[m] = 0.0;
-  for (int s = 0; s < ns; ++s) {
-    const int f = g.s_face[i * MAXF + s];
-    const double sa = g.s_sigA[i * MAXF + s];
-    for (int m = 0; m < N; ++m) acc[m] -= sa * F[(size_t)f * N + m];
-    ar += (sa * g.s_sig[i * MAXF + s]) * rf[f];
-  }
-  for (int m = 0; m < N; ++m) {
-    rhs[(size_t)i * N + m] = acc[m];
-    dW[(size_t)i * N + m] = 0.0;
-  }
-  diag[i] = 1.0 / g.dtv[i] + 0.5 * ar;
+// ---- predictor (Eqs. equ_delw, SGS_w; with ROT the rotational row of Eq.
+// SGS_wrot), monatomic W = (rho, rho U, rho E) and diatomic W = (rho, rho U,
+// rho E, rho E_rot).  The sweeps are chains of short dependent launches (a
+// colour of a 64 x 64 mesh is 32 waves), so what counts is the latency of
+// one turn.  Everything a turn needs that does not change during the sweeps
+// is therefore formed once per step, in the sweeps' own (colour-major) cell
+// order, and the sweeps carry W~ = W + dW with 1/rho and p beside dW: a turn
+// is one load of the cell's record, one gather of its neighbours' rows and
+// about 110 FP64 instructions with a single division.
+template <int D, bool ROT>
+struct Pred {
+  static constexpr int N = D + 2 + (ROT ? 1 : 0);
+  static constexpr int SR = 2 * N + 2;           // state row: W~, 1/rho, p, dW
+  static constexpr int MAXF = Cfg<D>::MAXF;
+  static constexpr int REC = D + 2 + N;          // per slot: (A/2) n (outward), A/2, (A/2) r, (A/2) G(W_j)
+};
+
+// slot types of the sweeps' neighbour table beside a cell index >= 0
+constexpr int PRED_NONE = -1, PRED_WALL = -2, PRED_SELF = -3;
+
+// 1/rho and p of a state: p = rho R T (T_t with ROT) = 2/3 of the internal
+// translational energy density.
+template <int D, bool ROT, int N = Pred<D, ROT>::N>
+__device__ __forceinline__ void pred_aux(const double (&w)[N], double& ir, double& p) {
+  ir = 1.0 / w[0];
+  double mm = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) mm += w[1 + d] * w[1 + d];
+  p = w[1 + D] - 0.5 * mm * ir;
+  if constexpr (ROT) p -= w[2 + D];
+  p *= 1.0 / 1.5;
 }
 
-// Euler flux of W through the unit normal n: (rho U.n, rho U U.n + p n,
-// (rho E + p) U.n), p = rho R T.
-template <int D>
-__device__ __forceinline__ void euler_flux(const double (&w)[D + 2], const double (&n)[D], double R, double (&G)[D + 2]) {
-  const double rho = w[0];
-  double U[D], uu = 0.0, un = 0.0;
+// Euler flux (rho U.n, rho U U.n + p n, (rho E + p) U.n[, rho E_rot U.n])
+// through hn, a multiple of the normal.
+template <int D, bool ROT, int N = Pred<D, ROT>::N>
+__device__ __forceinline__ void pred_flux(const double (&w)[N], double ir, double p, const double (&hn)[D],
+                                          double (&G)[N]) {
+  double mn = 0.0;
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    U[d] = w[1 + d] / rho;
-    uu += U[d] * U[d];
-    un += U[d] * n[d];
-  }
-  const double T = (w[1 + D] - 0.5 * rho * uu) / (1.5 * rho * R);
-  const double p = rho * R * T;
-  G[0] = rho * un;
+  for (int d = 0; d < D; ++d) mn += w[1 + d] * hn[d];
+  const double un = mn * ir;
+  G[0] = mn;
 #pragma unroll
-  for (int d = 0; d < D; ++d) G[1 + d] = rho * U[d] * un + p * n[d];
+  for (int d = 0; d < D; ++d) G[1 + d] = w[1 + d] * un + p * hn[d];
   G[1 + D] = (w[1 + D] + p) * un;
+  if constexpr (ROT) G[2 + D] = w[2 + D] * un;
 }
 
-// W reflected in a wall of unit normal n (normal momentum reversed).
-template <int D>
-__device__ __forceinline__ void mirror_state(const double (&w)[D + 2], const double (&n)[D], double (&o)[D + 2]) {
+// W reflected in a wall of unit normal n (normal momentum reversed; 1/rho
+// and p are the cell's own).
+template <int N, int D>
+__device__ __forceinline__ void mirror_state(const double (&w)[N], const double (&n)[D], double (&o)[N]) {
   double mn = 0.0;
 #pragma unroll
   for (int d = 0; d < D; ++d) mn += w[1 + d] * n[d];
-  o[0] = w[0];
 #pragma unroll
-  for (int d = 0; d < D; ++d) o[1 + d] = w[1 + d] - 2.0 * mn * n[d];
-  o[1 + D] = w[1 + D];
+  for (int m = 0; m < N; ++m) o[m] = w[m];
+#pragma unroll
+  for (int d = 0; d < D; ++d) o[1 + d] -= 2.0 * mn * n[d];
 }
 
-__device__ __forceinline__ bool wall_face(const Geo& g, int f) {
-  const int R = g.f_R[f];
-  return R < 0 && g.bc_kind[-1 - R] == 0;
-}
-
-// One colour of a PRSGS sweep on Eq. SGS_w: for each cell i of the colour,
-// dW_i = (rhs_i - sum_j A/2 [G(W_j + dW_j) - G(W_j)] + sum_j A r/2 dW_j) / diag_i
-// over interior neighbours j and wall faces (whose outside is the mirror of
-// the cell's own W and current dW), with the outward normal of i; a
-// far-field face holds the outside increment at zero.
-template <int D>
-__global__ void k_imp_macro(Geo g, GasP gas, const int* __restrict__ cells, int ncells, const double* __restrict__ W,
-                            const double* __restrict__ rf, const double* __restrict__ rhs, const double* __restrict__ diag,
-                            double* __restrict__ dW) {
-  constexpr int MAXF = Cfg<D>::MAXF, N = D + 2;
+// Records of the sweeps, one thread per cell in colour-major order: slot
+// records rec[slot][REC][nc] and neighbours nb[slot][nc], the right-hand side
+// rhs[N][nc] = -sum_f sigma A F_f^n, inv[nc] = 1 / (V/dt + 1/2 sum_f A r),
+// and the state rows st[nc] by cell index at dW = 0.
+template <int D, bool ROT>
+__global__ void k_pred_setup(Geo g, const int* __restrict__ cells, const double* __restrict__ F,
+                             const double* __restrict__ rf, const double* __restrict__ W, double* __restrict__ rec,
+                             int* __restrict__ nb, double* __restrict__ rhs, double* __restrict__ inv,
+                             double* __restrict__ st) {
+  using C = Pred<D, ROT>;
+  constexpr int MAXF = C::MAXF, N = C::N;
   const int t = blockIdx.x * BLOCK + threadIdx.x;
-  if (t >= ncells) return;
+  if (t >= g.nc) return;
   const int i = cells[t];
   const int ns = g.nslot[i];
-  double acc[N];
-  for (int m = 0; m < N; ++m) acc[m] = rhs[(size_t)i * N + m];
-  for (int s = 0; s < ns; ++s) {
-    const int j = g.s_nbr[i * MAXF + s];
-    const int f = g.s_face[i * MAXF + s];
-    if (j < 0 && !wall_face(g, f)) continue;
-    const double sa = g.s_sigA[i * MAXF + s];
-    const double sig = g.s_sig[i * MAXF + s];
-    const double halfA = 0.5 * (sa * sig);
-    double n[D];
-    for (int d = 0; d < D; ++d) n[d] = sig * g.f_nrm[(size_t)f * D + d];
-    double w0[N], w1[N], dj[N], G0[N], G1[N];
-    if (j >= 0) {
-      for (int m = 0; m < N; ++m) {
-        w0[m] = W[(size_t)j * N + m];
-        dj[m] = dW[(size_t)j * N + m];
+  const size_t nc = g.nc;
+  double acc[N], wi[N], ar = 0.0, iri, pi;
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    acc[m] = 0.0;
+    wi[m] = W[(size_t)i * N + m];
+  }
+  pred_aux<D, ROT>(wi, iri, pi);
+#pragma unroll
+  for (int s = 0; s < MAXF; ++s) {
+    int kind = PRED_NONE;
+    double hn[D], G0[N], ha = 0.0, ra = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) hn[d] = 0.0;
+#pragma unroll
+    for (int m = 0; m < N; ++m) G0[m] = 0.0;
+    if (s < ns) {
+      const int f = g.s_face[i * MAXF + s], j = g.s_nbr[i * MAXF + s];
+      const double sa = g.s_sigA[i * MAXF + s], sig = g.s_sig[i * MAXF + s];
+      for (int m = 0; m < N; ++m) acc[m] -= sa * F[(size_t)f * N + m];
+      ar += (sa * sig) * rf[f];
+      const bool wall = j < 0 && g.bc_kind[-1 - g.f_R[f]] == 0;
+      if (j >= 0 || wall) {
+        kind = wall ? PRED_WALL : (j == i ? PRED_SELF : j);
+        ha = 0.5 * (sa * sig);
+        ra = ha * rf[f];
+        double n[D], w0[N];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          n[d] = sig * g.f_nrm[(size_t)f * D + d];
+          hn[d] = ha * n[d];
+        }
+        double ir = iri, p = pi;
+        if (wall) {
+          mirror_state<N, D>(wi, n, w0);
+        } else {
+#pragma unroll
+          for (int m = 0; m < N; ++m) w0[m] = W[(size_t)j * N + m];
+          pred_aux<D, ROT>(w0, ir, p);
+        }
+        pred_flux<D, ROT>(w0, ir, p, hn, G0);
       }
-    } else {
-      double wi[N], di[N];
-      for (int m = 0; m < N; ++m) {
-        wi[m] = W[(size_t)i * N + m];
-        di[m] = dW[(size_t)i * N + m];
-      }
-      mirror_state<D>(wi, n, w0);
-      mirror_state<D>(di, n, dj);
     }
-    for (int m = 0; m < N; ++m) w1[m] = w0[m] + dj[m];
-    euler_flux<D>(w1, n, gas.R, G1);
-    euler_flux<D>(w0, n, gas.R, G0);
-    const double ra = halfA * rf[f];
-    for (int m = 0; m < N; ++m) {
-      acc[m] -= halfA * (G1[m] - G0[m]);
-      acc[m] += ra * dj[m];
+    nb[s * nc + t] = kind;
+    double* r = rec + (size_t)s * C::REC * nc + t;
+#pragma unroll
+    for (int d = 0; d < D; ++d) r[d * nc] = hn[d];
+    r[D * nc] = ha;
+    r[(D + 1) * nc] = ra;
+#pragma unroll
+    for (int m = 0; m < N; ++m) r[(D + 2 + m) * nc] = G0[m];
+  }
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    rhs[m * nc + t] = acc[m];
+    st[(size_t)i * C::SR + m] = wi[m];
+    st[(size_t)i * C::SR + N + 2 + m] = 0.0;
+  }
+  st[(size_t)i * C::SR + N] = iri;
+  st[(size_t)i * C::SR + N + 1] = pi;
+  inv[t] = 1.0 / (1.0 / g.dtv[i] + 0.5 * ar);
+}
+
+// Workgroups of the sweeps: one wave, so that the few thousand cells of a
+// colour spread over as many CUs as there are.
+constexpr int PRED_BLOCK = 64;
+
+// One turn of a colour of a PRSGS sweep on Eq. SGS_w: for each cell i of the
+// colour, dW_i = (rhs_i - sum_j A/2 [G(W_j + dW_j) - G(W_j)] + sum_j A r/2
+// dW_j) / diag_i over interior neighbours j and wall faces (whose outside is
+// the mirror of the cell's own W and current dW), with the outward normal
+// of i; a far-field face holds the outside increment at zero.  With ROT the
+// rotational row gains k = V/(Z tau) on its diagonal and k (rho R T - rho
+// E_rot^n) on its right-hand side, tau and rho R T at the cell's current
+// iterate (zr = Z, Rg = R).
+// reps > 1: the colour's turn comes reps times in a row (a symmetric sweep
+// ends and the next begins on the same colour).  No cell of the colour
+// reads another one's increment, so the neighbours' part is summed once and
+// only what reads the cell's own iterate (a wall's mirror state, a periodic
+// cell that is its own neighbour, the rotational source) is iterated; any
+// other cell would form the same value again.
+template <int D, bool ROT>
+__global__ __launch_bounds__(PRED_BLOCK) void k_pred_turn(Geo g, GasP vgas, double zr, double dt,
+                                                          const int* __restrict__ cells, int t0, int cnt, int reps,
+                                                          const double* __restrict__ W, const double* __restrict__ rec,
+                                                          const int* __restrict__ nb, const double* __restrict__ rhs,
+                                                          const double* __restrict__ inv, double* __restrict__ st,
+                                                          int* __restrict__ bad) {
+  using C = Pred<D, ROT>;
+  constexpr int MAXF = C::MAXF, N = C::N, SR = C::SR;
+  const int l = blockIdx.x * PRED_BLOCK + threadIdx.x;
+  if (l >= cnt) return;
+  const int t = t0 + l;
+  const size_t nc = g.nc;
+  const int i = cells[t];
+  int j[MAXF];
+  double hn[MAXF][D], ra[MAXF], G0[MAXF][N], acc[N], wi[N];
+  unsigned own = 0;
+#pragma unroll
+  for (int s = 0; s < MAXF; ++s) {
+    j[s] = nb[s * nc + t];
+    const double* r = rec + (size_t)s * C::REC * nc + t;
+#pragma unroll
+    for (int d = 0; d < D; ++d) hn[s][d] = r[d * nc];
+    ra[s] = r[(D + 1) * nc];
+#pragma unroll
+    for (int m = 0; m < N; ++m) G0[s][m] = r[(D + 2 + m) * nc];
+  }
+#pragma unroll
+  for (int m = 0; m < N; ++m) acc[m] = rhs[m * nc + t];
+  const double iv = inv[t];
+#pragma unroll
+  for (int m = 0; m < N; ++m) wi[m] = W[(size_t)i * N + m];
+  double w[MAXF][SR];
+#pragma unroll
+  for (int s = 0; s < MAXF; ++s) {
+    const double* row = st + (size_t)(j[s] >= 0 ? j[s] : i) * SR;
+#pragma unroll
+    for (int m = 0; m < SR; ++m) w[s][m] = row[m];
+  }
+#pragma unroll
+  for (int s = 0; s < MAXF; ++s) {
+    double ws[N], G1[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) ws[m] = w[s][m];
+    if (j[s] >= 0) {
+      pred_flux<D, ROT>(ws, w[s][N], w[s][N + 1], hn[s], G1);
+#pragma unroll
+      for (int m = 0; m < N; ++m) acc[m] += ra[s] * w[s][N + 2 + m] - (G1[m] - G0[s][m]);
+    } else if (j[s] < PRED_NONE) {
+      own |= 1u << s;
     }
   }
-  const double inv = diag[i];
-  for (int m = 0; m < N; ++m) dW[(size_t)i * N + m] = acc[m] / inv;
+  double wc[N], dc[N], ir, p;
+  if (!ROT && !own) {
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+      dc[m] = acc[m] * iv;
+      wc[m] = wi[m] + dc[m];
+    }
+    pred_aux<D, ROT>(wc, ir, p);
+  } else {
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+      wc[m] = st[(size_t)i * SR + m];
+      dc[m] = st[(size_t)i * SR + N + 2 + m];
+    }
+    ir = st[(size_t)i * SR + N];
+    p = st[(size_t)i * SR + N + 1];
+    for (int q = 0; q < reps; ++q) {
+      double a[N];
+#pragma unroll
+      for (int m = 0; m < N; ++m) a[m] = acc[m];
+#pragma unroll
+      for (int s = 0; s < MAXF; ++s) {
+        if (!((own >> s) & 1u)) continue;
+        double ws[N], ds[N], h[D], G1[N];
+        const double ha = rec[((size_t)s * C::REC + D) * nc + t];
+#pragma unroll
+        for (int d = 0; d < D; ++d) h[d] = hn[s][d] / ha;
+        if (j[s] == PRED_WALL && ha > 0.0) {
+          mirror_state<N, D>(wc, h, ws);
+          mirror_state<N, D>(dc, h, ds);
+        } else {
+#pragma unroll
+          for (int m = 0; m < N; ++m) { ws[m] = wc[m]; ds[m] = dc[m]; }
+        }
+        pred_flux<D, ROT>(ws, ir, p, hn[s], G1);
+#pragma unroll
+        for (int m = 0; m < N; ++m) a[m] += ra[s] * ds[m] - (G1[m] - G0[s][m]);
+      }
+      double k = 0.0;
+      if constexpr (ROT) {
+        const double rho = wc[0], Tr = wc[2 + D] / (rho * vgas.R), Tt = p / (rho * vgas.R);
+        if (rho > 0.0 && Tt > 0.0 && Tr > 0.0) {
+          k = dt / g.dtv[i] / (zr * tau_of(rho, Tt, vgas));
+          a[2 + D] += k * (rho * vgas.R * ((3.0 * Tt + 2.0 * Tr) / 5.0) - wi[2 + D]);
+        } else {
+          atomicMin(bad, i);
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < N; ++m) {
+        dc[m] = ROT && m == 2 + D ? a[m] / (1.0 / iv + k) : a[m] * iv;
+        wc[m] = wi[m] + dc[m];
+      }
+      pred_aux<D, ROT>(wc, ir, p);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    st[(size_t)i * SR + m] = wc[m];
+    st[(size_t)i * SR + N + 2 + m] = dc[m];
+  }
+  st[(size_t)i * SR + N] = ir;
+  st[(size_t)i * SR + N + 1] = p;
 }
 
 // Implicit flux of a face, in place over F^n (Eqs. delta_Flux, Roe):
-// F_f + 1/2 [G(W_L + dW_L) - G(W_L) + G(W_R + dW_R) - G(W_R)]
-// + 1/2 r (dW_L - dW_R) through the face normal, the outside of a boundary
-// face as in the predictor (mirror state at a wall, so that no mass crosses
-// it; increment 0 at the far field).  The explicit macro update then gives
-// W^{n+1} in flux form: exactly conservative after any number of sweeps.
-template <int D>
-__global__ void k_imp_fhat(Geo g, GasP gas, const double* __restrict__ W, const double* __restrict__ dW,
-                           const double* __restrict__ rf, double* __restrict__ F) {
-  constexpr int N = D + 2;
+// F_f + 1/2 [G(W~_L) - G(W_L) + G(W~_R) - G(W_R)] + 1/2 r (dW_L - dW_R)
+// through the face normal, the outside of a boundary face as in the
+// predictor (mirror state at a wall, so that no mass crosses it; increment 0
+// at the far field).  The explicit macro update then gives W^{n+1} in flux
+// form: exactly conservative after any number of sweeps.
+template <int D, bool ROT>
+__global__ void k_pred_flux(Geo g, const double* __restrict__ W, const double* __restrict__ st,
+                            const double* __restrict__ rf, double* __restrict__ F) {
+  using C = Pred<D, ROT>;
+  constexpr int N = C::N, SR = C::SR;
   const int f = blockIdx.x * BLOCK + threadIdx.x;
   if (f >= g.nf) return;
   const int L = g.f_L[f], R = g.f_R[f];
   const bool wall = R < 0 && g.bc_kind[-1 - R] == 0;
-  double n[D];
-  for (int d = 0; d < D; ++d) n[d] = g.f_nrm[(size_t)f * D + d];
-  double v[N], w0[N], w1[N], dL[N], G0[N], G1[N];
-  for (int m = 0; m < N; ++m) {
-    v[m] = F[(size_t)f * N + m];
-    w0[m] = W[(size_t)L * N + m];
-    dL[m] = dW[(size_t)L * N + m];
-    w1[m] = w0[m] + dL[m];
+  double n[D], hn[D], v[N];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    n[d] = g.f_nrm[(size_t)f * D + d];
+    hn[d] = 0.5 * n[d];
   }
-  euler_flux<D>(w1, n, gas.R, G1);
-  euler_flux<D>(w0, n, gas.R, G0);
-  for (int m = 0; m < N; ++m) v[m] = v[m] + 0.5 * (G1[m] - G0[m]);
   const double hr = 0.5 * rf[f];
-  double dR[N];
-  if (R >= 0 || wall) {
-    if (R >= 0) {
-      for (int m = 0; m < N; ++m) {
-        w0[m] = W[(size_t)R * N + m];
-        dR[m] = dW[(size_t)R * N + m];
-      }
-    } else {
-      double wl[N];
-      for (int m = 0; m < N; ++m) wl[m] = W[(size_t)L * N + m];
-      mirror_state<D>(wl, n, w0);
-      mirror_state<D>(dL, n, dR);
+#pragma unroll
+  for (int m = 0; m < N; ++m) v[m] = F[(size_t)f * N + m];
+  for (int side = 0; side < 2; ++side) {
+    if (side == 1 && R < 0 && !wall) continue;
+    const int c = side == 1 && R >= 0 ? R : L;
+    double w0[N], w1[N], dw[N], ir0, p0;
+#pragma unroll
+    for (int m = 0; m < N; ++m) {
+      w0[m] = W[(size_t)c * N + m];
+      w1[m] = st[(size_t)c * SR + m];
+      dw[m] = st[(size_t)c * SR + N + 2 + m];
     }
-    for (int m = 0; m < N; ++m) w1[m] = w0[m] + dR[m];
-    euler_flux<D>(w1, n, gas.R, G1);
-    euler_flux<D>(w0, n, gas.R, G0);
-    for (int m = 0; m < N; ++m) v[m] = v[m] + 0.5 * (G1[m] - G0[m]);
-  } else {
-    for (int m = 0; m < N; ++m) dR[m] = 0.0;
+    pred_aux<D, ROT>(w0, ir0, p0);
+    const double ir1 = st[(size_t)c * SR + N], p1 = st[(size_t)c * SR + N + 1];
+    if (side == 1 && wall) {
+      double t0[N], t1[N], td[N];
+      mirror_state<N, D>(w0, n, t0);
+      mirror_state<N, D>(w1, n, t1);
+      mirror_state<N, D>(dw, n, td);
+#pragma unroll
+      for (int m = 0; m < N; ++m) { w0[m] = t0[m]; w1[m] = t1[m]; dw[m] = td[m]; }
+    }
+    // both fluxes by the same expression, so that a zero increment changes
+    // nothing bit for bit
+    double e1[N], e0[N];
+    pred_flux<D, ROT>(w1, ir1, p1, hn, e1);
+    pred_flux<D, ROT>(w0, ir0, p0, hn, e0);
+    const double sr = side == 0 ? hr : -hr;
+#pragma unroll
+    for (int m = 0; m < N; ++m) v[m] = v[m] + ((e1[m] - e0[m]) + sr * dw[m]);
   }
-  for (int m = 0; m < N; ++m) v[m] = v[m] + hr * (dL[m] - dR[m]);
+#pragma unroll
   for (int m = 0; m < N; ++m) F[(size_t)f * N + m] = v[m];
 }
 
@@ -237,11 +405,12 @@ __global__ void k_imp_zero(int P, int nc, Leaves L, T* __restrict__ x) {
 // P components; dt/tau~ of cell i is tpar[i * tstride + toff].  With out
 // (the cell's last visit of the last sweep, when its increment is final),
 // also out = vin + dphi; out may be the buffer of res, which only the cell
-// itself reads.
+// itself reads.  reps > 1: the colour's turn comes reps times in a row; only
+// a cell that is its own (periodic) neighbour forms another value then.
 template <int D, typename T, int P = Cfg<D>::P>
 __global__ __launch_bounds__(BLOCK) void k_imp_micro(Geo g, Leaves L, const int* __restrict__ cells,
                                                      const T* res, T* __restrict__ dphi,
-                                                     const double* __restrict__ tpar, int tstride, int toff,
+                                                     const double* __restrict__ tpar, int tstride, int toff, int reps,
                                                      const T* __restrict__ vin = nullptr, T* out = nullptr) {
   constexpr int MAXF = Cfg<D>::MAXF;
   __shared__ double snrm[MAXF][D];
@@ -259,6 +428,10 @@ __global__ __launch_bounds__(BLOCK) void k_imp_micro(Geo g, Leaves L, const int*
   __syncthreads();
   const double dtt = tpar[(size_t)i * tstride + toff], dtv = g.dtv[i];
   const size_t cs = (size_t)g.nc * L.ld;
+  bool self = false;
+  for (int s = 0; s < ns; ++s) self = self || snbr[s] == i;
+  const int nrep = self ? reps : 1;
+  for (int r = 0; r < nrep; ++r)
   for (int k = threadIdx.x; k < L.n; k += BLOCK) {
     double xi[D], A;
     int u[D];
@@ -282,20 +455,20 @@ __global__ __launch_bounds__(BLOCK) void k_imp_micro(Geo g, Leaves L, const int*
     for (int p = 0; p < P; ++p) {
       const T x = (res[p * cs + o] - (T)dtv * off[p]) / (T)dg;
       dphi[p * cs + o] = x;
-      if (out) out[p * cs + o] = vin[p * cs + o] + x;
+      if (out && r == nrep - 1) out[p * cs + o] = vin[p * cs + o] + x;
     }
   }
 }
 
-// phi^{n+1} = phi^n + dphi, in place over dphi.
+// phi^{n+1} = phi^n (no micro sweeps: the increment is zero).
 template <typename T>
-__global__ void k_imp_finish(int P, int nc, Leaves L, const T* __restrict__ vin, T* __restrict__ x) {
+__global__ void k_imp_copy(int P, int nc, Leaves L, const T* __restrict__ vin, T* __restrict__ out) {
   const int i = blockIdx.x;
   const size_t cs = (size_t)nc * L.ld;
   for (int k = threadIdx.x; k < L.n; k += BLOCK)
     for (int p = 0; p < P; ++p) {
       const size_t o = p * cs + (size_t)i * L.ld + k;
-      x[o] = vin[o] + x[o];
+      out[o] = vin[o];
     }
 }
 
