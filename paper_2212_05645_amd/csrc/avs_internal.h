@@ -55,6 +55,18 @@ struct Geo {
   const double* bc_prim; // [nbc*(D+2)]
 };
 
+// One leaf's entry of the row table: what the kernels that give a lane to
+// each cell (or face) and take one leaf at a time read of it.  The leaf is
+// then the same for the whole wave, so its row comes through the scalar
+// cache into scalar registers.
+template <int D>
+struct LeafRow {
+  double xi[D];
+  float xf[D];           // xi in FP32
+  int u[D == 2 ? 2 : 3]; // half-finest grid index
+  double A, Ax[D], e, h; // A, A xi, A |xi|^2 / 2, A / 2
+};
+
 struct Leaves {
   int n;       // leaves
   int ld;      // VDF row stride
@@ -69,6 +81,7 @@ struct Leaves {
   // offset, where base + d cap + offset became a 64-bit vector add per load
   const double* xd[3];
   const int* ud[3];
+  const void* rows;   // [cap] LeafRow<D>
 };
 
 struct VGrid {          // the half-finest grid that carries every leaf centre

@@ -382,8 +382,8 @@ __device__ __forceinline__ void leaf_load_rows(const Leaves& L, int k, double (&
 // criterion can be compared bit for bit.
 template <int D>
 __global__ void k_leaf_geom(int n, int cap, const int* __restrict__ level, const int* __restrict__ idx,
-                            int* __restrict__ u, double* __restrict__ xi, double* __restrict__ w, VGrid vg,
-                            int lmax, int b0, int b1, int b2, double lo0, double lo1, double lo2, double hi0,
+                            int* __restrict__ u, double* __restrict__ xi, double* __restrict__ w,
+                            LeafRow<D>* __restrict__ rows, VGrid vg, int lmax, int b0, int b1, int b2, double lo0, double lo1, double lo2, double hi0,
                             double hi1, double hi2) {
 #pragma clang fp contract(off)
   const int k = blockIdx.x * BLOCK + threadIdx.x;
@@ -401,7 +401,29 @@ __global__ void k_leaf_geom(int n, int cap, const int* __restrict__ level, const
     a = (d == 0) ? h : a * h;
   }
   w[k] = a;
+  LeafRow<D> r;
+  double x2 = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const double x = xi[d * cap + k];
+    r.xi[d] = x;
+    r.xf[d] = (float)x;
+    r.u[d] = u[d * cap + k];
+    r.Ax[d] = a * x;
+    x2 += x * x;
+  }
+  r.A = a;
+  r.e = 0.5 * a * x2;
+  r.h = 0.5 * a;
+  rows[k] = r;
 }
+
+// The leaf rows as constant memory: read through the scalar cache at a
+// wave-uniform index.
+template <int D>
+using RowPtr = const __attribute__((address_space(4))) LeafRow<D>*;
+template <int D>
+__device__ __forceinline__ RowPtr<D> leaf_rows(const Leaves& L) { return (RowPtr<D>)(uintptr_t)L.rows; }
 
 // ------------------------------------------------ initial state / closure
 // phi = closure(g_eq(W), W): discrete Maxwellian corrected along its own
@@ -1311,6 +1333,328 @@ __global__ __launch_bounds__(BLOCK) void k_target(Geo g, Leaves L, VGrid vg, con
   d_target<D, R>(g, L, vg, tpar, Wn, lam, bad, blockIdx.x, blockIdx.y);
 }
 
+// ------------------------------------------ a lane per cell or per face
+// The target's closure and the interface equilibrium sum, over all leaves,
+// leaf weights times an equilibrium of one cell or face.  Here a workgroup
+// takes 64 cells (faces), one per lane, and its waves share out the leaves:
+// the leaf is the same for the whole wave, so its row sits in scalar
+// registers, the exponential tables [d][u][lane] are read without bank
+// conflicts, no sum crosses lanes (only the waves' sums are added at the
+// end), and the scalar part of 64 cells (records, closure solves) runs in
+// parallel instead of on one thread each.  The kernels with a workgroup per
+// cell (four faces) load the leaf into vector registers, reduce 14-20 sums
+// across 256 lanes and solve on one thread.  Target measured, workgroup per
+// cell against lane per cell: 4096 cells x 256 leaves FP64 48 + 6 (macro
+// kernel) -> 15 us, 11 880 x 1252 FP32 134 + 7 -> 42 us, 2574 x 4404 FP64
+// 3-D 66 + 8 -> 43 us, 36 864 x 19 972 FP32 3-D 1.81 -> 1.31 ms (bound by
+// VALU issue: about 54 instructions per cell and leaf against 71).
+// The tables of 64 lanes have to fit the LDS: lane_form is the rule.
+constexpr int LANE_WAVES = 16;
+constexpr int LANE_BLOCK = 64 * LANE_WAVES;
+constexpr size_t LANE_LDS = 144 * 1024;     // of 160 KiB per CU
+
+template <int D, typename R>
+constexpr size_t lane_tab_bytes(int numax) { return (size_t)D * numax * 64 * sizeof(R); }
+
+// True when the 64-lane form's tables fit (numax up to 144 in FP64 2-D, 288
+// in FP32 2-D, 192 in FP32 3-D).
+template <int D, typename R>
+inline bool lane_form(int numax) { return lane_tab_bytes<D, R>(numax) <= LANE_LDS; }
+
+// Dynamic LDS: the tables, later the waves' partial sums (nacc doubles per
+// lane from half of the waves).
+template <int D, typename R>
+inline size_t lane_lds(int numax, int nacc) {
+  const size_t t = lane_tab_bytes<D, R>(numax), r = (size_t)(LANE_WAVES / 2) * nacc * 64 * sizeof(double);
+  return t > r ? t : r;
+}
+
+// Leaf shares: a launch has ceil(n / 64) groups of lanes, each able to fill a
+// CU (or, with small tables, half of one).  When those do not fill the 256
+// CUs evenly the leaves are split over several workgroups per group, whose
+// sums a finishing kernel adds.  The number of shares is the one of least
+// estimated time, rounds of workgroups times the work of one in leaves: its
+// leaves, its tables (an exponential costs about what a leaf does) and 640
+// leaves' worth of reduction and latency; the finishing launch counts 1500.
+// (Sphere, 36 864 cells x 19 972 leaves, FP32: 576 groups are 2.25 rounds.
+// 2574 cells x 4404 leaves, FP64: 41 groups of 256 CUs.)
+// At most `most` shares (the partial sums' room).
+template <int D, typename R>
+inline int lane_shares(int count, int nleaf, int numax, int nacc, int64_t most) {
+  const int groups = (count + 63) / 64;
+  const int64_t per_cu = lane_lds<D, R>(numax, nacc) + 12 * 1024 <= 80 * 1024 ? 2 : 1, slots = 256 * per_cu;
+  int best = 1;
+  int64_t cost = INT64_MAX;
+  for (int s = 1; s <= 16 && s <= most; ++s) {
+    const int64_t rounds = ((int64_t)groups * s + slots - 1) / slots;
+    const int64_t c = rounds * per_cu * ((nleaf + s - 1) / s + D * numax + 640) + (s > 1 ? 1500 : 0);
+    if (c < cost) { cost = c; best = s; }
+  }
+  return best;
+}
+
+// Tables of the 64 lanes' Maxwellians from their records spar[NPAR][64]:
+// tab[d][u][lane] = exp(-(x_u - U_d)^2 / 2RT).
+template <int D, typename R>
+__device__ __forceinline__ void lane_tables(R* tab, const double (*spar)[64], const VGrid& vg) {
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    const double x0 = vg.x0[d], hh = vg.hh[d];
+    for (int t = threadIdx.x; t < vg.numax * 64; t += LANE_BLOCK) {
+      const int c = t & 63, u = t >> 6;
+      const double v = (x0 + u * hh) - spar[P_U + d][c];
+      tab[(size_t)d * vg.numax * 64 + t] = (R)exp(-(v * v) * spar[P_I2RT][c]);
+    }
+  }
+}
+
+// Adds the waves' sums lane by lane; the total is in wave 0.  part: LDS,
+// LANE_WAVES / 2 x N x 64 doubles.
+template <int N>
+__device__ __forceinline__ void lane_sum(double (&v)[N], double* part) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll 1
+  for (int half = LANE_WAVES / 2; half > 0; half >>= 1) {
+    __syncthreads();
+    if (w >= half && w < 2 * half) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) part[((w - half) * N + m) * 64 + lane] = v[m];
+    }
+    __syncthreads();
+    if (w < half) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) v[m] += part[(w * N + m) * 64 + lane];
+    }
+  }
+}
+
+// Solve J x = b by Gaussian elimination with partial pivoting, in the lane's
+// registers (every index static).
+template <int N>
+__device__ __forceinline__ bool solve_lane(double (&J)[N][N], double (&b)[N], double (&x)[N]) {
+  bool ok = true;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+#pragma unroll
+    for (int r = c + 1; r < N; ++r) {
+      const bool sw = fabs(J[r][c]) > fabs(J[c][c]);
+#pragma unroll
+      for (int k = c; k < N; ++k) {
+        const double p = J[c][k], q = J[r][k];
+        J[c][k] = sw ? q : p;
+        J[r][k] = sw ? p : q;
+      }
+      const double p = b[c], q = b[r];
+      b[c] = sw ? q : p;
+      b[r] = sw ? p : q;
+    }
+    ok = ok && fabs(J[c][c]) > 0.0;
+    const double inv = 1.0 / J[c][c];
+#pragma unroll
+    for (int r = c + 1; r < N; ++r) {
+      const double f = J[r][c] * inv;
+#pragma unroll
+      for (int k = c + 1; k < N; ++k) J[r][k] -= f * J[c][k];
+      b[r] -= f * b[c];
+    }
+  }
+#pragma unroll
+  for (int r = N - 1; r >= 0; --r) {
+    double s = b[r];
+#pragma unroll
+    for (int k = r + 1; k < N; ++k) s -= J[r][k] * x[k];
+    x[r] = s / J[r][r];
+  }
+  return ok;
+}
+
+// The closure's lambda from the sums acc (moments of the target, then the
+// Gram sums about U): J_lm = M_l[e_m] as gram_to_J forms it, J lambda = W - M.
+template <int D>
+__device__ __forceinline__ bool lane_closure(const double* acc, const double* w, const double* U, double RT,
+                                             double (&x)[D + 2]) {
+  constexpr int N = D + 2;
+  double J[N][N], b[N];
+  double U2 = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) U2 += U[d] * U[d];
+  const double hidden = D == 2 ? RT : 0.0;
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    const double s0 = acc[N + sym_index<D>(0, m)];
+    double en = 0.5 * acc[N + sym_index<D>(D + 1, m)] + 0.5 * (U2 + hidden) * s0;
+    J[0][m] = s0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const double sd = acc[N + sym_index<D>(1 + d, m)];
+      J[1 + d][m] = sd + U[d] * s0;
+      en += U[d] * sd;
+    }
+    J[D + 1][m] = en;
+    b[m] = w[m] - acc[m];
+  }
+  return solve_lane<N>(J, b, x);
+}
+
+// Macro update (d_macro) and target closure (d_target) of 64 cells, one per
+// lane; grid ceil(nc / 64) groups x `shares` of the leaves.  With one share
+// lambda is solved here, else the sums go to part[share][m][64 groups] for
+// k_target_close.
+template <int D, typename R>
+__device__ __forceinline__ void d_target_lanes(Geo g, Leaves L, VGrid vg, GasP gas, double dt,
+                                               const double* __restrict__ F, const double* __restrict__ W,
+                                               double* __restrict__ Wn, const double* __restrict__ qcur,
+                                               double* __restrict__ tpar, double* __restrict__ lam,
+                                               double* __restrict__ part, int* __restrict__ bad, int shares, int bx,
+                                               int by) {
+  constexpr int N = D + 2, NS = Cfg<D>::NS, MAXF = Cfg<D>::MAXF;
+  extern __shared__ double lds_d[];
+  R* tab = reinterpret_cast<R*>(lds_d);
+  __shared__ double spar[NPAR][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool valid = bx * 64 + lane < g.nc;
+  const int i = valid ? bx * 64 + lane : g.nc - 1;     // spare lanes repeat the last cell
+  double w[N];
+  if (wave == 0) {
+    const int ns = g.nslot[i];
+    double Fs[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) Fs[m] = 0.0;
+#pragma unroll
+    for (int s = 0; s < MAXF; ++s) {
+      const int f = s < ns ? g.s_face[i * MAXF + s] : 0;
+      const double sa = s < ns ? g.s_sigA[i * MAXF + s] : 0.0;
+      if (s < ns) {
+#pragma unroll
+        for (int m = 0; m < N; ++m) Fs[m] += sa * F[(size_t)f * N + m];
+      }
+    }
+    const double dtv = g.dtv[i];
+#pragma unroll
+    for (int m = 0; m < N; ++m) w[m] = W[(size_t)i * N + m] - dtv * Fs[m];
+    double rho, U[D], T, par[NPAR];
+    if (!prim_from_W<D>(w, gas, rho, U, T)) {
+      if (valid && by == 0) atomicMin(bad, i);
+      rho = 1.0;
+      T = 1.0;
+    }
+#pragma unroll
+    for (int m = 0; m < NPAR; ++m) par[m] = 0.0;
+    eq_record<D>(par, rho, U, T, qcur + (size_t)i * D, gas);
+    par[P_A] = dt / tau_of(rho, T, gas);
+    par[P_RHO] = rho;
+    par[P_T] = T;
+#pragma unroll
+    for (int m = 0; m < NPAR; ++m) spar[m][lane] = par[m];
+    if (valid && by == 0) {
+#pragma unroll
+      for (int m = 0; m < N; ++m) Wn[(size_t)i * N + m] = w[m];
+#pragma unroll
+      for (int m = 0; m <= P_T; ++m) tpar[(size_t)i * NPAR + m] = par[m];
+    }
+  }
+  __syncthreads();
+  lane_tables<D, R>(tab, spar, vg);
+  double U[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) U[d] = spar[P_U + d][lane];
+  // the record in R: the Shakhov values are formed as pass C forms them, so
+  // that the closure holds for the values pass C takes
+  R rp[NPAR];
+#pragma unroll
+  for (int m = 0; m < NPAR; ++m) rp[m] = (R)spar[m][lane];
+  __syncthreads();
+  // acc: moments of the Shakhov target (rho, m, rho E), then the Gram sums
+  double acc[N + NS];
+#pragma unroll
+  for (int m = 0; m < N + NS; ++m) acc[m] = 0.0;
+  const RowPtr<D> rows = leaf_rows<D>(L);
+  const R* tl = tab + lane;
+  const int per = (L.n + shares - 1) / shares, n = min(L.n, (by + 1) * per);
+#pragma unroll 2
+  for (int k = by * per + wave; k < n; k += LANE_WAVES) {
+    const RowPtr<D> r = rows + k;
+    R gr = rp[P_COEF];
+    R xr[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      gr *= tl[(d * vg.numax + r->u[d]) * 64];
+      xr[d] = sizeof(R) == 4 ? (R)r->xf[d] : (R)r->xi[d];
+    }
+    R Gr, Hr;
+    shakhov_r<D, R>(rp, gr, xr, Gr, Hr);
+    double c[D], c2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      c[d] = r->xi[d] - U[d];
+      c2 = d == 0 ? c[d] * c[d] : fma(c[d], c[d], c2);
+    }
+    const double G = Gr;
+    acc[0] = fma(r->A, G, acc[0]);
+#pragma unroll
+    for (int d = 0; d < D; ++d) acc[1 + d] = fma(r->Ax[d], G, acc[1 + d]);
+    acc[D + 1] = fma(r->e, G, acc[D + 1]);
+    if constexpr (D == 2) acc[D + 1] = fma(r->h, (double)Hr, acc[D + 1]);
+    gram_acc<D>(acc + N, r->A * (double)gr, c, c2);
+  }
+  lane_sum<N + NS>(acc, lds_d);
+  if (wave != 0) return;
+  if (shares > 1) {
+    const size_t rows64 = (size_t)((g.nc + 63) / 64) * 64;
+#pragma unroll
+    for (int m = 0; m < N + NS; ++m) part[((size_t)by * (N + NS) + m) * rows64 + bx * 64 + lane] = acc[m];
+    return;
+  }
+  double x[N];
+  const bool ok = lane_closure<D>(acc, w, U, spar[P_RT][lane], x);
+  if (valid) {
+    if (!ok) atomicMin(bad, i);
+#pragma unroll
+    for (int m = 0; m < N; ++m) lam[(size_t)i * N + m] = ok ? x[m] : 0.0;
+  }
+}
+
+// The closure of a target whose leaves were shared out: the shares' sums in
+// order, then the solve; one thread per cell.
+template <int D>
+__device__ __forceinline__ void d_target_close(int nc, int shares, const double* __restrict__ part,
+                                               const double* __restrict__ tpar, const double* __restrict__ Wn,
+                                               double* __restrict__ lam, int* __restrict__ bad, int bx) {
+  constexpr int N = D + 2, NS = Cfg<D>::NS;
+  const int i = bx * 64 + threadIdx.x;
+  if (i >= nc) return;
+  const size_t rows64 = (size_t)((nc + 63) / 64) * 64;
+  double acc[N + NS], w[N], x[N];
+#pragma unroll
+  for (int m = 0; m < N + NS; ++m) acc[m] = 0.0;
+  for (int s = 0; s < shares; ++s)
+#pragma unroll
+    for (int m = 0; m < N + NS; ++m) acc[m] += part[((size_t)s * (N + NS) + m) * rows64 + i];
+#pragma unroll
+  for (int m = 0; m < N; ++m) w[m] = Wn[(size_t)i * N + m];
+  const double* par = tpar + (size_t)i * NPAR;
+  const bool ok = lane_closure<D>(acc, w, par + P_U, par[P_RT], x);
+  if (!ok) atomicMin(bad, i);
+#pragma unroll
+  for (int m = 0; m < N; ++m) lam[(size_t)i * N + m] = ok ? x[m] : 0.0;
+}
+
+template <int D>
+__global__ __launch_bounds__(64) void k_target_close(int nc, int shares, const double* __restrict__ part,
+                                                     const double* __restrict__ tpar, const double* __restrict__ Wn,
+                                                     double* __restrict__ lam, int* __restrict__ bad) {
+  d_target_close<D>(nc, shares, part, tpar, Wn, lam, bad, blockIdx.x);
+}
+
+template <int D, typename R>
+__global__ __launch_bounds__(LANE_BLOCK) void k_target_lanes(Geo g, Leaves L, VGrid vg, GasP gas, double dt,
+                                                             const double* __restrict__ F, const double* __restrict__ W,
+                                                             double* __restrict__ Wn, const double* __restrict__ qcur,
+                                                             double* __restrict__ tpar, double* __restrict__ lam,
+                                                             double* __restrict__ part, int* __restrict__ bad) {
+  d_target_lanes<D, R>(g, L, vg, gas, dt, F, W, Wn, qcur, tpar, lam, part, bad, gridDim.y, blockIdx.x, blockIdx.y);
+}
+
 // -------------------------------------------------- pass C (S6, S7, S10)
 // Interface VDFs of every face of the cell (upwind reconstruction from the
 // interface buffer, blended with the interface Shakhov equilibrium; on
@@ -2133,9 +2477,10 @@ struct CaseArgs {
   double* fmom;    // face-moment partials of pass A [nf][2][nchs][NM]
   int nchs;        // their chunk stride
   int chunk, gx;   // pass A: leaves per workgroup, round_up(nc, 8)
+  int shares;      // leaf shares of the 64-lane target
 };
 
-enum { BK_PASSA, BK_FACEQ, BK_MACRO, BK_TARGET, BK_PASSC, BK_N };
+enum { BK_PASSA, BK_FACEQ, BK_MACRO, BK_TARGET, BK_LTARGET, BK_LCLOSE, BK_PASSC, BK_N };
 
 // Largest c with off[c] <= b (off has ncase + 1 increasing entries).
 __device__ __forceinline__ int find_case(const int* __restrict__ off, int ncase, int b) {
@@ -2165,6 +2510,7 @@ __device__ __forceinline__ Geo global_geo(Geo g) {
 }
 __device__ __forceinline__ Leaves global_leaves(Leaves L) {
   AVS_G(L.level); AVS_G(L.idx); AVS_G(L.u); AVS_G(L.xi); AVS_G(L.w);
+  // (L.rows is read as constant memory, leaf_rows)
   AVS_G(L.xd[0]); AVS_G(L.xd[1]); AVS_G(L.xd[2]); AVS_G(L.ud[0]); AVS_G(L.ud[1]); AVS_G(L.ud[2]);
   return L;
 }
@@ -2205,6 +2551,26 @@ __global__ __launch_bounds__(BLOCK) void kb_target(const CaseArgs<T>* __restrict
   const CaseArgs<T>* a = args + c;
   d_target<D, T>(global_geo(a->g), global_leaves(a->L), a->vg, gptr(a->tpar), gptr(a->Wn), gptr(a->lam), gptr(a->bad),
                  blockIdx.x - off[c], 0);
+}
+
+template <int D, typename T>
+__global__ __launch_bounds__(LANE_BLOCK) void kb_target_lanes(const CaseArgs<T>* __restrict__ args,
+                                                              const int* __restrict__ off, int ncase) {
+  const int c = find_case(off, ncase, blockIdx.x);
+  const CaseArgs<T>* a = args + c;
+  const int groups = (a->g.nc + 63) / 64, lb = blockIdx.x - off[c];
+  d_target_lanes<D, T>(global_geo(a->g), global_leaves(a->L), a->vg, a->gas, a->dt, gptr(a->F), gptr(a->W), gptr(a->Wn),
+                       gptr(a->q), gptr(a->tpar), gptr(a->lam), reinterpret_cast<double*>(gptr(a->vout)), gptr(a->bad),
+                       a->shares, lb % groups, lb / groups);
+}
+
+template <int D, typename T>
+__global__ __launch_bounds__(64) void kb_target_close(const CaseArgs<T>* __restrict__ args,
+                                                      const int* __restrict__ off, int ncase) {
+  const int c = find_case(off, ncase, blockIdx.x);
+  const CaseArgs<T>* a = args + c;
+  d_target_close<D>(a->g.nc, a->shares, reinterpret_cast<const double*>(gptr(a->vout)), gptr(a->tpar), gptr(a->Wn),
+                    gptr(a->lam), gptr(a->bad), blockIdx.x - off[c]);
 }
 
 // TWO: two leaves' loads in flight per thread (the batched tuner picks)

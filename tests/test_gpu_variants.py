@@ -7,7 +7,7 @@ from workloads import fields as F
 from workloads import meshes as MM
 
 from test_gpu_implicit import dia_pair
-from test_gpu_parity import make_pair, random_tree, rel
+from test_gpu_parity import fieldrel, make_pair, random_tree, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +48,44 @@ def test_repeated_colour_turns(avs, nx, ny, diatomic):
         o.step_implicit(2, 3, 3)
         v, W = cs.get_state()
     assert rel(v, o.phi) < 1e-11 and rel(W, o.W) < 1e-11
+
+
+@pytest.mark.parametrize("nx,ny,base,levels,prec", [
+    (9, 7, 8, 2, 0),      # one lane short of a group of 64 cells
+    (8, 8, 8, 2, 0),      # exactly one group
+    (13, 5, 8, 2, 0),     # one cell in the second group
+    (3, 2, 72, 0, 0),     # largest tables of the 64-lane form, leaves in several shares
+    (3, 2, 73, 0, 0),     # just beyond: a workgroup per cell
+    (5, 4, 16, 3, 1),     # FP32
+])
+def test_lane_groups(avs, nx, ny, base, levels, prec):
+    """A lane per cell and per face: group remainders, leaf shares, both
+    sides of the table limit; two explicit steps with walls (FP64 to 1e-12
+    per step as the other step tests; FP32 1e-5 of the field)."""
+    mesh = MM.box2d(nx, ny, periodic=(True, False), sides=dict(bottom=0, top=0),
+                    bcs=[(MM.WALL, (1.0, 0.1, 0.0, 1.1))])
+    vs = dict(dim=2, lo=(-6, -6), hi=(6, 6), base=(base, base), max_level=levels)
+    prim = F.perturbed_uniform(mesh['ncells'], 2, 21, amp=0.1, uamp=0.3)
+    cs, o = make_pair(avs, mesh, vs, GAS, F._cfl_dt(mesh, 0.5, (6.0, 6.0)), prim, tree=random_tree(vs, 22, levels),
+                      noise=0.02, seed=23, precision=prec)
+    cs.step(2)
+    o.step(2)
+    v, W = cs.get_state()
+    if prec:
+        assert fieldrel(W, o.W) < 1e-5 and fieldrel(v, o.phi) < 1e-5
+    else:
+        assert rel(v, o.phi) < 2e-12 and rel(W, o.W) < 2e-12
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_lane_groups_3d(avs, prec):
+    mesh = MM.box3d(5, 3, 5)
+    vs = dict(dim=3, lo=(-5.0,) * 3, hi=(5.0,) * 3, base=(5, 5, 5), max_level=2)
+    prim = F.perturbed_uniform(mesh['ncells'], 3, 31, amp=0.1, uamp=0.3)
+    cs, o = make_pair(avs, mesh, vs, GAS, F._cfl_dt(mesh, 0.5, (5.0,) * 3), prim, tree=random_tree(vs, 32, 2),
+                      noise=0.02, seed=33, precision=prec)
+    cs.step(1)
+    o.step(1)
+    v, W = cs.get_state()
+    tol = 1e-5 if prec else 1e-12
+    assert fieldrel(v, o.phi) < tol and fieldrel(W, o.W) < tol
