@@ -456,6 +456,13 @@ int target_shares(const avs_ctx* ctx) {
   return lane_shares<D, T>(ctx->nc, ctx->nleaf[ctx->lcur], ctx->vg.numax, nacc, most);
 }
 
+// The same for the interface stage.
+template <int D, typename T>
+int face_shares(const avs_ctx* ctx) {
+  const int64_t most = (int64_t)(ctx->vdf_buf_bytes / (round_up(std::max(ctx->nf, 1), 64) * (D + 2) * sizeof(double)));
+  return lane_shares<D, T>(ctx->nf, ctx->nleaf[ctx->lcur], ctx->vg.numax, D + 2, most);
+}
+
 // W^{n+1} from the fluxes F, the target records and the closure's lambda.
 template <int D, typename T>
 avs_status launch_target(avs_ctx* ctx) {
@@ -513,7 +520,19 @@ avs_status launch_interfaces(avs_ctx* ctx) {
                                                             ctx->fmom, ctx->nchs, chunk);
     CKL();
   }
-  {
+  if (ctx->nf > 0 && lane_form<D, T>(nu)) {
+    ProfScope ps(ctx, K_FACE_EQFLUX);
+    const int shares = face_shares<D, T>(ctx), groups = (ctx->nf + 63) / 64;
+    double* part = (double*)ctx->vdf[ctx->cur ^ 1];
+    k_face_lanes<D, T><<<dim3(groups, shares), LANE_BLOCK, lane_face_lds<D, T>(nu), ctx->stream>>>(
+        ctx->geo, L, ctx->vg, ctx->gas, ctx->h, ctx->bden, ctx->bfin, ctx->fmom, ctx->nchs, nch, ctx->fpar, ctx->F, part,
+        ctx->bad);
+    CKL();
+    if (shares > 1) {
+      k_face_close<D><<<groups, 64, 0, ctx->stream>>>(ctx->geo, shares, part, ctx->fpar, ctx->F);
+      CKL();
+    }
+  } else {
     ProfScope ps(ctx, K_FACE_EQFLUX);
     k_face_eq<D, T><<<(ctx->nf + face_batch<D>() - 1) / face_batch<D>(), BLOCK, (size_t)face_batch<D>() * D * nu * sizeof(T),
                       ctx->stream>>>(
@@ -771,6 +790,7 @@ hipError_t raise_lds() {
                        (const void*)k_face_eq<D, T>,      (const void*)kb_face_eq<D, T>,
                        (const void*)k_target<D, T>,       (const void*)kb_target<D, T>,
                        (const void*)k_target_lanes<D, T>, (const void*)kb_target_lanes<D, T>,
+                       (const void*)k_face_lanes<D, T>,   (const void*)kb_face_lanes<D, T>,
                        (const void*)k_remap_correct<D, T>, (const void*)kb_remap_correct<D, T>,
                        (const void*)k_init_vdf<D, T>};
   for (const void* fn : fns) {
@@ -892,6 +912,7 @@ CaseArgs<T> case_args(avs_ctx* c, int flip, int chunk) {
   a.nchs = c->nchs;
   a.chunk = chunk;
   a.gx = (int)round_up(c->nc, 8);
+  a.fshares = c->D == 2 ? face_shares<2, T>(c) : face_shares<3, T>(c);
   a.shares = c->D == 2 ? target_shares<2, T>(c) : target_shares<3, T>(c);
   return a;
 }
@@ -914,7 +935,9 @@ avs_status batch_upload(avs_batch* b) {
     const int gx = (int)round_up(c->nc, 8);
     const int fb = c->D == 2 ? face_batch<2>() : face_batch<3>();
     const bool lanes = c->D == 2 ? lane_form<2, T>(c->vg.numax) : lane_form<3, T>(c->vg.numax);
-    const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), (c->nf + fb - 1) / fb,
+    const int fg = (c->nf + 63) / 64;
+    const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), lanes ? 0 : (c->nf + fb - 1) / fb,
+                           lanes ? fg * args[i].fshares : 0, lanes && args[i].fshares > 1 ? fg : 0,
                            lanes ? 0 : (c->nc + BLOCK - 1) / BLOCK, lanes ? 0 : c->nc, lanes ? (c->nc + 63) / 64 * args[i].shares : 0,
                            lanes && args[i].shares > 1 ? (c->nc + 63) / 64 : 0, gx};
     for (int k = 0; k < BK_N; ++k) off[k * (n + 1) + i + 1] = off[k * (n + 1) + i] + cnt[k];
@@ -941,9 +964,20 @@ avs_status batch_launch(avs_batch* b, int nsteps) {
     const CaseArgs<T>* a = args + (s & 1) * n;
     kb_passA<D, T><<<b->nblk[BK_PASSA], passA_threads<D>(), 0, b->stream>>>(a, off + BK_PASSA * (n + 1), n);
     CKL();
-    kb_face_eq<D, T><<<b->nblk[BK_FACEQ], BLOCK, (size_t)face_batch<D>() * D * numax * sizeof(T), b->stream>>>(
-        a, off + BK_FACEQ * (n + 1), n);
-    CKL();
+    if (b->nblk[BK_FACEQ]) {
+      kb_face_eq<D, T><<<b->nblk[BK_FACEQ], BLOCK, (size_t)face_batch<D>() * D * numax * sizeof(T), b->stream>>>(
+          a, off + BK_FACEQ * (n + 1), n);
+      CKL();
+    }
+    if (b->nblk[BK_LFACE]) {
+      kb_face_lanes<D, T><<<b->nblk[BK_LFACE], LANE_BLOCK, lane_face_lds<D, T>(lane_numax), b->stream>>>(
+          a, off + BK_LFACE * (n + 1), n);
+      CKL();
+    }
+    if (b->nblk[BK_LFCLOSE]) {
+      kb_face_close<D, T><<<b->nblk[BK_LFCLOSE], 64, 0, b->stream>>>(a, off + BK_LFCLOSE * (n + 1), n);
+      CKL();
+    }
     if (b->nblk[BK_TARGET]) {
       kb_macro<D, T><<<b->nblk[BK_MACRO], BLOCK, 0, b->stream>>>(a, off + BK_MACRO * (n + 1), n);
       CKL();

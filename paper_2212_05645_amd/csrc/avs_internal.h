@@ -59,12 +59,13 @@ struct Geo {
 // each cell (or face) and take one leaf at a time read of it.  The leaf is
 // then the same for the whole wave, so its row comes through the scalar
 // cache into scalar registers.
+// 64 bytes: one line of the scalar cache, one load.
 template <int D>
-struct LeafRow {
+struct alignas(64) LeafRow {
   double xi[D];
+  double A, x2h;         // weight, |xi|^2 / 2
   float xf[D];           // xi in FP32
-  int u[D == 2 ? 2 : 3]; // half-finest grid index
-  double A, Ax[D], e, h; // A, A xi, A |xi|^2 / 2, A / 2
+  int u[D];              // half-finest grid index
 };
 
 struct Leaves {

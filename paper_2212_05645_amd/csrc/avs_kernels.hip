@@ -211,7 +211,8 @@ template <int D>
 __device__ __forceinline__ void eq_record(double* par, double rho, const double (&U)[D], double T, const double* q,
                                           const GasP& gas) {
   const double RT = gas.R * T;
-  par[P_COEF] = rho * pow(2.0 * M_PI * RT, -0.5 * D);
+  const double x2 = 2.0 * M_PI * RT;
+  par[P_COEF] = rho / (D == 2 ? x2 : x2 * sqrt(x2));       // (2 pi R T)^(-D/2)
 #pragma unroll
   for (int d = 0; d < 3; ++d) par[P_U + d] = d < D ? U[d] : 0.0;
   par[P_RT] = RT;
@@ -409,12 +410,10 @@ __global__ void k_leaf_geom(int n, int cap, const int* __restrict__ level, const
     r.xi[d] = x;
     r.xf[d] = (float)x;
     r.u[d] = u[d * cap + k];
-    r.Ax[d] = a * x;
     x2 += x * x;
   }
   r.A = a;
-  r.e = 0.5 * a * x2;
-  r.h = 0.5 * a;
+  r.x2h = 0.5 * x2;
   rows[k] = r;
 }
 
@@ -1022,21 +1021,22 @@ __global__ __launch_bounds__(passA_threads<D>(), (passA_waves<D, T>())) void k_p
 // Flux of a raw-moment set through normal n: (n.m1, n.m2, n.e1).
 template <int D>
 __device__ __forceinline__ void raw_flux(const double* m, const double* n, double* F) {
-  F[0] = 0.0;
-  for (int d = 0; d < D; ++d) F[0] += n[d] * m[1 + d];
-  int idx[3][3];
-  int t = 1 + D;
-  for (int d = 0; d < D; ++d)
-    for (int e = d; e < D; ++e) { idx[d][e] = t; idx[e][d] = t; ++t; }
+  constexpr int t2 = 1 + D, e1 = 2 + D + D * (D + 1) / 2;
+  double f0 = 0.0, fe = 0.0;
+#pragma unroll
   for (int d = 0; d < D; ++d) {
+    f0 += n[d] * m[1 + d];
+    fe += n[d] * m[e1 + d];
     double v = 0.0;
-    for (int e = 0; e < D; ++e) v += n[e] * m[idx[d][e]];
+#pragma unroll
+    for (int e = 0; e < D; ++e) {
+      const int a = d < e ? d : e, b = d < e ? e : d;
+      v += n[e] * m[t2 + a * D - a * (a - 1) / 2 + (b - a)];
+    }
     F[1 + d] = v;
   }
-  const int e1 = 2 + D + D * (D + 1) / 2;
-  double v = 0.0;
-  for (int d = 0; d < D; ++d) v += n[d] * m[e1 + d];
-  F[D + 1] = v;
+  F[0] = f0;
+  F[D + 1] = fe;
 }
 
 // ------------------------------------------------------ interface (S5-S8)
@@ -1058,6 +1058,44 @@ __device__ __forceinline__ void raw_flux(const double* m, const double* n, doubl
 #endif
 template <int D>
 constexpr int face_batch() { return D == 2 ? AVS_FACE_BATCH2 : AVS_FACE_BATCH3; }
+
+// Interface state of a raw-moment set m (Eq. w_interface): tau, heat flux
+// relaxed over h at rate Pr/tau, Shakhov record and blend weights into par,
+// raw flux through n into F; false if the state is not physical.
+template <int D>
+__device__ __forceinline__ bool interface_record(const double* m, const double* n, const GasP& gas, double h,
+                                                 double* par, double* F) {
+  const double rho = m[0];
+  double U[D], ke = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) { U[d] = m[1 + d] / rho; ke += U[d] * U[d]; }
+  constexpr int ie = 1 + D + D * (D + 1) / 2;
+  const double E = m[ie];
+  const double T = (E - 0.5 * rho * ke) / (1.5 * rho * gas.R);
+  if (!(rho > 0.0 && T > 0.0)) return false;
+  // q about U from raw moments: e1_d - U_d E - sum_e U_e (m2_de - rho U_d U_e) + |U|^2/2 (m1_d - U_d rho)
+  double q[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    double v = m[ie + 1 + d] - U[d] * E;
+#pragma unroll
+    for (int e = 0; e < D; ++e) {
+      const int a = d < e ? d : e, b = d < e ? e : d;
+      v -= U[e] * (m[1 + D + a * D - a * (a - 1) / 2 + (b - a)] - rho * U[d] * U[e]);
+    }
+    v += 0.5 * ke * (m[1 + d] - U[d] * rho);
+    q[d] = v;
+  }
+  const double tf = tau_of(rho, T, gas);
+  const double qs = tf / (tf + h * gas.Pr);
+#pragma unroll
+  for (int d = 0; d < D; ++d) q[d] *= qs;
+  eq_record<D>(par, rho, U, T, q, gas);
+  par[P_A] = tf / (tf + h);
+  par[P_B] = h / (tf + h);
+  raw_flux<D>(m, n, F);
+  return true;
+}
 
 template <int D, typename R>
 __device__ __forceinline__ void d_face_eq(Geo g, Leaves L, VGrid vg, GasP gas, double h, const double* __restrict__ bden,
@@ -1109,34 +1147,9 @@ __device__ __forceinline__ void d_face_eq(Geo g, Leaves L, VGrid vg, GasP gas, d
       }
       for (int t = 0; t < NM; ++t) m[t] = sm[s][t];
       if (Rc >= 0) {
-        const double rho = m[0];
-        double U[D], ke = 0.0;
-        for (int d = 0; d < D; ++d) { U[d] = m[1 + d] / rho; ke += U[d] * U[d]; }
-        const int ie = 1 + D + D * (D + 1) / 2;
-        const double E = m[ie];
-        const double T = (E - 0.5 * rho * ke) / (1.5 * rho * gas.R);
-        if (!(rho > 0.0 && T > 0.0)) {
+        if (!interface_record<D>(m, n, gas, h, spar[s], sF[s])) {
           atomicMin(bad, g.nc + f);
         } else {
-          // q about U from raw moments: e1_d - U_d E - sum_e U_e (m2_de - rho U_d U_e) + |U|^2/2 (m1_d - U_d rho)
-          int idx[3][3];
-          int t = 1 + D;
-          for (int d = 0; d < D; ++d)
-            for (int e = d; e < D; ++e) { idx[d][e] = t; idx[e][d] = t; ++t; }
-          double q[D];
-          for (int d = 0; d < D; ++d) {
-            double v = m[ie + 1 + d] - U[d] * E;
-            for (int e = 0; e < D; ++e) v -= U[e] * (m[idx[d][e]] - rho * U[d] * U[e]);
-            v += 0.5 * ke * (m[1 + d] - U[d] * rho);
-            q[d] = v;
-          }
-          const double tf = tau_of(rho, T, gas);
-          const double qs = tf / (tf + h * gas.Pr);
-          for (int d = 0; d < D; ++d) q[d] *= qs;
-          eq_record<D>(spar[s], rho, U, T, q, gas);
-          spar[s][P_A] = tf / (tf + h);
-          spar[s][P_B] = h / (tf + h);
-          raw_flux<D>(m, n, sF[s]);
           ok = 1;
         }
       } else {
@@ -1346,7 +1359,7 @@ __global__ __launch_bounds__(BLOCK) void k_target(Geo g, Leaves L, VGrid vg, con
 // across 256 lanes and solve on one thread.  Target measured, workgroup per
 // cell against lane per cell: 4096 cells x 256 leaves FP64 48 + 6 (macro
 // kernel) -> 15 us, 11 880 x 1252 FP32 134 + 7 -> 42 us, 2574 x 4404 FP64
-// 3-D 66 + 8 -> 43 us, 36 864 x 19 972 FP32 3-D 1.81 -> 1.31 ms (bound by
+// 3-D 66 + 8 -> 41 us, 36 864 x 19 972 FP32 3-D 1.81 -> 1.24 ms (bound by
 // VALU issue: about 54 instructions per cell and leaf against 71).
 // The tables of 64 lanes have to fit the LDS: lane_form is the rule.
 constexpr int LANE_WAVES = 16;
@@ -1367,6 +1380,13 @@ template <int D, typename R>
 inline size_t lane_lds(int numax, int nacc) {
   const size_t t = lane_tab_bytes<D, R>(numax), r = (size_t)(LANE_WAVES / 2) * nacc * 64 * sizeof(double);
   return t > r ? t : r;
+}
+
+// The interface stage's: the faces' raw moments wait in the same place.
+template <int D, typename R>
+inline size_t lane_face_lds(int numax) {
+  const size_t t = lane_lds<D, R>(numax, D + 2), m = (size_t)Cfg<D>::NM * 64 * sizeof(double);
+  return t > m ? t : m;
 }
 
 // Leaf shares: a launch has ceil(n / 64) groups of lanes, each able to fill a
@@ -1589,12 +1609,12 @@ __device__ __forceinline__ void d_target_lanes(Geo g, Leaves L, VGrid vg, GasP g
       c[d] = r->xi[d] - U[d];
       c2 = d == 0 ? c[d] * c[d] : fma(c[d], c[d], c2);
     }
-    const double G = Gr;
-    acc[0] = fma(r->A, G, acc[0]);
+    const double aG = r->A * (double)Gr;
+    acc[0] += aG;
 #pragma unroll
-    for (int d = 0; d < D; ++d) acc[1 + d] = fma(r->Ax[d], G, acc[1 + d]);
-    acc[D + 1] = fma(r->e, G, acc[D + 1]);
-    if constexpr (D == 2) acc[D + 1] = fma(r->h, (double)Hr, acc[D + 1]);
+    for (int d = 0; d < D; ++d) acc[1 + d] = fma(r->xi[d], aG, acc[1 + d]);
+    acc[D + 1] = fma(r->x2h, aG, acc[D + 1]);
+    if constexpr (D == 2) acc[D + 1] = fma(0.5 * r->A, (double)Hr, acc[D + 1]);
     gram_acc<D>(acc + N, r->A * (double)gr, c, c2);
   }
   lane_sum<N + NS>(acc, lds_d);
@@ -1653,6 +1673,173 @@ __global__ __launch_bounds__(LANE_BLOCK) void k_target_lanes(Geo g, Leaves L, VG
                                                              double* __restrict__ tpar, double* __restrict__ lam,
                                                              double* __restrict__ part, int* __restrict__ bad) {
   d_target_lanes<D, R>(g, L, vg, gas, dt, F, W, Wn, qcur, tpar, lam, part, bad, gridDim.y, blockIdx.x, blockIdx.y);
+}
+
+// Interface stage (d_face_eq) of 64 faces, one per lane; grid ceil(nf / 64)
+// groups x `shares` of the leaves.  With one share the flux is finished
+// here, else share 0 leaves its raw part in F and the equilibrium sums go to
+// part[share][m][64 groups] for k_face_close.  Against four faces per
+// workgroup: 8320 faces x 256 leaves FP64 38 -> 12 us, 17 930 x 1252 FP32 79
+// -> 55 us, 110 976 x 19 972 FP32 3-D 2.25 -> 2.00 ms (VALU issue: 30
+// instructions per face and leaf).
+template <int D, typename R>
+__device__ __forceinline__ void d_face_lanes(Geo g, Leaves L, VGrid vg, GasP gas, double h,
+                                             const double* __restrict__ bden, const double* __restrict__ bfin,
+                                             const double* __restrict__ fmom, int nchs, int nch,
+                                             double* __restrict__ fpar, double* __restrict__ F,
+                                             double* __restrict__ part, int* __restrict__ bad, int shares, int bx,
+                                             int by) {
+  constexpr int NM = Cfg<D>::NM, N = D + 2;
+  extern __shared__ double lds_d[];
+  R* tab = reinterpret_cast<R*>(lds_d);
+  __shared__ double spar[NPAR][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int f = bx * 64 + lane;
+  const bool valid = f < g.nf;
+  // raw moments of each interface VDF: the partials of pass A, chunk by chunk,
+  // L side then R side (a boundary face has its interior side only); they
+  // wait in the tables' place
+  double* sm = lds_d;
+  for (int t = threadIdx.x; t < 64 * NM; t += LANE_BLOCK) {
+    const int s = t / NM, m = t - s * NM, ff = bx * 64 + s;
+    double v = 0.0;
+    if (ff < g.nf) {
+      const double* p0 = fmom + (size_t)ff * 2 * nchs * NM + m;
+      const double* p1 = p0 + (size_t)nchs * NM;
+      const bool two = g.f_R[ff] >= 0;
+      for (int c = 0; c < nch; ++c) {
+        v += p0[(size_t)c * NM];
+        if (two) v += p1[(size_t)c * NM];
+      }
+    }
+    sm[m * 64 + s] = v;
+  }
+  __syncthreads();
+  double Fr[N], n[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) n[d] = valid ? g.f_nrm[(size_t)f * D + d] : 0.0;
+  bool ok = false;
+  if (wave == 0) {
+    double par[NPAR], m[NM];
+#pragma unroll
+    for (int t = 0; t < NPAR; ++t) par[t] = 0.0;
+#pragma unroll
+    for (int t = 0; t < NM; ++t) m[t] = sm[t * 64 + lane];
+#pragma unroll
+    for (int t = 0; t < N; ++t) Fr[t] = 0.0;
+    const int Rc = valid ? g.f_R[f] : 0;
+    if (valid && Rc >= 0) {
+      ok = interface_record<D>(m, n, gas, h, par, Fr);
+      if (!ok && by == 0) atomicMin(bad, g.nc + f);
+      if (!ok) {
+#pragma unroll
+        for (int t = 0; t < NPAR; ++t) par[t] = 0.0;
+      }
+      if (ok && by == 0) {
+#pragma unroll
+        for (int t = 0; t < NPAR; ++t) fpar[(size_t)f * NPAR + t] = par[t];
+      }
+    } else if (valid && by == 0) {
+      const int bc = -1 - Rc;
+      raw_flux<D>(m, n, Fr);
+      const double* fin = bfin + (size_t)f * N;
+      double scale = 1.0;
+      if (g.bc_kind[bc] == 0) {
+        scale = Fr[0] / bden[f];
+        fpar[(size_t)f * NPAR] = scale;
+      }
+#pragma unroll
+      for (int t = 0; t < N; ++t) F[(size_t)f * N + t] = Fr[t] + scale * fin[t];
+    }
+    // lanes without an interior face carry a zero record (a zero Maxwellian)
+#pragma unroll
+    for (int t = 0; t < NPAR; ++t) spar[t][lane] = par[t];
+  }
+  __syncthreads();
+  lane_tables<D, R>(tab, spar, vg);
+  R rp[NPAR];
+#pragma unroll
+  for (int t = 0; t < NPAR; ++t) rp[t] = (R)spar[t][lane];
+  __syncthreads();
+  double acc[N];
+#pragma unroll
+  for (int t = 0; t < N; ++t) acc[t] = 0.0;
+  const RowPtr<D> rows = leaf_rows<D>(L);
+  const R* tl = tab + lane;
+  const int per = (L.n + shares - 1) / shares, k1 = min(L.n, (by + 1) * per);
+#pragma unroll 4
+  for (int k = by * per + wave; k < k1; k += LANE_WAVES) {
+    const RowPtr<D> r = rows + k;
+    R gr = rp[P_COEF];
+    R xr[D];
+    double sn = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      gr *= tl[(d * vg.numax + r->u[d]) * 64];
+      xr[d] = sizeof(R) == 4 ? (R)r->xf[d] : (R)r->xi[d];
+      sn = d == 0 ? r->xi[0] * n[0] : fma(r->xi[d], n[d], sn);
+    }
+    R G, H;
+    shakhov_r<D, R>(rp, gr, xr, G, H);
+    const double sA = sn * r->A, aG = sA * (double)G;
+    acc[0] += aG;
+#pragma unroll
+    for (int d = 0; d < D; ++d) acc[1 + d] = fma(r->xi[d], aG, acc[1 + d]);
+    acc[D + 1] = fma(r->x2h, aG, acc[D + 1]);
+    if constexpr (D == 2) acc[D + 1] = fma(0.5 * sA, (double)H, acc[D + 1]);
+  }
+  lane_sum<N>(acc, lds_d);
+  if (wave != 0 || !ok) return;
+  const double a = spar[P_A][lane], b = spar[P_B][lane];
+  if (shares > 1) {
+    const size_t rows64 = (size_t)((g.nf + 63) / 64) * 64;
+#pragma unroll
+    for (int t = 0; t < N; ++t) part[((size_t)by * N + t) * rows64 + f] = acc[t];
+    if (by == 0) {
+#pragma unroll
+      for (int t = 0; t < N; ++t) F[(size_t)f * N + t] = a * Fr[t];
+    }
+    return;
+  }
+#pragma unroll
+  for (int t = 0; t < N; ++t) F[(size_t)f * N + t] = a * Fr[t] + b * acc[t];
+}
+
+template <int D, typename R>
+__global__ __launch_bounds__(LANE_BLOCK) void k_face_lanes(Geo g, Leaves L, VGrid vg, GasP gas, double h,
+                                                           const double* __restrict__ bden,
+                                                           const double* __restrict__ bfin,
+                                                           const double* __restrict__ fmom, int nchs, int nch,
+                                                           double* __restrict__ fpar, double* __restrict__ F,
+                                                           double* __restrict__ part, int* __restrict__ bad) {
+  d_face_lanes<D, R>(g, L, vg, gas, h, bden, bfin, fmom, nchs, nch, fpar, F, part, bad, gridDim.y, blockIdx.x,
+                     blockIdx.y);
+}
+
+// F += b sum of the shares' equilibrium sums, interior faces with a physical
+// state (b of a face without one is never read: the step has failed).
+template <int D>
+__device__ __forceinline__ void d_face_close(const Geo& g, int shares, const double* __restrict__ part,
+                                             const double* __restrict__ fpar, double* __restrict__ F, int bx) {
+  constexpr int N = D + 2;
+  const int f = bx * 64 + threadIdx.x;
+  if (f >= g.nf || g.f_R[f] < 0) return;
+  const size_t rows64 = (size_t)((g.nf + 63) / 64) * 64;
+  const double b = fpar[(size_t)f * NPAR + P_B];
+  double acc[N];
+#pragma unroll
+  for (int t = 0; t < N; ++t) acc[t] = 0.0;
+  for (int s = 0; s < shares; ++s)
+#pragma unroll
+    for (int t = 0; t < N; ++t) acc[t] += part[((size_t)s * N + t) * rows64 + f];
+#pragma unroll
+  for (int t = 0; t < N; ++t) F[(size_t)f * N + t] += b * acc[t];
+}
+
+template <int D>
+__global__ __launch_bounds__(64) void k_face_close(Geo g, int shares, const double* __restrict__ part,
+                                                   const double* __restrict__ fpar, double* __restrict__ F) {
+  d_face_close<D>(g, shares, part, fpar, F, blockIdx.x);
 }
 
 // -------------------------------------------------- pass C (S6, S7, S10)
@@ -2477,10 +2664,10 @@ struct CaseArgs {
   double* fmom;    // face-moment partials of pass A [nf][2][nchs][NM]
   int nchs;        // their chunk stride
   int chunk, gx;   // pass A: leaves per workgroup, round_up(nc, 8)
-  int shares;      // leaf shares of the 64-lane target
+  int shares, fshares;   // leaf shares of the 64-lane target and interface stage
 };
 
-enum { BK_PASSA, BK_FACEQ, BK_MACRO, BK_TARGET, BK_LTARGET, BK_LCLOSE, BK_PASSC, BK_N };
+enum { BK_PASSA, BK_FACEQ, BK_LFACE, BK_LFCLOSE, BK_MACRO, BK_TARGET, BK_LTARGET, BK_LCLOSE, BK_PASSC, BK_N };
 
 // Largest c with off[c] <= b (off has ncase + 1 increasing entries).
 __device__ __forceinline__ int find_case(const int* __restrict__ off, int ncase, int b) {
@@ -2534,6 +2721,26 @@ __global__ __launch_bounds__(BLOCK) void kb_face_eq(const CaseArgs<T>* __restric
   d_face_eq<D, T>(global_geo(a->g), global_leaves(a->L), a->vg, a->gas, a->h, gptr(a->bden), gptr(a->bfin),
                   gptr(a->fmom), a->nchs, (a->L.n + a->chunk - 1) / a->chunk, gptr(a->fpar), gptr(a->F),
                   gptr(a->bad), blockIdx.x - off[c]);
+}
+
+template <int D, typename T>
+__global__ __launch_bounds__(LANE_BLOCK) void kb_face_lanes(const CaseArgs<T>* __restrict__ args,
+                                                            const int* __restrict__ off, int ncase) {
+  const int c = find_case(off, ncase, blockIdx.x);
+  const CaseArgs<T>* a = args + c;
+  const int groups = (a->g.nf + 63) / 64, lb = blockIdx.x - off[c];
+  d_face_lanes<D, T>(global_geo(a->g), global_leaves(a->L), a->vg, a->gas, a->h, gptr(a->bden), gptr(a->bfin),
+                     gptr(a->fmom), a->nchs, (a->L.n + a->chunk - 1) / a->chunk, gptr(a->fpar), gptr(a->F),
+                     reinterpret_cast<double*>(gptr(a->vout)), gptr(a->bad), a->fshares, lb % groups, lb / groups);
+}
+
+template <int D, typename T>
+__global__ __launch_bounds__(64) void kb_face_close(const CaseArgs<T>* __restrict__ args, const int* __restrict__ off,
+                                                    int ncase) {
+  const int c = find_case(off, ncase, blockIdx.x);
+  const CaseArgs<T>* a = args + c;
+  d_face_close<D>(global_geo(a->g), a->fshares, reinterpret_cast<const double*>(gptr(a->vout)), gptr(a->fpar),
+                  gptr(a->F), blockIdx.x - off[c]);
 }
 
 template <int D, typename T>
