@@ -554,8 +554,13 @@ avs_status launch_step(avs_ctx* ctx, bool last_residual) {
   if (avs_status st = launch_target<D, T>(ctx)) return st;
   {
     ProfScope ps(ctx, K_PASSC);
-    k_passC<D, T><<<(unsigned)round_up(ctx->nc, 8), BLOCK, (size_t)(MAXF + 1) * D * nu * sizeof(T), ctx->stream>>>(
-        ctx->geo, L, ctx->vg, vin, (const T*)ctx->fv, vout, ctx->fpar, ctx->tpar, ctx->lam, ctx->mom, ctx->q);
+    const size_t shm = passC_tab<D, T>(nu);
+    if (passC_wave_form<D, T>(L.n, nu))
+      k_passC<D, T, 64><<<(unsigned)round_up(ctx->nc, 8), 64, shm, ctx->stream>>>(
+          ctx->geo, L, ctx->vg, vin, (const T*)ctx->fv, vout, ctx->fpar, ctx->tpar, ctx->lam, ctx->mom, ctx->q);
+    else
+      k_passC<D, T, BLOCK><<<(unsigned)round_up(ctx->nc, 8), BLOCK, shm, ctx->stream>>>(
+          ctx->geo, L, ctx->vg, vin, (const T*)ctx->fv, vout, ctx->fpar, ctx->tpar, ctx->lam, ctx->mom, ctx->q);
     CKL();
   }
   if (last_residual) {
@@ -785,7 +790,7 @@ hipError_t raise_lds() {
   static bool done = false;
   if (done) return hipSuccess;
   const int b = (int)kLdsMax;
-  const void* fns[] = {(const void*)k_passC<D, T>,        (const void*)k_passC_res<D, T>,
+  const void* fns[] = {(const void*)k_passC<D, T, BLOCK>, (const void*)k_passC_res<D, T>,
                        (const void*)kb_passC<D, T, true>, (const void*)kb_passC<D, T, false>,
                        (const void*)k_face_eq<D, T>,      (const void*)kb_face_eq<D, T>,
                        (const void*)k_target<D, T>,       (const void*)kb_target<D, T>,
@@ -935,11 +940,12 @@ avs_status batch_upload(avs_batch* b) {
     const int gx = (int)round_up(c->nc, 8);
     const int fb = c->D == 2 ? face_batch<2>() : face_batch<3>();
     const bool lanes = c->D == 2 ? lane_form<2, T>(c->vg.numax) : lane_form<3, T>(c->vg.numax);
+    const bool wavec = c->D == 2 ? passC_wave_form<2, T>(nl, c->vg.numax) : passC_wave_form<3, T>(nl, c->vg.numax);
     const int fg = (c->nf + 63) / 64;
     const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), lanes ? 0 : (c->nf + fb - 1) / fb,
                            lanes ? fg * args[i].fshares : 0, lanes && args[i].fshares > 1 ? fg : 0,
                            lanes ? 0 : (c->nc + BLOCK - 1) / BLOCK, lanes ? 0 : c->nc, lanes ? (c->nc + 63) / 64 * args[i].shares : 0,
-                           lanes && args[i].shares > 1 ? (c->nc + 63) / 64 : 0, gx};
+                           lanes && args[i].shares > 1 ? (c->nc + 63) / 64 : 0, wavec ? 0 : gx, wavec ? gx : 0};
     for (int k = 0; k < BK_N; ++k) off[k * (n + 1) + i + 1] = off[k * (n + 1) + i] + cnt[k];
   }
   for (int k = 0; k < BK_N; ++k) b->nblk[k] = off[k * (n + 1) + n];
@@ -954,10 +960,14 @@ avs_status batch_launch(avs_batch* b, int nsteps) {
   const int n = (int)b->cases.size();
   const CaseArgs<T>* args = reinterpret_cast<const CaseArgs<T>*>(b->ws);
   const int* off = reinterpret_cast<const int*>(b->ws + batch_args_bytes(n));
-  int numax = 0, lane_numax = 0;      // over all members; over those in the 64-lane form
+  // over all members; over those in the 64-lane forms; over those whose
+  // tables allow the wave form of pass C (whatever their leaf counts are now:
+  // a captured launch keeps its LDS size)
+  int numax = 0, lane_numax = 0, wave_numax = 0;
   for (avs_ctx* c : b->cases) {
     numax = std::max(numax, c->vg.numax);
     if (lane_form<D, T>(c->vg.numax)) lane_numax = std::max(lane_numax, c->vg.numax);
+    if (passC_tab<D, T>(c->vg.numax) <= PASSC_WAVE_TAB) wave_numax = std::max(wave_numax, c->vg.numax);
   }
   constexpr int MAXF = Cfg<D>::MAXF;
   for (int s = 0; s < nsteps; ++s) {
@@ -993,13 +1003,20 @@ avs_status batch_launch(avs_batch* b, int nsteps) {
       kb_target_close<D, T><<<b->nblk[BK_LCLOSE], 64, 0, b->stream>>>(a, off + BK_LCLOSE * (n + 1), n);
       CKL();
     }
-    const size_t shc = (size_t)(MAXF + 1) * D * numax * sizeof(T);
+    const size_t shc = (size_t)(MAXF + 1) * D * sizeof(T);
     const bool two = b->passc_two < 0 ? passc_two_leaves<D, T>() : b->passc_two == 1;
-    if (two)
-      kb_passC<D, T, true><<<b->nblk[BK_PASSC], BLOCK, shc, b->stream>>>(a, off + BK_PASSC * (n + 1), n);
-    else
-      kb_passC<D, T, false><<<b->nblk[BK_PASSC], BLOCK, shc, b->stream>>>(a, off + BK_PASSC * (n + 1), n);
-    CKL();
+    if (b->nblk[BK_PASSC]) {
+      const int* o = off + BK_PASSC * (n + 1);
+      if (two) kb_passC<D, T, true><<<b->nblk[BK_PASSC], BLOCK, shc * numax, b->stream>>>(a, o, n);
+      else kb_passC<D, T, false><<<b->nblk[BK_PASSC], BLOCK, shc * numax, b->stream>>>(a, o, n);
+      CKL();
+    }
+    if (b->nblk[BK_WPASSC]) {
+      const int* o = off + BK_WPASSC * (n + 1);
+      if (two) kb_passC<D, T, true, 64><<<b->nblk[BK_WPASSC], 64, shc * wave_numax, b->stream>>>(a, o, n);
+      else kb_passC<D, T, false, 64><<<b->nblk[BK_WPASSC], 64, shc * wave_numax, b->stream>>>(a, o, n);
+      CKL();
+    }
   }
   return AVS_OK;
 }

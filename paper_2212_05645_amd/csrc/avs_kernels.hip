@@ -189,13 +189,13 @@ __device__ __forceinline__ void shakhov(const double* par, double g, const doubl
 // Compute-type variants used by the sweep kernels: R = double in the FP64
 // form, float in the FP32 form (records stay FP64 in memory and are
 // converted once per workgroup).
-template <int D, typename R>
+template <int D, typename R, int NT = BLOCK>
 __device__ __forceinline__ void build_tab_r(R* tab, const double* par, const VGrid& vg) {
   const double i2rt = par[P_I2RT];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     const double x0 = vg.x0[d], hh = vg.hh[d], U = par[P_U + d];
-    for (int u = threadIdx.x; u < vg.numax; u += BLOCK) {
+    for (int u = threadIdx.x; u < vg.numax; u += NT) {
       const double c = (x0 + u * hh) - U;
       tab[d * vg.numax + u] = (R)exp(-(c * c) * i2rt);
     }
@@ -1923,7 +1923,14 @@ struct LeafIn {
 // With RES set, the kernel stores the explicit increment of the implicit
 // micro system instead, (dt/tau~)(g~ - phi^n) - (dt/V) sum_f sigma A xi.n
 // phi_f (Eq. SGS_phi's right-hand side times dt/V), and skips the moments.
-template <int D, typename T, bool RES = false, bool TWO = passc_two_leaves<D, T>()>
+//
+// NT threads per cell.  A cell's set-up (a chain of dependent loads, the
+// exponential tables, the records) takes the same time for one wave as for
+// four; with few leaves it is most of the kernel, and one wave per cell
+// (passC_wave_form) has four times as many cells at it at once; it also
+// issues the first leaf's loads ahead of the tables (in the other form the
+// registers that takes cost 3-D a wave per SIMD).
+template <int D, typename T, bool RES = false, bool TWO = passc_two_leaves<D, T>(), int NT = BLOCK>
 __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __restrict__ vin,
                                         const T* __restrict__ fv, T* __restrict__ vout,
                                         const double* __restrict__ fpar, const double* __restrict__ tpar,
@@ -1933,10 +1940,11 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
   extern __shared__ double lds_d[];
   T* lds = reinterpret_cast<T*>(lds_d);
   __shared__ double red[4 * (N + D)];
+  __shared__ double dpar[(MAXF + 1) * NPAR];
   __shared__ T spar[(MAXF + 1) * NPAR];
   __shared__ double snrm[MAXF][D];
   __shared__ T snrt[MAXF][D];
-  __shared__ int sface[MAXF], snbr[MAXF];
+  __shared__ int snbr[MAXF];
   __shared__ T ssa[MAXF], ssc[MAXF];
   __shared__ T slam[N];
   const int i = xcd_cell(g, bx);
@@ -1945,7 +1953,7 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
   const int nu = vg.numax;
   const size_t cs = (size_t)g.nc * L.ld;
   const size_t fs = (size_t)g.nf * L.ld;
-  for (int t = threadIdx.x; t < (MAXF + 1) * NPAR; t += BLOCK) {
+  for (int t = threadIdx.x; t < (MAXF + 1) * NPAR; t += NT) {
     const int s = t / NPAR, m = t - s * NPAR;
     double v = 0.0;
     if (s < MAXF) {
@@ -1953,12 +1961,12 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
     } else {
       v = tpar[(size_t)i * NPAR + m];
     }
+    dpar[t] = v;
     spar[t] = (T)v;
   }
   if (threadIdx.x < MAXF) {
     const int s = threadIdx.x;
     const int f = s < ns ? g.s_face[i * MAXF + s] : 0;
-    sface[s] = f;
     snbr[s] = s < ns ? g.s_nbr[i * MAXF + s] : -1;
     ssa[s] = s < ns ? (T)g.s_sigA[i * MAXF + s] : (T)0;
     // wall: density ratio of the incoming Maxwellian (first record slot of a
@@ -1987,12 +1995,27 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
     vrow[p] = vin + p * cs + (size_t)i * L.ld;
     orow[p] = vout + p * cs + (size_t)i * L.ld;
   }
+  auto load = [&](int k, LeafIn<D, T>& x) {
+    const unsigned ko = (unsigned)k * (unsigned)sizeof(T);
+    leaf_load<D>(L, k, x.xi, x.A, x.u);
+#pragma unroll
+    for (int p = 0; p < P; ++p) x.phi[p] = at_(vrow[p], ko);
+    // unconditional, so that all rows of the leaf are in flight together (a
+    // slot beyond the cell's faces reads face 0 and is never used)
+#pragma unroll
+    for (int s = 0; s < MAXF; ++s)
+#pragma unroll
+      for (int p = 0; p < P; ++p) x.row[s][p] = at_(frow[s][p], ko);
+  };
+  constexpr bool EARLY = NT == 64;
+  LeafIn<D, T> x0;
+  if (EARLY && (int)threadIdx.x < L.n) load(threadIdx.x, x0);
   __syncthreads();
 #pragma unroll
   for (int s = 0; s < MAXF; ++s) {
-    if (s < ns && snbr[s] >= 0) build_tab_r<D, T>(lds + s * D * nu, fpar + (size_t)sface[s] * NPAR, vg);
+    if (s < ns && snbr[s] >= 0) build_tab_r<D, T, NT>(lds + s * D * nu, dpar + s * NPAR, vg);
   }
-  build_tab_r<D, T>(lds + MAXF * D * nu, tpar + (size_t)i * NPAR, vg);
+  build_tab_r<D, T, NT>(lds + MAXF * D * nu, dpar + MAXF * NPAR, vg);
   __syncthreads();
   const T* tp = spar + MAXF * NPAR;
   // the unrolled face loop in 3-D and FP32 (2-D FP64, bound by HBM, is no
@@ -2006,18 +2029,6 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
 #pragma unroll
   for (int m = 0; m < N + D; ++m) acc[m] = 0.0;
 
-  auto load = [&](int k, LeafIn<D, T>& x) {
-    const unsigned ko = (unsigned)k * (unsigned)sizeof(T);
-    leaf_load<D>(L, k, x.xi, x.A, x.u);
-#pragma unroll
-    for (int p = 0; p < P; ++p) x.phi[p] = at_(vrow[p], ko);
-    // unconditional, so that all rows of the leaf are in flight together (a
-    // slot beyond the cell's faces reads face 0 and is never used)
-#pragma unroll
-    for (int s = 0; s < MAXF; ++s)
-#pragma unroll
-      for (int p = 0; p < P; ++p) x.row[s][p] = at_(frow[s][p], ko);
-  };
   auto process = [&](int k, const LeafIn<D, T>& x) {
     T xr[D];
 #pragma unroll
@@ -2137,38 +2148,57 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
   };
 
   if constexpr (!TWO) {
-    for (int k = threadIdx.x; k < L.n; k += BLOCK) {
-      LeafIn<D, T> x;
-      load(k, x);
-      process(k, x);
+    for (int k = threadIdx.x; k < L.n; k += NT) {
+      if (!EARLY || k != (int)threadIdx.x) load(k, x0);
+      process(k, x0);
     }
   } else {
-    LeafIn<D, T> x0, x1;
-    int k = threadIdx.x;
-    if (k < L.n) load(k, x0);
-    for (; k < L.n; k += 2 * BLOCK) {
-      if (k + BLOCK < L.n) load(k + BLOCK, x1);
+    LeafIn<D, T> x1;
+    if (!EARLY && (int)threadIdx.x < L.n) load(threadIdx.x, x0);
+    for (int k = threadIdx.x; k < L.n; k += 2 * NT) {
+      if (k + NT < L.n) load(k + NT, x1);
       process(k, x0);
-      if (k + BLOCK >= L.n) break;
-      if (k + 2 * BLOCK < L.n) load(k + 2 * BLOCK, x0);
-      process(k + BLOCK, x1);
+      if (k + NT >= L.n) break;
+      if (k + 2 * NT < L.n) load(k + 2 * NT, x0);
+      process(k + NT, x1);
     }
   }
   if constexpr (RES) return;
-  block_sum<N + D>(acc, red);
-  if (threadIdx.x == 0) {
-    for (int m = 0; m < N; ++m) mom[(size_t)i * N + m] = acc[m];
-    for (int d = 0; d < D; ++d) qout[(size_t)i * D + d] = acc[N + d];
+  if constexpr (NT == 64) {
+    int m;
+    const double v = wave_totals<N + D>(acc, m);
+    if (m < N) mom[(size_t)i * N + m] = v;
+    else if (m < N + D) qout[(size_t)i * D + m - N] = v;
+  } else {
+    block_sum<N + D>(acc, red);
+    if (threadIdx.x == 0) {
+      for (int m = 0; m < N; ++m) mom[(size_t)i * N + m] = acc[m];
+      for (int d = 0; d < D; ++d) qout[(size_t)i * D + d] = acc[N + d];
+    }
   }
 }
 
+// One wave per cell where the leaves are few and the cell's tables small
+// enough for many such workgroups in a CU's LDS.  Measured, four waves / one:
+// 4096 cells x 256 leaves FP64 (2.5 KiB of tables) 53 / 32 us; 11 880 x 1252
+// FP32 (5 KiB) 157 / 128; 3840 x 1200 FP32 3-D (5.3 KiB) 79 / 71, x 2400
+// 115 / 115; 4608 x 300 FP32 (10 KiB) 44 / 37, x 600 53 / 52, x 1200 66 / 79.
 template <int D, typename T>
-__global__ __launch_bounds__(BLOCK, (waves_hint<D, T>())) void k_passC(Geo g, Leaves L, VGrid vg, const T* __restrict__ vin,
+constexpr size_t passC_tab(int numax) { return (size_t)(Cfg<D>::MAXF + 1) * D * numax * sizeof(T); }
+constexpr size_t PASSC_WAVE_TAB = 12 * 1024;
+template <int D, typename T>
+inline bool passC_wave_form(int nleaf, int numax) {
+  const size_t tab = passC_tab<D, T>(numax);
+  return (tab <= 6 * 1024 && nleaf <= 1536) || (tab <= PASSC_WAVE_TAB && nleaf <= 512);
+}
+
+template <int D, typename T, int NT>
+__global__ __launch_bounds__(NT, (waves_hint<D, T>())) void k_passC(Geo g, Leaves L, VGrid vg, const T* __restrict__ vin,
                                                      const T* __restrict__ fv, T* __restrict__ vout,
                                                      const double* __restrict__ fpar, const double* __restrict__ tpar,
                                                      const double* __restrict__ lam, double* __restrict__ mom,
                                                      double* __restrict__ qout) {
-  d_passC<D, T>(g, L, vg, vin, fv, vout, fpar, tpar, lam, mom, qout, blockIdx.x);
+  d_passC<D, T, false, passc_two_leaves<D, T>(), NT>(g, L, vg, vin, fv, vout, fpar, tpar, lam, mom, qout, blockIdx.x);
 }
 
 // ----------------------------------------------- boundary Maxwellians (S7)
@@ -2719,7 +2749,7 @@ struct CaseArgs {
   int shares, fshares;   // leaf shares of the 64-lane target and interface stage
 };
 
-enum { BK_PASSA, BK_FACEQ, BK_LFACE, BK_LFCLOSE, BK_MACRO, BK_TARGET, BK_LTARGET, BK_LCLOSE, BK_PASSC, BK_N };
+enum { BK_PASSA, BK_FACEQ, BK_LFACE, BK_LFCLOSE, BK_MACRO, BK_TARGET, BK_LTARGET, BK_LCLOSE, BK_PASSC, BK_WPASSC, BK_N };
 
 // Largest c with off[c] <= b (off has ncase + 1 increasing entries).
 __device__ __forceinline__ int find_case(const int* __restrict__ off, int ncase, int b) {
@@ -2832,13 +2862,14 @@ __global__ __launch_bounds__(64) void kb_target_close(const CaseArgs<T>* __restr
                     gptr(a->lam), gptr(a->bad), blockIdx.x - off[c]);
 }
 
-// TWO: two leaves' loads in flight per thread (the batched tuner picks)
-template <int D, typename T, bool TWO = passc_two_leaves<D, T>()>
-__global__ __launch_bounds__(BLOCK, (waves_hint<D, T>())) void kb_passC(const CaseArgs<T>* __restrict__ args,
+// TWO: two leaves' loads in flight per thread (the batched tuner picks); NT
+// threads per cell
+template <int D, typename T, bool TWO = passc_two_leaves<D, T>(), int NT = BLOCK>
+__global__ __launch_bounds__(NT, (waves_hint<D, T>())) void kb_passC(const CaseArgs<T>* __restrict__ args,
                                                                        const int* __restrict__ off, int ncase) {
   const int c = find_case(off, ncase, blockIdx.x);
   const CaseArgs<T>* a = args + c;
-  d_passC<D, T, false, TWO>(global_geo(a->g), global_leaves(a->L), a->vg, gptr(a->vin), gptr(a->fv), gptr(a->vout), gptr(a->fpar),
+  d_passC<D, T, false, TWO, NT>(global_geo(a->g), global_leaves(a->L), a->vg, gptr(a->vin), gptr(a->fv), gptr(a->vout), gptr(a->fpar),
                 gptr(a->tpar), gptr(a->lam), gptr(a->mom), gptr(a->q), blockIdx.x - off[c]);
 }
 

@@ -57,11 +57,18 @@ def test_repeated_colour_turns(avs, nx, ny, diatomic):
     (3, 2, 72, 0, 0),     # largest tables of the 64-lane form, leaves in several shares
     (3, 2, 73, 0, 0),     # just beyond: a workgroup per cell
     (5, 4, 16, 3, 1),     # FP32
+    (3, 3, 5, 0, 0),      # fewer leaves than lanes
+    (3, 3, 8, 0, 0),      # one leaf per lane
+    (3, 3, 38, 0, 0),     # pass C: last sizes with one wave per cell
+    (3, 3, 40, 0, 0),     # and first with four
+    (3, 3, 38, 0, 1),
+    (3, 3, 40, 0, 1),
 ])
 def test_lane_groups(avs, nx, ny, base, levels, prec):
     """A lane per cell and per face: group remainders, leaf shares, both
-    sides of the table limit; two explicit steps with walls (FP64 to 1e-12
-    per step as the other step tests; FP32 1e-5 of the field)."""
+    sides of the table limit; one or four waves per cell in pass C; two
+    explicit steps with walls (FP64 to 1e-12 per step as the other step
+    tests; FP32 1e-5 of the field)."""
     mesh = MM.box2d(nx, ny, periodic=(True, False), sides=dict(bottom=0, top=0),
                     bcs=[(MM.WALL, (1.0, 0.1, 0.0, 1.1))])
     vs = dict(dim=2, lo=(-6, -6), hi=(6, 6), base=(base, base), max_level=levels)
