@@ -59,33 +59,6 @@ __device__ __forceinline__ int xcd_cell(const Geo& g, int x) {
 }
 
 // ---------------------------------------------------------------- reductions
-template <int N>
-__device__ __forceinline__ void block_sum(double (&v)[N], double* red) {
-#pragma unroll
-  for (int m = 0; m < N; ++m) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[m] += __shfl_xor(v[m], o);
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) {
-#pragma unroll
-    for (int m = 0; m < N; ++m) red[w * N + m] = v[m];
-  }
-  __syncthreads();
-  // one entry's four partials at a time: the empty asm that takes the sum
-  // as an operand, with a memory clobber, forms each total before the next
-  // entry is read (otherwise all 4N reads are issued at once and the sums
-  // sunk past the barrier: for N = 25 that held 200 registers and set the
-  // occupancy of the whole kernel)
-#pragma unroll
-  for (int m = 0; m < N; ++m) {
-    v[m] = (red[m] + red[N + m]) + (red[2 * N + m] + red[3 * N + m]);
-    __asm__ volatile("" : "+v"(v[m]) : : "memory");
-  }
-  __syncthreads();
-}
-
 // Totals over a wave of N values per lane: every step halves the values a
 // lane carries (it hands one half to its partner and adds the partner's
 // other half), so that N values take about N + 6 exchanges instead of 6 N
@@ -122,21 +95,36 @@ __device__ __forceinline__ double wave_totals(const double (&v)[N], int& id) {
   return x[0];
 }
 
+template <int N>
+__device__ __forceinline__ void block_sum(double (&v)[N], double* red) {
+  int id;
+  const double x = wave_totals<N>(v, id);
+  const int w = threadIdx.x >> 6;
+  __syncthreads();
+  if (id < N) red[w * N + id] = x;
+  __syncthreads();
+  // one entry's four partials at a time: the empty asm that takes the sum
+  // as an operand, with a memory clobber, forms each total before the next
+  // entry is read (otherwise all 4N reads are issued at once and the sums
+  // sunk past the barrier: for N = 25 that held 200 registers and set the
+  // occupancy of the whole kernel)
+#pragma unroll
+  for (int m = 0; m < N; ++m) {
+    v[m] = (red[m] + red[N + m]) + (red[2 * N + m] + red[3 * N + m]);
+    __asm__ volatile("" : "+v"(v[m]) : : "memory");
+  }
+  __syncthreads();
+}
+
 // Block total of each of N per-thread values, returned to thread t < N for
 // entry t (other threads get 0); the same association as block_sum.
 template <int N>
 __device__ __forceinline__ double block_sum_pick(double (&v)[N], double* red) {
-#pragma unroll
-  for (int m = 0; m < N; ++m) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[m] += __shfl_xor(v[m], o);
-  }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int id;
+  const double x = wave_totals<N>(v, id);
+  const int w = threadIdx.x >> 6;
   __syncthreads();
-  if (lane == 0) {
-#pragma unroll
-    for (int m = 0; m < N; ++m) red[w * N + m] = v[m];
-  }
+  if (id < N) red[w * N + id] = x;
   __syncthreads();
   const int t = threadIdx.x;
   const double r = t < N ? (red[t] + red[N + t]) + (red[2 * N + t] + red[3 * N + t]) : 0.0;
