@@ -2697,11 +2697,11 @@ static hipError_t mlp_lds_attr() {
   static bool done = false;
   if (done) return hipSuccess;
   hipError_t e = hipFuncSetAttribute((const void*)k_mlp_tile<FWD_LOGITS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)LDS_BYTES);
+                                     (int)LDS_FWD);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)k_mlp_tile<FWD_FLAGS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
+    e = hipFuncSetAttribute((const void*)k_mlp_tile<FWD_FLAGS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_FWD);
   if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)k_mlp_tile<TRAIN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
+    e = hipFuncSetAttribute((const void*)k_mlp_tile<TRAIN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_TRAIN);
   done = e == hipSuccess;
   return e;
 }
@@ -2711,7 +2711,7 @@ static avs_status mlp_upload(avs_mlp* mlp, const float* params_host) {
   MCK(hipMemcpyAsync(mlp->prm, params_host, sizeof(float) * NPARAM, hipMemcpyHostToDevice, mlp->stream));
   MCK(hipMemsetAsync(mlp->m, 0, sizeof(float) * NPARAM, mlp->stream));
   MCK(hipMemsetAsync(mlp->v, 0, sizeof(float) * NPARAM, mlp->stream));
-  k_mlp_pack<<<(PWN + TPB - 1) / TPB, TPB, 0, mlp->stream>>>(mlp->prm, mlp->wbf);
+  k_mlp_pack<<<(PT1 + TPB - 1) / TPB, TPB, 0, mlp->stream>>>(mlp->prm, mlp->wbf);
   MCK(hipGetLastError());
   MCK(hipStreamSynchronize(mlp->stream));
   mlp->t = 0;
@@ -2723,11 +2723,11 @@ static avs_status mlp_grad_into(avs_mlp* mlp, const uint16_t* feat, const int8_t
   using namespace mlp;
   const int nt = (int)((n + TILE - 1) / TILE);
   MCK(mlp_lds_attr());
-  k_mlp_tile<TRAIN><<<nt, TPB, LDS_BYTES, mlp->stream>>>((int)n, feat, rows, mlp->wbf, mlp->prm, nullptr, nullptr, 0,
+  k_mlp_tile<TRAIN><<<nt, MPB, LDS_TRAIN, mlp->stream>>>((int)n, feat, rows, mlp->wbf, mlp->prm, nullptr, nullptr, 0,
                                                          nullptr, flags, (float)(1.0 / (double)n), mlp->gpart,
                                                          mlp->lossp);
   MCK(hipGetLastError());
-  k_mlp_reduce<<<(NPARAM + TPB - 1) / TPB, TPB, 0, mlp->stream>>>(nt, mlp->gpart, mlp->lossp, 1.0 / (double)n, grad,
+  k_mlp_reduce<<<(NPARAM + 1 + RED - 1) / RED, RED, 0, mlp->stream>>>(nt, mlp->gpart, mlp->lossp, 1.0 / (double)n, grad,
                                                                   mlp->loss);
   MCK(hipGetLastError());
   return AVS_OK;
@@ -2753,7 +2753,7 @@ static avs_status mlp_adam_launch(avs_mlp* mlp, const float* grad, const avs_ada
   k_mlp_adam<<<(NPARAM + TPB - 1) / TPB, TPB, 0, mlp->stream>>>(grad, mlp->prm, mlp->m, mlp->v, hp->lr, hp->beta1,
                                                                 hp->beta2, hp->eps, c1, c2, mlp->wbf);
   MCK(hipGetLastError());
-  k_mlp_pack<<<(PWN + TPB - 1) / TPB, TPB, 0, mlp->stream>>>(mlp->prm, mlp->wbf);
+  k_mlp_pack<<<(PT1 + TPB - 1) / TPB, TPB, 0, mlp->stream>>>(mlp->prm, mlp->wbf);
   MCK(hipGetLastError());
   mlp->t = t;
   return AVS_OK;
@@ -2820,7 +2820,7 @@ avs_status avs_mlp_forward(avs_mlp* mlp, const uint16_t* feat_dev, int64_t n, fl
   if (n < 0 || n > INT32_MAX - TILE) return fail(AVS_E_INVALID, "n outside [0, 2^31 - 64]");
   if (n == 0) return AVS_OK;
   MCK(mlp_lds_attr());
-  k_mlp_tile<FWD_LOGITS><<<(int)((n + TILE - 1) / TILE), TPB, LDS_BYTES, mlp->stream>>>(
+  k_mlp_tile<FWD_LOGITS><<<(int)((n + TILE - 1) / TILE), MPB, LDS_FWD, mlp->stream>>>(
       (int)n, feat_dev, nullptr, mlp->wbf, mlp->prm, logits_dev, nullptr, 0, nullptr, nullptr, 0.f, nullptr, nullptr);
   MCK(hipGetLastError());
   return AVS_OK;
@@ -2899,7 +2899,7 @@ avs_status avs_adapt_learned(avs_ctx* ctx, avs_mlp* mlp, double C1, double C2, c
     ProfScope ps(ctx, K_LEARNED);
     if (avs_status st = launch_features(ctx, mlp, ctx->feat)) return st;
     CK(mlp_lds_attr());
-    k_mlp_tile<FWD_FLAGS><<<(L.n + TILE - 1) / TILE, TPB, LDS_BYTES, ctx->stream>>>(
+    k_mlp_tile<FWD_FLAGS><<<(L.n + TILE - 1) / TILE, MPB, LDS_FWD, ctx->stream>>>(
         L.n, ctx->feat, nullptr, mlp->wbf, mlp->prm, nullptr, L.level, ctx->lmax, ctx->raw, nullptr, 0.f, nullptr,
         nullptr);
     CKL();

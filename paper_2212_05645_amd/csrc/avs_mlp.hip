@@ -23,18 +23,37 @@ namespace mlp {
 constexpr int NIN = 28, NINP = 32, NH = 128, NOUT = 3, NOUTP = 16;
 constexpr int TILE = 64;                                   // samples per workgroup
 constexpr int TPB = 256;                                   // 4 wave64 per workgroup
+// the tile kernel's 8 waves: 16 of the 64 samples and half of the columns
+// each (a training batch is one workgroup per CU at most, so what counts is
+// how long one tile takes)
+constexpr int MPB = 512;
 // flat float32 parameter vector (row-major, input index first)
 constexpr int O_W1 = 0, O_B1 = O_W1 + NIN * NH, O_W2 = O_B1 + NH, O_B2 = O_W2 + NH * NH, O_W3 = O_B2 + NH,
               O_B3 = O_W3 + NH * NOUT, NPARAM = O_B3 + NOUT;
-// padded bfloat16 weights: W1 [32][128], W2 [128][128], W3 [128][16]
-constexpr int PW1 = 0, PW2 = PW1 + NINP * NH, PW3 = PW2 + NH * NH, PWN = PW3 + NH * NOUTP;
+// padded bfloat16 weights: W1 [32][128], W2 [128][128], W3 [128][16], then
+// the transposes W1T [128][32], W2T [128][128], W3T [16][128]
+constexpr int PW1 = 0, PW2 = PW1 + NINP * NH, PW3 = PW2 + NH * NH, PT1 = PW3 + NH * NOUTP, PT2 = PT1 + NINP * NH,
+              PT3 = PT2 + NH * NH, PWN = PT3 + NH * NOUTP;
 // padded float32 gradient of one tile
 constexpr int G_W1 = 0, G_B1 = G_W1 + NINP * NH, G_W2 = G_B1 + NH, G_B2 = G_W2 + NH * NH, G_W3 = G_B2 + NH,
               G_B3 = G_W3 + NH * NOUTP, GN = G_B3 + NOUTP;
-// LDS layout of the fused kernel (bfloat16 elements)
-constexpr int L_W1 = 0, L_W2 = L_W1 + NINP * NH, L_W3 = L_W2 + NH * NH, L_X = L_W3 + NH * NOUTP,
-              L_H1 = L_X + TILE * NINP, L_H2 = L_H1 + TILE * NH, L_DZ = L_H2 + TILE * NH, L_END = L_DZ + TILE * NOUTP;
-constexpr size_t LDS_BYTES = (size_t)L_END * 2 + (2 * NH + NOUTP) * 4 + TILE * NOUT * 4 + TILE * 4 + 64 * 8;
+// LDS layout of the fused kernel (bfloat16 elements).  Every matrix is held
+// so that the four consecutive k of an MFMA operand are one 8-byte read, the
+// ones read along both of their dimensions twice; rows are padded by 8 bytes
+// so that 16 rows fall on different banks.  (Element by element, an operand
+// was four 2-byte reads; with 4 waves per tile.  Gradient of 8192 rows 40 ->
+// 18 us, logits of 19 678 rows 25 -> 7.6 us; both bound by the latency of one
+// tile.)  H2 takes H1's place (a wave
+// reads and writes its own 16 rows only) except in training, where W2 takes
+// W2T's place once the forward pass is through with it.
+constexpr int SNI = NINP + 4, SNH = NH + 4, SNO = NOUTP + 4, STL = TILE + 4;   // padded rows
+constexpr int L_T1 = 0, L_T2 = L_T1 + NH * SNI, L_T3 = L_T2 + NH * SNH, L_X = L_T3 + NOUTP * SNH,
+              L_H = L_X + TILE * SNI, L_FWD = L_H + TILE * SNH;
+constexpr int L_H2 = L_FWD, L_W3 = L_H2 + TILE * SNH, L_XT = L_W3 + NH * SNO, L_H1T = L_XT + NINP * STL,
+              L_H2T = L_H1T + NH * STL, L_DZ = L_H2T + NH * STL, L_DZT = L_DZ + TILE * SNO,
+              L_TRAIN = L_DZT + NOUTP * STL;
+constexpr size_t LDS_TAIL = (2 * NH + NOUTP) * 4 + TILE * NOUT * 4 + TILE * 4 + 64 * 8;
+constexpr size_t LDS_FWD = (size_t)L_FWD * 2 + LDS_TAIL, LDS_TRAIN = (size_t)L_TRAIN * 2 + LDS_TAIL;
 
 typedef short bf4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -54,22 +73,35 @@ __device__ __forceinline__ uint16_t d2bf(double x) {
   return (uint16_t)(__float_as_uint(v) >> 16);
 }
 
-// acc += A[16 x K] B[K x 16] on v_mfma_f32_16x16x16bf16_1k.  Element (r, k)
-// of A sits at a[r*ars + k*acs], element (k, c) of B at b[k*brs + c*bcs]
-// (LDS).  Lane l supplies row l%16 of A and column l%16 of B for k in
-// 4(l/16)..4(l/16)+3 of each 16-wide step; it receives C[4(l/16)+j][l%16].
-__device__ __forceinline__ void mma(f4& acc, const uint16_t* a, int ars, int acs, const uint16_t* b, int brs, int bcs,
-                                    int K, int lane) {
+// acc[t] += A[16 x K] B_t[K x 16] for NT column blocks on
+// v_mfma_f32_16x16x16bf16_1k, k ascending.  Row r of A sits at a + r*as, its
+// k contiguous; column c of B_t at b + t*bt + c*bs, k contiguous (LDS).  Lane
+// l supplies row l%16 of A and column l%16 of B for k in 4(l/16)..4(l/16)+3 of
+// each 16-wide step; it receives C[4(l/16)+j][l%16].  The NT independent
+// chains keep the matrix cores fed.
+template <int K, int NT>
+__device__ __forceinline__ void mma(f4 (&acc)[NT], const uint16_t* a, int as, const uint16_t* b, int bs, int bt,
+                                    int lane) {
   const int r = lane & 15, kq = 4 * (lane >> 4);
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    bf4 va, vb;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      va[j] = (short)a[r * ars + (k0 + kq + j) * acs];
-      vb[j] = (short)b[(k0 + kq + j) * brs + r * bcs];
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    const bf4 va = *reinterpret_cast<const bf4*>(a + r * as + k0 + kq);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const bf4 vb = *reinterpret_cast<const bf4*>(b + t * bt + r * bs + k0 + kq);
+      acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, vb, acc[t], 0, 0, 0);
     }
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va, vb, acc, 0, 0, 0);
   }
+}
+
+// Copy a row-major global matrix of ROWS rows of COLS elements into padded
+// LDS rows (8 bytes at a time).
+template <int ROWS, int COLS, int STRIDE>
+__device__ __forceinline__ void stage(uint16_t* dst, const uint16_t* __restrict__ src) {
+  constexpr int V = COLS / 4;
+#pragma unroll
+  for (int v = threadIdx.x; v < ROWS * V; v += MPB)
+    *reinterpret_cast<uint2*>(dst + (v / V) * STRIDE + (v % V) * 4) = reinterpret_cast<const uint2*>(src)[v];
 }
 
 __device__ __forceinline__ int label_of(int8_t f) { return f == 1 ? 1 : (f == -1 ? 2 : 0); }
@@ -81,14 +113,14 @@ enum Mode { FWD_LOGITS = 0, FWD_FLAGS = 1, TRAIN = 2 };
 // ties; split only below lmax, merge only above the roots); TRAIN writes the
 // tile's padded gradient and its summed loss.
 template <int MODE>
-__global__ __launch_bounds__(TPB) void k_mlp_tile(int n, const uint16_t* __restrict__ X, const int32_t* __restrict__ rows,
+__global__ __launch_bounds__(MPB) void k_mlp_tile(int n, const uint16_t* __restrict__ X, const int32_t* __restrict__ rows,
                                                   const uint16_t* __restrict__ wbf, const float* __restrict__ prm,
                                                   float* __restrict__ logits, const int* __restrict__ level, int lmax,
                                                   int8_t* __restrict__ raw, const int8_t* __restrict__ flags, float inv_n,
                                                   float* __restrict__ gpart, double* __restrict__ lossp) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   uint16_t* s = reinterpret_cast<uint16_t*>(lds_raw);
-  float* sB1 = reinterpret_cast<float*>(lds_raw + (size_t)L_END * 2);
+  float* sB1 = reinterpret_cast<float*>(lds_raw + (size_t)(MODE == TRAIN ? L_TRAIN : L_FWD) * 2);
   float* sB2 = sB1 + NH;
   float* sB3 = sB2 + NH;                 // NOUTP
   float* sZ = sB3 + NOUTP;               // TILE * NOUT
@@ -96,70 +128,104 @@ __global__ __launch_bounds__(TPB) void k_mlp_tile(int n, const uint16_t* __restr
   double* sL = reinterpret_cast<double*>(sY + TILE);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int row0 = blockIdx.x * TILE;
+  constexpr int LH2 = MODE == TRAIN ? L_H2 : L_H;
 
   // weights, biases, input tile, labels
-  {
-    const uint4* src = reinterpret_cast<const uint4*>(wbf);
-    uint4* dst = reinterpret_cast<uint4*>(s + L_W1);
-    for (int v = tid; v < PWN / 8; v += TPB) dst[v] = src[v];
-    for (int j = tid; j < NH; j += TPB) {
-      sB1[j] = prm[O_B1 + j];
-      sB2[j] = prm[O_B2 + j];
+  stage<NH, NINP, SNI>(s + L_T1, wbf + PT1);
+  stage<NH, NH, SNH>(s + L_T2, wbf + PT2);
+  stage<NOUTP, NH, SNH>(s + L_T3, wbf + PT3);
+  if (MODE == TRAIN) stage<NH, NOUTP, SNO>(s + L_W3, wbf + PW3);
+  for (int j = tid; j < NH; j += MPB) {
+    sB1[j] = prm[O_B1 + j];
+    sB2[j] = prm[O_B2 + j];
+  }
+  if (tid < NOUTP) sB3[tid] = tid < NOUT ? prm[O_B3 + tid] : 0.f;
+  for (int v = tid; v < TILE * NINP / 4; v += MPB) {
+    const int r = v / (NINP / 4), c = v % (NINP / 4), g = row0 + r;
+    uint2 val = make_uint2(0, 0);
+    if (g < n) {
+      const int src_row = rows ? rows[g] : g;
+      val = reinterpret_cast<const uint2*>(X + (size_t)src_row * NINP)[c];
     }
-    if (tid < NOUTP) sB3[tid] = tid < NOUT ? prm[O_B3 + tid] : 0.f;
-    for (int v = tid; v < TILE * NINP / 8; v += TPB) {
-      const int r = v / (NINP / 8), c = v % (NINP / 8), g = row0 + r;
-      uint4 val = make_uint4(0, 0, 0, 0);
-      if (g < n) {
-        const int src_row = rows ? rows[g] : g;
-        val = reinterpret_cast<const uint4*>(X + (size_t)src_row * NINP)[c];
-      }
-      reinterpret_cast<uint4*>(s + L_X)[v] = val;
+    *reinterpret_cast<uint2*>(s + L_X + r * SNI + 4 * c) = val;
+    if (MODE == TRAIN) {
+      uint16_t* t = s + L_XT + 4 * c * STL + r;
+      t[0] = (uint16_t)val.x;
+      t[STL] = (uint16_t)(val.x >> 16);
+      t[2 * STL] = (uint16_t)val.y;
+      t[3 * STL] = (uint16_t)(val.y >> 16);
     }
-    if (MODE == TRAIN && tid < TILE) {
-      const int g = row0 + tid;
-      sY[tid] = g < n ? label_of(flags[rows ? rows[g] : g]) : -1;
-    }
+  }
+  if (MODE == TRAIN && tid < TILE) {
+    const int g = row0 + tid;
+    sY[tid] = g < n ? label_of(flags[rows ? rows[g] : g]) : -1;
   }
   __syncthreads();
   const int rq = 4 * (lane >> 4), cl = lane & 15;
-  const int wr = 16 * wave;   // first row of this wave's slab
+  const int wr = 16 * (wave & 3);           // first row of this wave's slab
+  constexpr int NT = NH / 16 / 2;           // its column blocks, from t0
+  const int t0 = NT * (wave >> 2);
+  const f4 zero = {0.f, 0.f, 0.f, 0.f};
+  // the four values of column c for rows wr + rq .. + 3, into the rows and
+  // (training) into the transpose
+  auto put = [&](uint16_t* m, uint16_t* mt, int c, const uint16_t (&x)[4]) {
+    if (m) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) m[(wr + rq + j) * SNH + c] = x[j];
+    }
+    if (mt)
+      *reinterpret_cast<uint2*>(mt + c * STL + wr + rq) =
+          make_uint2((uint32_t)x[0] | ((uint32_t)x[1] << 16), (uint32_t)x[2] | ((uint32_t)x[3] << 16));
+  };
 
   // H1 = bf16(relu(X W1 + b1))
-  for (int ct = 0; ct < NH / 16; ++ct) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    mma(acc, s + L_X + wr * NINP, NINP, 1, s + L_W1 + ct * 16, NH, 1, NINP, lane);
+  {
+    f4 acc[NT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = wr + rq + j, c = ct * 16 + cl;
-      s[L_H1 + r * NH + c] = f2bf(fmaxf(acc[j] + sB1[c], 0.f));
+    for (int t = 0; t < NT; ++t) acc[t] = zero;
+    mma<NINP, NT>(acc, s + L_X + wr * SNI, SNI, s + L_T1 + t0 * 16 * SNI, SNI, 16 * SNI, lane);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = (t0 + t) * 16 + cl;
+      uint16_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = f2bf(fmaxf(acc[t][j] + sB1[c], 0.f));
+      put(s + L_H, MODE == TRAIN ? s + L_H1T : nullptr, c, x);
     }
   }
   __syncthreads();
-  // H2 = bf16(relu(H1 W2 + b2))
-  for (int ct = 0; ct < NH / 16; ++ct) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    mma(acc, s + L_H1 + wr * NH, NH, 1, s + L_W2 + ct * 16, NH, 1, NH, lane);
+  // H2 = bf16(relu(H1 W2 + b2)); the wave's rows of H1 are read before any of
+  // H2 is written
+  {
+    f4 acc[NT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = wr + rq + j, c = ct * 16 + cl;
-      s[L_H2 + r * NH + c] = f2bf(fmaxf(acc[j] + sB2[c], 0.f));
+    for (int t = 0; t < NT; ++t) acc[t] = zero;
+    mma<NH, NT>(acc, s + L_H + wr * SNH, SNH, s + L_T2 + t0 * 16 * SNH, SNH, 16 * SNH, lane);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = (t0 + t) * 16 + cl;
+      uint16_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = f2bf(fmaxf(acc[t][j] + sB2[c], 0.f));
+      put(s + LH2, MODE == TRAIN ? s + L_H2T : nullptr, c, x);
     }
+    if (MODE == TRAIN) stage<NH, NH, SNH>(s + L_T2, wbf + PW2);     // for dH1
   }
   __syncthreads();
   // Z = H2 W3 + b3 (float32)
-  {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    mma(acc, s + L_H2 + wr * NH, NH, 1, s + L_W3, NOUTP, 1, NH, lane);
+  if (wave < 4) {
+    f4 acc[1] = {zero};
+    mma<NH, 1>(acc, s + LH2 + wr * SNH, SNH, s + L_T3, SNH, 0, lane);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int r = wr + rq + j;
-      if (cl < NOUT) sZ[r * NOUT + cl] = acc[j] + sB3[cl];
+      if (cl < NOUT) sZ[r * NOUT + cl] = acc[0][j] + sB3[cl];
     }
   }
   __syncthreads();
   if (MODE == FWD_LOGITS) {
-    for (int v = tid; v < TILE * NOUT; v += TPB) {
+    for (int v = tid; v < TILE * NOUT; v += MPB) {
       const int g = row0 + v / NOUT;
       if (g < n) logits[(size_t)g * NOUT + v % NOUT] = sZ[v];
     }
@@ -186,8 +252,7 @@ __global__ __launch_bounds__(TPB) void k_mlp_tile(int n, const uint16_t* __restr
   if (tid < TILE) {
     const int y = sY[tid];
     double li = 0.0;
-    uint16_t* dz = s + L_DZ + tid * NOUTP;
-    for (int c = 0; c < NOUTP; ++c) dz[c] = 0;
+    uint16_t d[NOUT] = {0, 0, 0};
     if (y >= 0) {
       const float* z = sZ + tid * NOUT;
       const float m = fmaxf(fmaxf(z[0], z[1]), z[2]);
@@ -197,7 +262,13 @@ __global__ __launch_bounds__(TPB) void k_mlp_tile(int n, const uint16_t* __restr
         sum += e[c];
       }
       li = (double)logf(sum) + (double)m - (double)z[y];
-      for (int c = 0; c < NOUT; ++c) dz[c] = f2bf((e[c] / sum - (c == y ? 1.f : 0.f)) * inv_n);
+      for (int c = 0; c < NOUT; ++c) d[c] = f2bf((e[c] / sum - (c == y ? 1.f : 0.f)) * inv_n);
+    }
+#pragma unroll
+    for (int c = 0; c < NOUTP; ++c) {
+      const uint16_t x = c < NOUT ? d[c < NOUT ? c : 0] : (uint16_t)0;
+      s[L_DZ + tid * SNO + c] = x;
+      s[L_DZT + c * STL + tid] = x;
     }
     sL[tid] = li;
   }
@@ -205,71 +276,90 @@ __global__ __launch_bounds__(TPB) void k_mlp_tile(int n, const uint16_t* __restr
   float* gp = gpart + (size_t)blockIdx.x * GN;
   if (tid == 0) {
     double t = 0.0;
+#pragma unroll 16
     for (int i = 0; i < TILE; ++i) t += sL[i];
     lossp[blockIdx.x] = t;
   }
-  // dW3 = H2^T dZ  [128 x 16], db3
-  for (int rt = 2 * wave; rt < 2 * wave + 2; ++rt) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    mma(acc, s + L_H2 + rt * 16, 1, NH, s + L_DZ, NOUTP, 1, TILE, lane);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) gp[G_W3 + (rt * 16 + rq + j) * NOUTP + cl] = acc[j];
-  }
-  if (tid < NOUTP) {
+  // sums over the tile's samples of one column, in sample order
+  auto col_sum = [&](const uint16_t* mt) {
     float t = 0.f;
-    for (int i = 0; i < TILE; ++i) t += bf2f(s[L_DZ + i * NOUTP + tid]);
-    gp[G_B3 + tid] = t;
-  }
-  __syncthreads();
-  // dH2 = bf16((dZ W3^T) * (H2 > 0)), in place over H2
-  for (int ct = 0; ct < NH / 16; ++ct) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    mma(acc, s + L_DZ + wr * NOUTP, NOUTP, 1, s + L_W3 + ct * 16 * NOUTP, 1, NOUTP, NOUTP, lane);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int e = L_H2 + (wr + rq + j) * NH + ct * 16 + cl;
-      s[e] = bf2f(s[e]) > 0.f ? f2bf(acc[j]) : (uint16_t)0;
+    for (int i = 0; i < TILE; i += 4) {
+      const bf4 v = *reinterpret_cast<const bf4*>(mt + i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) t += bf2f((uint16_t)v[j]);
+    }
+    return t;
+  };
+  // dW3 = H2^T dZ  [128 x 16], db3
+  {
+    const int rt = wave;
+    f4 acc[1] = {zero};
+    mma<TILE, 1>(acc, s + L_H2T + rt * 16 * STL, STL, s + L_DZT, STL, 0, lane);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) gp[G_W3 + (rt * 16 + rq + j) * NOUTP + cl] = acc[0][j];
+  }
+  if (tid < NOUTP) gp[G_B3 + tid] = col_sum(s + L_DZT + tid * STL);
+  __syncthreads();
+  // dH2 = bf16((dZ W3^T) * (H2 > 0)), in place over H2 and its transpose
+  {
+    f4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = zero;
+    mma<NOUTP, NT>(acc, s + L_DZ + wr * SNO, SNO, s + L_W3 + t0 * 16 * SNO, SNO, 16 * SNO, lane);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = (t0 + t) * 16 + cl;
+      uint16_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x[j] = bf2f(s[L_H2 + (wr + rq + j) * SNH + c]) > 0.f ? f2bf(acc[t][j]) : (uint16_t)0;
+      put(s + L_H2, s + L_H2T, c, x);
     }
   }
   __syncthreads();
   // dW2 = H1^T dH2 [128 x 128], db2
-  for (int rt = 2 * wave; rt < 2 * wave + 2; ++rt)
-    for (int ct = 0; ct < NH / 16; ++ct) {
-      f4 acc = {0.f, 0.f, 0.f, 0.f};
-      mma(acc, s + L_H1 + rt * 16, 1, NH, s + L_H2 + ct * 16, NH, 1, TILE, lane);
+  {
+    const int rt = wave;
+    f4 acc[NH / 16];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) gp[G_W2 + (rt * 16 + rq + j) * NH + ct * 16 + cl] = acc[j];
-    }
-  if (tid < NH) {
-    float t = 0.f;
-    for (int i = 0; i < TILE; ++i) t += bf2f(s[L_H2 + i * NH + tid]);
-    gp[G_B2 + tid] = t;
+    for (int t = 0; t < NH / 16; ++t) acc[t] = zero;
+    mma<TILE, NH / 16>(acc, s + L_H1T + rt * 16 * STL, STL, s + L_H2T, STL, 16 * STL, lane);
+#pragma unroll
+    for (int t = 0; t < NH / 16; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) gp[G_W2 + (rt * 16 + rq + j) * NH + t * 16 + cl] = acc[t][j];
   }
+  if (tid < NH) gp[G_B2 + tid] = col_sum(s + L_H2T + tid * STL);
   __syncthreads();
-  // dH1 = bf16((dH2 W2^T) * (H1 > 0)), in place over H1
-  for (int ct = 0; ct < NH / 16; ++ct) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    mma(acc, s + L_H2 + wr * NH, NH, 1, s + L_W2 + ct * 16 * NH, 1, NH, NH, lane);
+  // dH1 = bf16((dH2 W2^T) * (H1 > 0)), into H1's transpose
+  {
+    f4 acc[NT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int e = L_H1 + (wr + rq + j) * NH + ct * 16 + cl;
-      s[e] = bf2f(s[e]) > 0.f ? f2bf(acc[j]) : (uint16_t)0;
+    for (int t = 0; t < NT; ++t) acc[t] = zero;
+    mma<NH, NT>(acc, s + L_H2 + wr * SNH, SNH, s + L_T2 + t0 * 16 * SNH, SNH, 16 * SNH, lane);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = (t0 + t) * 16 + cl;
+      uint16_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x[j] = bf2f(s[L_H + (wr + rq + j) * SNH + c]) > 0.f ? f2bf(acc[t][j]) : (uint16_t)0;
+      put(nullptr, s + L_H1T, c, x);
     }
   }
   __syncthreads();
   // dW1 = X^T dH1 [32 x 128], db1
-  for (int t = 4 * wave; t < 4 * wave + 4; ++t) {
-    const int rt = t / (NH / 16), ct = t % (NH / 16);
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    mma(acc, s + L_X + rt * 16, 1, NINP, s + L_H1 + ct * 16, NH, 1, TILE, lane);
+  {
+    const int rt = wave >> 2, c0 = 2 * (wave & 3);
+    f4 acc[2] = {zero, zero};
+    mma<TILE, 2>(acc, s + L_XT + rt * 16 * STL, STL, s + L_H1T + c0 * 16 * STL, STL, 16 * STL, lane);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) gp[G_W1 + (rt * 16 + rq + j) * NH + ct * 16 + cl] = acc[j];
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) gp[G_W1 + (rt * 16 + rq + j) * NH + (c0 + t) * 16 + cl] = acc[t][j];
   }
-  if (tid < NH) {
-    float t = 0.f;
-    for (int i = 0; i < TILE; ++i) t += bf2f(s[L_H1 + i * NH + tid]);
-    gp[G_B1 + tid] = t;
-  }
+  if (tid < NH) gp[G_B1 + tid] = col_sum(s + L_H1T + tid * STL);
 }
 
 // Padded position of flat parameter p.
@@ -286,19 +376,39 @@ __device__ __forceinline__ int padded_of(int p) {
 }
 
 // Sum of the tile gradients in tile order; loss = sum of tile losses / n.
-__global__ __launch_bounds__(TPB) void k_mlp_reduce(int ntile, const float* __restrict__ gpart,
+// One wave per workgroup (20 611 parameters spread over all CUs) and 32
+// tiles' loads in flight ahead of their adds (one at a time they were 128
+// dependent loads; 8192 rows 37 -> 7.7 us).
+constexpr int RED = 64;
+__global__ __launch_bounds__(RED) void k_mlp_reduce(int ntile, const float* __restrict__ gpart,
                                                     const double* __restrict__ lossp, double inv_n,
                                                     float* __restrict__ grad, double* __restrict__ loss) {
-  const int p = blockIdx.x * TPB + threadIdx.x;
+  const int p = blockIdx.x * RED + threadIdx.x;
   if (p < NPARAM) {
-    const int q = padded_of(p);
+    const float* g = gpart + padded_of(p);
     float t = 0.f;
-    for (int b = 0; b < ntile; ++b) t += gpart[(size_t)b * GN + q];
+    int b = 0;
+    for (; b + 32 <= ntile; b += 32) {
+      float x[32];
+#pragma unroll
+      for (int j = 0; j < 32; ++j) x[j] = g[(size_t)(b + j) * GN];
+#pragma unroll
+      for (int j = 0; j < 32; ++j) t += x[j];
+    }
+    for (; b < ntile; ++b) t += g[(size_t)b * GN];
     grad[p] = t;
   }
-  if (p == 0) {
+  if (p == NPARAM) {       // a thread of its own: the last workgroup has room
     double t = 0.0;
-    for (int b = 0; b < ntile; ++b) t += lossp[b];
+    int b = 0;
+    for (; b + 32 <= ntile; b += 32) {
+      double x[32];
+#pragma unroll
+      for (int j = 0; j < 32; ++j) x[j] = lossp[b + j];
+#pragma unroll
+      for (int j = 0; j < 32; ++j) t += x[j];
+    }
+    for (; b < ntile; ++b) t += lossp[b];
     *loss = t * inv_n;
   }
 }
@@ -320,21 +430,27 @@ __global__ __launch_bounds__(TPB) void k_mlp_adam(const float* __restrict__ grad
   prm[p] = (float)np_;
 }
 
-// bfloat16 weights in the padded layout (padding left at zero).
+// bfloat16 weights in the padded layout (padding left at zero) and their
+// transposes; one thread per element of W1, W2, W3.
 __global__ __launch_bounds__(TPB) void k_mlp_pack(const float* __restrict__ prm, uint16_t* __restrict__ wbf) {
   const int e = blockIdx.x * TPB + threadIdx.x;
-  if (e >= PWN) return;
+  if (e >= PT1) return;
   float val = 0.f;
+  int t;
   if (e < PW2) {
     const int r = e / NH, c = e % NH;
     if (r < NIN) val = prm[O_W1 + r * NH + c];
+    t = PT1 + c * NINP + r;
   } else if (e < PW3) {
+    const int r = (e - PW2) / NH, c = (e - PW2) % NH;
     val = prm[O_W2 + (e - PW2)];
+    t = PT2 + c * NH + r;
   } else {
     const int r = (e - PW3) / NOUTP, c = (e - PW3) % NOUTP;
     if (c < NOUT) val = prm[O_W3 + r * NOUT + c];
+    t = PT3 + c * NH + r;
   }
-  wbf[e] = f2bf(val);
+  wbf[e] = wbf[t] = f2bf(val);
 }
 
 // ------------------------------------------------------------ features

@@ -6,7 +6,10 @@ import pytest
 from workloads import fields as F
 from workloads import meshes as MM
 
+from oracle import mlp_oracle as M
+
 from test_gpu_implicit import dia_pair
+from test_gpu_learned import dev, params, to_bits
 from test_gpu_parity import fieldrel, make_pair, random_tree, rel
 
 pytestmark = pytest.mark.gpu
@@ -96,3 +99,21 @@ def test_lane_groups_3d(avs, prec):
     v, W = cs.get_state()
     tol = 1e-5 if prec else 1e-12
     assert fieldrel(v, o.phi) < tol and fieldrel(W, o.W) < tol
+
+
+@pytest.mark.parametrize("n", [1, 63, 65, 64 * 32, 64 * 33 + 1])
+def test_gradient_tile_remainders(avs, n):
+    """The network's gradient over batches that end inside a tile of 64 rows
+    and whose tiles end inside the reduction's group of 32 (tolerances of the
+    larger batch's test: a bfloat16 rounding may fall the other way)."""
+    rng = np.random.default_rng(n)
+    p = params(41)
+    mlp = avs.Mlp(p, max_batch=n)
+    X = np.zeros((n, 32))
+    X[:, :28] = M.bf16_round(rng.uniform(-1.5, 1.5, (n, 28)))
+    flags = rng.integers(-1, 2, n).astype(np.int8)
+    g, loss = mlp.grad(dev(to_bits(X)), dev(flags))
+    lr, gr = M.loss_and_grad(p, X[:, :28], M.labels_from_flags(flags))
+    assert abs(loss - lr) <= 1e-5 * abs(lr)
+    G = g.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(G - gr) <= 1e-3 * np.linalg.norm(gr)
