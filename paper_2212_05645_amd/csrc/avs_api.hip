@@ -1596,6 +1596,8 @@ struct avs_dia {
   DiaGas gp{};
   double *v[2] = {nullptr, nullptr}, *fv = nullptr, *W[2] = {nullptr, nullptr};
   double *q = nullptr, *F = nullptr, *tp = nullptr, *lam = nullptr;
+  double *fmom = nullptr, *frec = nullptr, *crec = nullptr;   // moment partials of the faces, face and cell records
+  int nchs = 0;                                               // chunk stride of fmom
   double *rf = nullptr, *irhs = nullptr, *idiag = nullptr, *prow = nullptr, *pst = nullptr;   // implicit predictor
   int* pnb = nullptr;
   int* bad = nullptr;
@@ -1630,7 +1632,12 @@ size_t dia_layout(const avs_ctx* c, int64_t max_leaves, avs_dia* d, char* base) 
   double* pst = cv.take<double>(nc * (2 * NW + 2));
   int* pnb = cv.take<int>(nc * (size_t)c->maxf);
   int* bad = cv.take<int>(4);
+  const size_t nchs = (cap + CHUNK - 1) / CHUNK;
+  double* fmom = cv.take<double>((nf + 1) * 2 * nchs * (D == 2 ? Dg<2>::NM : Dg<3>::NM));
+  double* frec = cv.take<double>((nf + 1) * (size_t)Dg<2>::REC);
+  double* crec = cv.take<double>(nc * (size_t)Dg<2>::REC);
   if (d) {
+    d->fmom = fmom; d->frec = frec; d->crec = crec; d->nchs = (int)nchs;
     d->fv = fv; d->W[0] = W0; d->W[1] = W1; d->q = q; d->F = F; d->tp = tp; d->lam = lam; d->bad = bad;
     d->rf = rf; d->irhs = irhs; d->idiag = idiag; d->prow = prow; d->pst = pst; d->pnb = pnb;
   }
@@ -1648,46 +1655,71 @@ avs_status dia_check_bad(avs_dia* d) {
 
 size_t dia_shm(const avs_ctx* ctx) { return (size_t)2 * ctx->D * ctx->vg.numax * sizeof(double); }
 
+template <int D, int MODE>
+avs_status dia_update(avs_dia* d, const double* vin, double* vout) {
+  avs_ctx* ctx = d->ctx;
+  k_dg_update<D, MODE><<<(unsigned)round_up(ctx->nc, 8), BLOCK, 0, ctx->stream>>>(
+      ctx->geo, ctx->leaves(ctx->lcur), vin, d->fv, d->frec, vout, d->tp, d->crec, d->lam, d->q);
+  CKL();
+  return AVS_OK;
+}
+
 template <int D>
 avs_status dia_init(avs_dia* d) {
   avs_ctx* ctx = d->ctx;
   const Leaves L = ctx->leaves(ctx->lcur);
   const int nc = ctx->nc;
   const unsigned gc = (unsigned)((nc + BLOCK - 1) / BLOCK);
-  k_dg_initrec<D><<<gc, BLOCK, 0, ctx->stream>>>(nc, d->gp, d->W[0], d->tp, d->bad);
+  // two faces' tables per workgroup of the interface stage
+  CK(hipFuncSetAttribute((const void*)k_dg_face<D>, hipFuncAttributeMaxDynamicSharedMemorySize, DG_FB * 48 * 1024));
+  k_dg_initrec<D><<<gc, BLOCK, 0, ctx->stream>>>(nc, d->gp, d->W[0], d->tp, d->crec, d->bad);
   CKL();
-  k_dg_target<D><<<nc, BLOCK, dia_shm(ctx), ctx->stream>>>(ctx->geo, L, ctx->vg, d->gp, d->tp, d->W[0], d->lam, 1,
+  k_dg_target<D><<<nc, BLOCK, dia_shm(ctx), ctx->stream>>>(ctx->geo, L, ctx->vg, d->tp, d->crec, d->W[0], d->lam, 1,
                                                            d->bad);
   CKL();
-  k_dg_update<D><<<nc, BLOCK, dia_shm(ctx), ctx->stream>>>(ctx->geo, L, ctx->vg, d->gp, nullptr, nullptr, d->v[0], d->tp,
-                                                           d->lam, d->q, 1);
+  return dia_update<D, 1>(d, nullptr, d->v[0]);
+}
+
+// Reconstruction and interface stage of a step (with rf also the predictor's
+// r_f from W^n).
+template <int D>
+avs_status dia_interfaces(avs_dia* d, double* rf) {
+  avs_ctx* ctx = d->ctx;
+  const Leaves L = ctx->leaves(ctx->lcur);
+  const int c = d->cur, nch = (L.n + CHUNK - 1) / CHUNK;
+  k_dg_recon<D><<<dim3((unsigned)round_up(ctx->nc, 8), (unsigned)nch), passA_threads<D>(), 0, ctx->stream>>>(
+      ctx->geo, L, ctx->h, d->v[c], ctx->bcpair, d->gp.R, d->fv, d->fmom, d->nchs, CHUNK);
+  CKL();
+  if (ctx->nf > 0) {
+    k_dg_face<D><<<(ctx->nf + DG_FB - 1) / DG_FB, BLOCK, DG_FB * dia_shm(ctx), ctx->stream>>>(
+        ctx->geo, L, ctx->vg, ctx->gas, d->gp, ctx->h, d->fmom, d->nchs, nch, ctx->bden, ctx->bfin, d->frec, d->F, d->bad,
+        rf ? d->W[c] : nullptr, rf);
+    CKL();
+  }
+  return AVS_OK;
+}
+
+// W^{n+1}, the target record and its closure.
+template <int D>
+avs_status dia_macro(avs_dia* d) {
+  avs_ctx* ctx = d->ctx;
+  const Leaves L = ctx->leaves(ctx->lcur);
+  const int c = d->cur;
+  k_dg_macro<D><<<(unsigned)((ctx->nc + BLOCK - 1) / BLOCK), BLOCK, 0, ctx->stream>>>(
+      ctx->geo, ctx->gas, d->gp, ctx->dt, d->F, d->W[c], d->W[c ^ 1], d->q, d->tp, d->crec, d->bad);
+  CKL();
+  k_dg_target<D><<<ctx->nc, BLOCK, dia_shm(ctx), ctx->stream>>>(ctx->geo, L, ctx->vg, d->tp, d->crec, d->W[c ^ 1], d->lam,
+                                                                0, d->bad);
   CKL();
   return AVS_OK;
 }
 
 template <int D>
 avs_status dia_steps(avs_dia* d, int nsteps) {
-  avs_ctx* ctx = d->ctx;
-  const Leaves L = ctx->leaves(ctx->lcur);
-  const unsigned gc = (unsigned)((ctx->nc + BLOCK - 1) / BLOCK);
-  const size_t shm = dia_shm(ctx);
   for (int s = 0; s < nsteps; ++s) {
-    const int c = d->cur;
-    k_dg_recon<D><<<dim3((unsigned)round_up(ctx->nc, 8), (unsigned)((L.n + CHUNK - 1) / CHUNK)), BLOCK, 0,
-                    ctx->stream>>>(ctx->geo, L, ctx->h, d->v[c], d->fv, d->gp, CHUNK);
-    CKL();
-    k_dg_face<D><<<ctx->nf, BLOCK, shm, ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->gas, d->gp, ctx->h, d->fv, d->F,
-                                                       d->bad, nullptr, nullptr);
-    CKL();
-    k_dg_macro<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, d->gp, ctx->dt, d->F, d->W[c], d->W[c ^ 1], d->q,
-                                                 d->tp, d->bad);
-    CKL();
-    k_dg_target<D><<<ctx->nc, BLOCK, shm, ctx->stream>>>(ctx->geo, L, ctx->vg, d->gp, d->tp, d->W[c ^ 1], d->lam, 0,
-                                                         d->bad);
-    CKL();
-    k_dg_update<D><<<ctx->nc, BLOCK, shm, ctx->stream>>>(ctx->geo, L, ctx->vg, d->gp, d->v[c], d->fv, d->v[c ^ 1], d->tp,
-                                                         d->lam, d->q, 0);
-    CKL();
+    if (avs_status st = dia_interfaces<D>(d, nullptr)) return st;
+    if (avs_status st = dia_macro<D>(d)) return st;
+    if (avs_status st = dia_update<D, 0>(d, d->v[d->cur], d->v[d->cur ^ 1])) return st;
     d->cur ^= 1;
   }
   return AVS_OK;
@@ -1702,31 +1734,17 @@ template <int D>
 avs_status dia_steps_implicit(avs_dia* d, int nsteps, int n_macro, int n_micro) {
   avs_ctx* ctx = d->ctx;
   const Leaves L = ctx->leaves(ctx->lcur);
-  const unsigned gc = (unsigned)((ctx->nc + BLOCK - 1) / BLOCK);
-  const size_t shm = dia_shm(ctx);
   const int ncol = (int)ctx->col_off.size() - 1;
   for (int st = 0; st < nsteps; ++st) {
     const int c = d->cur;
-    k_dg_recon<D><<<dim3((unsigned)round_up(ctx->nc, 8), (unsigned)((L.n + CHUNK - 1) / CHUNK)), BLOCK, 0,
-                    ctx->stream>>>(ctx->geo, L, ctx->h, d->v[c], d->fv, d->gp, CHUNK);
-    CKL();
-    k_dg_face<D><<<ctx->nf, BLOCK, shm, ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->gas, d->gp, ctx->h, d->fv, d->F,
-                                                       d->bad, d->W[c], d->rf);
-    CKL();
+    if (avs_status sp = dia_interfaces<D>(d, d->rf)) return sp;
     if (avs_status sp = run_predictor<D, true>(ctx, n_macro, d->gp.Z, d->W[c], d->rf, d->prow, d->pnb, d->irhs,
                                                d->idiag, d->pst, d->F, d->bad))
       return sp;
-    k_dg_macro<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->gas, d->gp, ctx->dt, d->F, d->W[c], d->W[c ^ 1], d->q,
-                                                 d->tp, d->bad);
-    CKL();
-    k_dg_target<D><<<ctx->nc, BLOCK, shm, ctx->stream>>>(ctx->geo, L, ctx->vg, d->gp, d->tp, d->W[c ^ 1], d->lam, 0,
-                                                         d->bad);
-    CKL();
+    if (avs_status sp = dia_macro<D>(d)) return sp;
     double* res = d->v[c ^ 1];
     double* dphi = d->fv;
-    k_dg_update<D><<<ctx->nc, BLOCK, shm, ctx->stream>>>(ctx->geo, L, ctx->vg, d->gp, d->v[c], d->fv, res, d->tp,
-                                                         d->lam, d->q, 2);
-    CKL();
+    if (avs_status sp = dia_update<D, 2>(d, d->v[c], res)) return sp;
     k_imp_zero<double><<<ctx->nc, BLOCK, 0, ctx->stream>>>(3, ctx->nc, L, dphi);
     CKL();
     // a cell's last visit writes phi^{n+1} over its right-hand side
@@ -1782,7 +1800,7 @@ avs_status dia_remap_state(avs_dia* d) {
   CKL();
   // the heat fluxes of the remapped state for the next step's target
   const unsigned gc = (unsigned)((ctx->nc + BLOCK - 1) / BLOCK);
-  k_dg_initrec<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->nc, d->gp, d->W[c], d->tp, d->bad);
+  k_dg_initrec<D><<<gc, BLOCK, 0, ctx->stream>>>(ctx->nc, d->gp, d->W[c], d->tp, d->crec, d->bad);
   CKL();
   k_dg_heat<D><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->geo, Ln, d->v[c ^ 1], d->tp, d->q);
   CKL();

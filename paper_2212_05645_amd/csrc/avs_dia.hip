@@ -5,14 +5,18 @@
 // cell and leaf, [3][cell][leaf]: G, H (the 3 - D hidden translational
 // degrees of freedom; identically zero in 3-D) and R (rotational energy,
 // two degrees of freedom); D + 3 conserved variables (rho, rho U, rho E,
-// rho E_rot).  One pass per stage, written for clarity rather than speed:
+// rho E_rot).
 //   k_dg_recon   limited least-squares reconstruction at x_f - xi h into the
-//                interface rows (boundary Maxwellian triples on incoming leaves)
+//                interface rows (boundary equilibrium triples on incoming
+//                leaves) and the faces' raw moment partials: pass A of the
+//                monatomic step with three components
 //   k_dg_face    interface moments, rotational and heat-flux relaxation over h,
-//                Rykov equilibrium, characteristic blend in place, flux F_f
+//                the Rykov record of every face, flux F_f
 //   k_dg_macro   W* = W - dt/V sum sigma A F, point-implicit rotational exchange
 //   k_dg_target  closure coefficients of the Rykov target ((D+3)^2 system)
-//   k_dg_update  flux divergence, relaxation, heat fluxes of phi^{n+1}
+//   k_dg_update  characteristic blend of the interface rows with the face
+//                records' equilibria, flux divergence, relaxation, heat fluxes
+//                of phi^{n+1}
 // Part of the library's single translation unit, after avs_kernels.hip.
 
 namespace avs {
@@ -25,7 +29,18 @@ struct Dg {
   static constexpr int IT = 1 + D, IR = 2 + D, IQT = 3 + D, IQR = 3 + 2 * D, IDT = 3 + 3 * D, IER = 4 + 3 * D,
                        IT0 = 5 + 3 * D, NT = 6 + 3 * D;
   static constexpr int MAXF = Cfg<D>::MAXF;
-  static constexpr int NACC = NW * (1 + NW);   // moments of the base and of the NW closure directions
+  // closure sums: the base triple's moments, then sum A g (1, c_d, c_d c_e (d <= e), |c|^2 c_d, |c|^4)
+  static constexpr int NACC = NW + 2 + 2 * D + D * (D + 1) / 2;
+  // equilibrium record: what one evaluation at a leaf needs.  RA: a face's
+  // blend weight a (of a boundary face the factor of its incoming leaves), a
+  // cell's weight of the part at T; U[D]; q_t / (15 p_t R T_t); (1 - delta)
+  // q_r; 1/(R T_t), 1/(R T), the ratio of the slopes of the two parts, 1/(p_t
+  // R T_t), omega_1/(p R T), (3-D) R T_t, (3-D) R T, R T_r, R T; the
+  // Maxwellians' coefficients (with a face's weights) and 1/(2 R T)
+  static constexpr int RA = 0, RU = 1, RQT = 1 + D, RQR = 1 + 2 * D, RIT = 1 + 3 * D, RI0 = RIT + 1, RS = RIT + 2,
+                       RMT = RIT + 3, RM0 = RIT + 4, RHT = RIT + 5, RH0 = RIT + 6, RRR = RIT + 7, RR0 = RIT + 8,
+                       RCT = RIT + 9, RC0 = RIT + 10, RXT = RIT + 11, RX0 = RIT + 12, REC = 24;
+  static constexpr int NM = FaceMom<D, 3>::NM;
 };
 
 struct DiaGas {
@@ -38,63 +53,84 @@ __device__ __forceinline__ double dg_norm(double rho, double RT) {
   return D == 2 ? rho / (2.0 * M_PI * RT) : rho * pow(2.0 * M_PI * RT, -0.5 * D);
 }
 
-// Rykov equilibrium triple at one leaf (c = xi - U), or, with t_only, the
-// translational part at (T_t, T_r) with zero heat fluxes; gt and g are the
-// Maxwellians at T_t and at T = (3 T_t + 2 T_r)/5.
+// The record of the Rykov equilibrium of (rho, U, T_t, T_r, q_t, q_r): the
+// part at T_t with weight wt, that at T with weight wr.
 template <int D>
-__device__ __forceinline__ void dg_equilibrium(const DiaGas& gp, double rho, const double (&c)[D], double Tt, double Tr,
-                                               const double* qt, const double* qr, bool t_only, double gt, double g,
-                                               double& G, double& H, double& Rr) {
-  const double R = gp.R;
+__device__ __forceinline__ void dg_record(const DiaGas& gp, double rho, const double* U, double Tt, double Tr,
+                                          const double* qt, const double* qr, double wt, double wr, double* r) {
+  using C = Dg<D>;
   const double T = (3.0 * Tt + 2.0 * Tr) / 5.0;
-  double c2 = 0.0, cqt = 0.0, cqr = 0.0;
-#pragma unroll
-  for (int d = 0; d < D; ++d) c2 += c[d] * c[d];
-  const double RTt = R * Tt, RT = R * T;
-  const double hid = 3 - D;
-  if (t_only) {
-    G = gt;
-    H = hid * RTt * gt;
-    Rr = R * Tr * gt;
-    return;
-  }
+  const double RTt = gp.R * Tt, RT = gp.R * T, it = 1.0 / (rho * RTt * RTt), i0 = 1.0 / (rho * RT * RT);
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    cqt += c[d] * qt[d];
-    cqr += c[d] * qr[d];
+    r[C::RU + d] = U[d];
+    r[C::RQT + d] = qt[d] * it / 15.0;
+    r[C::RQR + d] = (1.0 - gp.delta) * qr[d];
   }
-  const double pt = rho * RTt, p = rho * RT;
-  const double at = cqt / (15.0 * pt * RTt), ar = gp.omega0 * cqt / (15.0 * p * RT);
-  const double Gt = gt * (1.0 + at * (c2 / RTt - (D + 2.0)));
-  const double Gr = g * (1.0 + ar * (c2 / RT - (D + 2.0)));
-  const double Ht = hid * RTt * gt * (1.0 + at * (c2 / RTt - D));
-  const double Hr = hid * RT * g * (1.0 + ar * (c2 / RT - D));
-  const double Rt = R * Tr * (Gt + (1.0 - gp.delta) * cqr / (pt * RTt) * gt);
-  const double Rq = RT * (Gr + gp.omega1 * (1.0 - gp.delta) * cqr / (p * RT) * g);
-  const double wt = 1.0 - 1.0 / gp.Z, wr = 1.0 / gp.Z;
-  G = wt * Gt + wr * Gr;
-  H = wt * Ht + wr * Hr;
-  Rr = wt * Rt + wr * Rq;
+  r[C::RIT] = 1.0 / RTt;
+  r[C::RI0] = 1.0 / RT;
+  r[C::RS] = gp.omega0 * (RTt * RTt) / (RT * RT);
+  r[C::RMT] = it;
+  r[C::RM0] = gp.omega1 * i0;
+  r[C::RHT] = (3 - D) * RTt;
+  r[C::RH0] = (3 - D) * RT;
+  r[C::RRR] = gp.R * Tr;
+  r[C::RR0] = RT;
+  r[C::RCT] = wt * dg_norm<D>(rho, RTt);
+  r[C::RC0] = wr * dg_norm<D>(rho, RT);
+  r[C::RXT] = 0.5 / RTt;
+  r[C::RX0] = 0.5 / RT;
 }
 
-// Separable per-axis tables of the Maxwellians at T_t and at T (the
-// half-finest grid carries every leaf centre), built by the whole block
-// from a record r = (rho, U[D], T_t, T_r, ...); followed by a barrier.
-template <int D>
-__device__ __forceinline__ void dg_tables(const double* r, double R, const VGrid& vg, double* tabt, double* tabr,
-                                          double* part, double* parr) {
-  if (threadIdx.x == 0) {
-    const double Tt = r[Dg<D>::IT], T = (3.0 * r[Dg<D>::IT] + 2.0 * r[Dg<D>::IR]) / 5.0;
-    part[P_COEF] = dg_norm<D>(r[0], R * Tt);
-    parr[P_COEF] = dg_norm<D>(r[0], R * T);
-    for (int d = 0; d < 3; ++d) part[P_U + d] = parr[P_U + d] = d < D ? r[1 + d] : 0.0;
-    part[P_I2RT] = 0.5 / (R * Tt);
-    parr[P_I2RT] = 0.5 / (R * T);
+// The two parts of the equilibrium triple of a record (any address space) at
+// one leaf (c = xi - U), from its Maxwellians gt and g0 at T_t and T with
+// their coefficients: with u = a (q.c) gt of the part's slope,
+//   G = gt + u (c^2/(R T) - (D+2)),  H = (3-D) R T (G + 2 u),
+//   R = R T_r (G + (1-delta) q_r.c m gt)
+// (R T in place of R T_r in the part at T).
+template <int D, typename RP>
+__device__ __forceinline__ void dg_parts(RP r, const double (&c)[D], double c2, double gt, double g0, double (&t)[3],
+                                         double (&e)[3]) {
+  using C = Dg<D>;
+  double at = 0.0, cr = 0.0;
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    at += c[d] * r[C::RQT + d];
+    cr += c[d] * r[C::RQR + d];
   }
-  __syncthreads();
-  build_tab<D>(tabt, part, vg);
-  build_tab<D>(tabr, parr, vg);
-  __syncthreads();
+  const double ut = at * gt, u0 = r[C::RS] * at * g0;
+  t[0] = gt + ut * (c2 * r[C::RIT] - (D + 2.0));
+  e[0] = g0 + u0 * (c2 * r[C::RI0] - (D + 2.0));
+  t[1] = D == 2 ? r[C::RHT] * (t[0] + 2.0 * ut) : 0.0;
+  e[1] = D == 2 ? r[C::RH0] * (e[0] + 2.0 * u0) : 0.0;
+  t[2] = r[C::RRR] * (t[0] + r[C::RMT] * cr * gt);
+  e[2] = r[C::RR0] * (e[0] + r[C::RM0] * cr * g0);
+}
+
+// Per-axis tables of the two Maxwellians of `n` records r (stride REC) with
+// their coefficients, [record][part][d][numax], in units of one wave's 64
+// entries; records with a zero bit in `mask` are left out.
+template <int D>
+__device__ __forceinline__ void dg_rec_tables(double* tab, const double* r, int n, unsigned mask, const VGrid& vg) {
+  using C = Dg<D>;
+  const int per = (vg.numax + 63) >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int t = wave; t < n * 2 * D * per; t += BLOCK / 64) {
+    const int row = t / per, u = (t - row * per) * 64 + lane;
+    const int s = row / (2 * D), pd = row - s * 2 * D, part = pd / D, d = pd - part * D;
+    if (!((mask >> s) & 1u) || u >= vg.numax) continue;
+    const double c = (vg.x0[d] + u * vg.hh[d]) - r[s * C::REC + C::RU + d];
+    const double v = exp(-(c * c) * r[s * C::REC + C::RXT + part]);
+    tab[row * vg.numax + u] = d == 0 ? r[s * C::REC + C::RCT + part] * v : v;
+  }
+}
+
+template <int D>
+__device__ __forceinline__ double dg_tab(const double* tab, int numax, const int (&u)[D]) {
+  double g = tab[u[0]];
+#pragma unroll
+  for (int d = 1; d < D; ++d) g *= tab[d * numax + u[d]];
+  return g;
 }
 
 // rho, U, T_t, T_r, T from W = (rho, rho U, rho E, rho E_rot).
@@ -127,358 +163,202 @@ __device__ __forceinline__ void dg_mom(double* m, double A, const double (&xi)[D
   m[2 + D] += A * Rr;
 }
 
+// Pass A with three components: the interface moments are summed here, where
+// the values are in registers.  At 8192 cells x 9988 leaves 1.95 ms for 5.9 GB
+// (3 waves per SIMD: the limiter of three components and the sums share 150
+// registers); the interface stage, which took 2.42 ms with two passes over the
+// stored rows, 0.43 ms without any.
 template <int D>
-__global__ __launch_bounds__(BLOCK) void k_dg_recon(Geo g, Leaves L, double h, const double* __restrict__ vin,
-                                                   double* __restrict__ fv, DiaGas gp, int chunk) {
-  constexpr int MAXF = Dg<D>::MAXF;
-  const int i = xcd_cell(g, blockIdx.x);
-  if (i < 0) return;
-  const int k0 = blockIdx.y * chunk, k1 = min(L.n, k0 + chunk);
-  const int ns = g.nslot[i];
-  const size_t cs = (size_t)g.nc * L.ld, fs = (size_t)g.nf * L.ld;
-  // neighbour rows (a slot without an interior neighbour reads the cell's
-  // own row and is skipped), so that every load of a leaf is issued before
-  // any is used
-  size_t nb[MAXF];
-  unsigned mask = 0;
-#pragma unroll
-  for (int s = 0; s < MAXF; ++s) {
-    const int j = s < ns ? g.s_nbr[i * MAXF + s] : -1;
-    if (j >= 0) mask |= 1u << s;
-    nb[s] = (size_t)(j >= 0 ? j : i) * L.ld;
-  }
-  // the cell's LSQ coefficients and face offsets, held for the leaf loop
-  double cf[MAXF][D], dd[MAXF][D];
-#pragma unroll
-  for (int s = 0; s < MAXF; ++s)
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      cf[s][d] = s < ns ? g.s_lsq[(size_t)(i * MAXF + s) * D + d] : 0.0;
-      dd[s][d] = s < ns ? g.s_d[(size_t)(i * MAXF + s) * D + d] : 0.0;
-    }
-  const double eps2 = g.eps2[i];
-  for (int k = k0 + threadIdx.x; k < k1; k += BLOCK) {
-    double xi[D], A;
-    int u[D];
-    leaf_load<D>(L, k, xi, A, u);
-    double ph[3], gr[3][D], pmax[3], pmin[3], nv[MAXF][3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) ph[p] = vin[p * cs + (size_t)i * L.ld + k];
-#pragma unroll
-    for (int s = 0; s < MAXF; ++s)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) nv[s][p] = vin[p * cs + nb[s] + k];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) gr[p][d] = 0.0;
-      pmax[p] = pmin[p] = ph[p];
-    }
-#pragma unroll
-    for (int s = 0; s < MAXF; ++s) {
-      if (!(mask & (1u << s))) continue;
-#pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        const double v = nv[s][p];
-        const double dv = v - ph[p];
-#pragma unroll
-        for (int d = 0; d < D; ++d) gr[p][d] += dv * cf[s][d];
-        pmax[p] = fmax(pmax[p], v);
-        pmin[p] = fmin(pmin[p], v);
-      }
-    }
-    // Venkatakrishnan psi_f = N/Dn with a = |D2|, b = |D1| (same sign),
-    // N = b^2 + eps^2 + 2ab, Dn = b^2 + 2a^2 + ab + eps^2 (psi = 1 for
-    // D2 = 0); a, b and eps scaled by the power of two above the largest of
-    // them, the minimum over faces kept as a fraction by cross-multiplication
-    // and ended by one division
-    double lg[3][D];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      double d2s[MAXF];
-      const double up0 = pmax[p] - ph[p], dn0 = ph[p] - pmin[p];
-      double mx = fmax(up0, dn0);
-#pragma unroll
-      for (int s = 0; s < MAXF; ++s) {
-        double d2 = 0.0;
-#pragma unroll
-        for (int d = 0; d < D; ++d) d2 += gr[p][d] * dd[s][d];
-        d2s[s] = d2;
-        if (s < ns) mx = fmax(fabs(d2), mx);
-      }
-      double lim = 1.0;
-      // below the smallest normal number the differences carry no
-      // information: the slope stays unlimited
-      if (ns > 0 && mx > 1e-300) {
-        int ex;
-        (void)frexp(mx, &ex);
-        const double inv = ldexp(1.0, -ex);
-        const double e2 = fmin(eps2 * inv * inv, 1e30);
-        const double up = up0 * inv, dn = dn0 * inv;
-        double Nm = 1.0, Dm = 0.0;
-#pragma unroll
-        for (int s = 0; s < MAXF; ++s) {
-          if (s < ns) {
-            const double a = fabs(d2s[s]) * inv;
-            const double b = d2s[s] > 0.0 ? up : dn;
-            const double c = b * b + e2 + 1e-300;
-            const double Nn = c + 2.0 * a * b;
-            const double Dd = c + a * (2.0 * a + b);
-            if (Nn * Dm < Nm * Dd) {
-              Nm = Nn;
-              Dm = Dd;
-            }
-          }
-        }
-        lim = Nm / Dm;
-      }
-#pragma unroll
-      for (int d = 0; d < D; ++d) lg[p][d] = lim * gr[p][d];
-    }
-    for (int s = 0; s < ns; ++s) {
-      const int f = g.s_face[i * MAXF + s];
-      const double sig = g.s_sig[i * MAXF + s];
-      const double sn = normal_speed<D>(xi, g.f_nrm + (size_t)f * D);
-      const bool upwind = sig > 0.0 ? sn >= 0.0 : sn < 0.0;
-      const int Rc = g.f_R[f];
-      const size_t o = (size_t)f * L.ld + k;
-      if (upwind) {
-        double r[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d) r[d] = g.s_d[(size_t)(i * MAXF + s) * D + d] - xi[d] * h;
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          double x = 0.0;
-#pragma unroll
-          for (int d = 0; d < D; ++d) x += lg[p][d] * r[d];
-          fv[p * fs + o] = ph[p] + x;
-        }
-      } else if (Rc < 0) {
-        // incoming leaf of a boundary face: the equilibrium triple of the
-        // wall (unit density, scaled by the wall density later) or of the far field
-        const int b = -1 - Rc;
-        const double* st = g.bc_prim + (size_t)b * (D + 2);
-        const double rho = g.bc_kind[b] == 0 ? 1.0 : st[0];
-        double c2 = 0.0;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          const double c = xi[d] - st[1 + d];
-          c2 += c * c;
-        }
-        const double RT = gp.R * st[1 + D];
-        const double gv = dg_norm<D>(rho, RT) * exp(-c2 / (2.0 * RT));
-        fv[o] = gv;
-        fv[fs + o] = (3 - D) * RT * gv;
-        fv[2 * fs + o] = RT * gv;
-      }
-    }
-  }
+__global__ __launch_bounds__(passA_threads<D>(), 2) void k_dg_recon(Geo g, Leaves L, double h, const double* __restrict__ vin,
+                                                                   const double* __restrict__ bcpair, double R,
+                                                                   double* __restrict__ fv, double* __restrict__ fmom,
+                                                                   int nchs, int chunk) {
+  d_passA<D, double, 3>(g, L, vin, bcpair, h, fv, fmom, nchs, chunk, blockIdx.x, blockIdx.y, R);
 }
 
-// block sum of NN doubles per thread; every thread gets the sums
-template <int NN>
-__device__ __forceinline__ void dg_sum(double* v, double* red) {
-  for (int m = 0; m < NN; ++m) {
-    double x = v[m];
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o);
-    if ((threadIdx.x & 63) == 0) red[(threadIdx.x >> 6) * NN + m] = x;
-  }
-  __syncthreads();
-  if (threadIdx.x < NN) {
-    double x = 0.0;
-    for (int w = 0; w < BLOCK / 64; ++w) x += red[w * NN + threadIdx.x];
-    red[BLOCK / 64 * NN + threadIdx.x] = x;
-  }
-  __syncthreads();
-  for (int m = 0; m < NN; ++m) v[m] = red[BLOCK / 64 * NN + m];
-  __syncthreads();
-}
+// Faces per workgroup: a leaf is loaded once for all of them (bound by FP64
+// arithmetic: two parts of the equilibrium per face and leaf).
+constexpr int DG_FB = 2;
 
-// With rf (the implicit step), also r_f = |U.n| + a + 2 mu/(rho dl) of the
-// predictor: interior faces from the interface moment state (rho, U, T_t of
-// the reconstructed rows, its tau), boundary faces from the cell's W^n and
-// dl = 2 (x_f - x_i).n; a = sqrt(5/3 R T_t), mu/rho = tau R T_t.
+// Interface stage from the moment partials of k_dg_recon: on an interior face
+// the moment state, T_r and the heat fluxes relaxed over h, the record of the
+// equilibrium (weights folded in: it evaluates to b times the equilibrium)
+// and F = a sum A s psi phibar + sum A s psi b g; on a boundary face the
+// outgoing raw flux plus the incoming wall or far-field flux.  With rf (the
+// implicit step), also r_f = |U.n| + a + 2 mu/(rho dl) of the predictor:
+// interior faces from the interface moment state (rho, U, T_t, its tau),
+// boundary faces from the cell's W^n and dl = 2 (x_f - x_i).n; a = sqrt(5/3 R
+// T_t), mu/rho = tau R T_t.
 template <int D>
 __global__ __launch_bounds__(BLOCK) void k_dg_face(Geo g, Leaves L, VGrid vg, GasP vgas, DiaGas gp, double h,
-                                                  double* __restrict__ fv, double* __restrict__ F, int* __restrict__ bad,
-                                                  const double* __restrict__ W, double* __restrict__ rf) {
+                                                  const double* __restrict__ fmom, int nchs, int nch,
+                                                  const double* __restrict__ bden, const double* __restrict__ bfin,
+                                                  double* __restrict__ frec, double* __restrict__ F,
+                                                  int* __restrict__ bad, const double* __restrict__ W,
+                                                  double* __restrict__ rf) {
   using C = Dg<D>;
-  constexpr int NW = C::NW;
+  constexpr int NW = C::NW, NM = C::NM, REC = C::REC, FB = DG_FB, MAXF = C::MAXF, O2 = NW + 2 * D;
   extern __shared__ double lds_d[];
-  __shared__ double red[(BLOCK / 64 + 1) * (Dg<D>::NW + 2 * D + D * (D + 1) / 2)];
-  __shared__ double rec[C::NT], part[NPAR], parr[NPAR];
-  const int f = blockIdx.x;
-  const int Rc = g.f_R[f];
-  const size_t fs = (size_t)g.nf * L.ld;
-  double n[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) n[d] = g.f_nrm[(size_t)f * D + d];
-  double* row0 = fv + (size_t)f * L.ld;
-  if (Rc >= 0) {
-    // one pass of raw moments: the conserved moments, then
-    // e1_d = sum A (xi^2 G + H)/2 xi_d, p_de = sum A G xi_d xi_e (d <= e) and
-    // r1_d = sum A R xi_d, from which the heat fluxes about U follow
-    constexpr int NP = D * (D + 1) / 2, NS = NW + 2 * D + NP;
-    double m[NS];
-    for (int t = 0; t < NS; ++t) m[t] = 0.0;
-    for (int k = threadIdx.x; k < L.n; k += BLOCK) {
-      double xi[D], A;
-      int u[D];
-      leaf_load<D>(L, k, xi, A, u);
-      const double Gv = row0[k], Hv = row0[fs + k], Rv = row0[2 * fs + k];
-      dg_mom<D>(m, A, xi, Gv, Hv, Rv);
-      double xi2 = 0.0;
-#pragma unroll
-      for (int d = 0; d < D; ++d) xi2 += xi[d] * xi[d];
-      const double ek = A * 0.5 * (xi2 * Gv + Hv), ag = A * Gv, ar = A * Rv;
-      int t = NW + 2 * D;
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        m[NW + d] += ek * xi[d];
-        m[NW + D + d] += ar * xi[d];
-#pragma unroll
-        for (int e = d; e < D; ++e) m[t++] += ag * xi[d] * xi[e];
+  __shared__ double red[4 * FB * NW], srec[FB * REC], sm[FB][NM], sF[FB][NW], sn_[FB][D];
+  __shared__ int sok[FB];
+  const int f0 = blockIdx.x * FB, nfb = min(FB, g.nf - f0);
+  // the partials of k_dg_recon, chunk by chunk, L side then R side (a
+  // boundary face has its interior side only)
+  if (threadIdx.x < FB * NM) {
+    const int s = threadIdx.x / NM, t = threadIdx.x - s * NM;
+    double v = 0.0;
+    if (s < nfb) {
+      const double* p0 = fmom + (size_t)(f0 + s) * 2 * nchs * NM + t;
+      const double* p1 = p0 + (size_t)nchs * NM;
+      const bool two = g.f_R[f0 + s] >= 0;
+      for (int c = 0; c < nch; ++c) {
+        v += p0[(size_t)c * NM];
+        if (two) v += p1[(size_t)c * NM];
       }
     }
-    dg_sum<NS>(m, red);
-    double rho, U[D], Ttb, Trb, T;
-    const bool ok = dg_temps<D>(m, gp.R, rho, U, Ttb, Trb, T);
-    // q_t = sum A (|c|^2 G + H)/2 c and q_r = sum A R c with c = xi - U,
-    // expanded in the raw moments
-    double q[C::NQ];
-    {
-      double uu = 0.0, um = 0.0, pu[D];
-#pragma unroll
+    sm[s][t] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < FB) {
+    const int s = threadIdx.x, f = f0 + s;
+    sok[s] = 0;
+    if (s < nfb) {
+      const int Rc = g.f_R[f];
+      double n[D], m[NM], fl[NW];
+      for (int d = 0; d < D; ++d) sn_[s][d] = n[d] = g.f_nrm[(size_t)f * D + d];
+      for (int t = 0; t < NM; ++t) m[t] = sm[s][t];
+      // raw flux: (n.m1, n.m2, n.(e1 + r1), n.r1)
+      for (int t = 0; t < NW; ++t) fl[t] = 0.0;
       for (int d = 0; d < D; ++d) {
-        uu += U[d] * U[d];
-        um += U[d] * m[1 + d];
-      }
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        pu[d] = 0.0;
-#pragma unroll
+        fl[0] += n[d] * m[1 + d];
+        fl[1 + D] += n[d] * (m[NW + d] + m[NW + D + d]);
+        fl[2 + D] += n[d] * m[NW + D + d];
         for (int e = 0; e < D; ++e) {
           const int a = d < e ? d : e, b = d < e ? e : d;
-          pu[d] += U[e] * m[NW + 2 * D + a * D - a * (a - 1) / 2 + (b - a)];
+          fl[1 + d] += n[e] * m[O2 + a * D - a * (a - 1) / 2 + (b - a)];
         }
       }
-      const double e0 = m[1 + D] - m[2 + D];
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        q[d] = m[NW + d] - U[d] * e0 - pu[d] + U[d] * um + 0.5 * uu * (m[1 + d] - U[d] * m[0]);
-        q[D + d] = m[NW + D + d] - U[d] * m[2 + D];
-      }
-    }
-    if (threadIdx.x == 0) {
-      if (!ok) atomicMin(bad, g.nc + f);
-      const double tf = ok ? tau_of(rho, Ttb, vgas) : 1.0;
-      if (rf) {
-        constexpr int MAXF = Dg<D>::MAXF;
-        const size_t so = (size_t)g.f_L[f] * MAXF + g.f_sL[f];
-        double un = 0.0, dl2 = 0.0;
+      if (Rc >= 0) {
+        double rho, U[D], Ttb, Trb, T;
+        const bool ok = dg_temps<D>(m, gp.R, rho, U, Ttb, Trb, T);
+        // q_t = sum A (|c|^2 G + H)/2 c and q_r = sum A R c with c = xi - U,
+        // expanded in the raw moments
+        double qt[D], qr[D], uu = 0.0, um = 0.0;
         for (int d = 0; d < D; ++d) {
-          un += U[d] * n[d];
-          dl2 += g.s_dx[so * D + d] * g.s_dx[so * D + d];
+          uu += U[d] * U[d];
+          um += U[d] * m[1 + d];
         }
-        const double RTt = gp.R * Ttb;
-        rf[f] = fabs(un) + sqrt(5.0 / 3.0 * RTt) + 2.0 * tf * RTt / sqrt(dl2);
+        const double e0 = m[1 + D] - m[2 + D];
+        for (int d = 0; d < D; ++d) {
+          double pu = 0.0;
+          for (int e = 0; e < D; ++e) {
+            const int a = d < e ? d : e, b = d < e ? e : d;
+            pu += U[e] * m[O2 + a * D - a * (a - 1) / 2 + (b - a)];
+          }
+          qt[d] = m[NW + d] - U[d] * e0 - pu + U[d] * um + 0.5 * uu * (m[1 + d] - U[d] * m[0]);
+          qr[d] = m[NW + D + d] - U[d] * m[2 + D];
+        }
+        if (!ok) atomicMin(bad, g.nc + f);
+        const double tf = ok ? tau_of(rho, Ttb, vgas) : 1.0;
+        if (rf) {
+          const size_t so = (size_t)g.f_L[f] * MAXF + g.f_sL[f];
+          double un = 0.0, dl2 = 0.0;
+          for (int d = 0; d < D; ++d) {
+            un += U[d] * n[d];
+            dl2 += g.s_dx[so * D + d] * g.s_dx[so * D + d];
+          }
+          const double RTt = gp.R * Ttb;
+          rf[f] = fabs(un) + sqrt(5.0 / 3.0 * RTt) + 2.0 * tf * RTt / sqrt(dl2);
+        }
+        const double kz = h / (gp.Z * tf);
+        const double ER = (m[2 + D] + kz * (rho * gp.R * T)) / (1.0 + kz);
+        const double Tr = ER / (rho * gp.R);
+        const double Tt = Ttb + (2.0 / 3.0) * (Trb - Tr);
+        const double lt = (1.0 - 1.0 / gp.Z) / 3.0 + gp.omega0 / (3.0 * gp.Z);
+        const double lr = (1.0 - gp.delta) * ((1.0 - 1.0 / gp.Z) * Tr / Tt + gp.omega1 / gp.Z);
+        for (int d = 0; d < D; ++d) {
+          qt[d] = qt[d] / (1.0 + (1.0 - lt) * h / tf);
+          qr[d] = qr[d] / (1.0 + (1.0 - lr) * h / tf);
+        }
+        const double a = tf / (tf + h), b = h / (tf + h);
+        double r[REC];
+        r[REC - 1] = 0.0;
+        dg_record<D>(gp, rho, U, Tt, Tr, qt, qr, b * (1.0 - 1.0 / gp.Z), b / gp.Z, r);
+        r[C::RA] = a;
+        for (int t = 0; t < C::RX0 + 1; ++t) srec[s * REC + t] = frec[(size_t)f * REC + t] = r[t];
+        for (int t = 0; t < NW; ++t) sF[s][t] = a * fl[t];
+        sok[s] = 1;
+      } else {
+        const int bc = -1 - Rc;
+        if (rf) {
+          const int c = g.f_L[f];
+          const size_t so = (size_t)c * MAXF + g.f_sL[f];
+          double rho, U[D], Tt, Tr, T;
+          if (!dg_temps<D>(W + (size_t)c * NW, gp.R, rho, U, Tt, Tr, T)) atomicMin(bad, c);
+          double un = 0.0, dn = 0.0;
+          for (int d = 0; d < D; ++d) {
+            un += U[d] * n[d];
+            dn += g.s_d[so * D + d] * n[d];
+          }
+          const double RTt = gp.R * Tt;
+          rf[f] = fabs(un) + sqrt(5.0 / 3.0 * RTt) + 2.0 * tau_of(rho, Tt, vgas) * RTt / (2.0 * dn);
+        }
+        // incoming flux from the monatomic tables of the boundary: R = R T g
+        const double* fin = bfin + (size_t)f * (D + 2);
+        const double RT = gp.R * g.bc_prim[(size_t)bc * (D + 2) + 1 + D];
+        const double sc = g.bc_kind[bc] == 0 ? fl[0] / bden[f] : 1.0;
+        frec[(size_t)f * REC + C::RA] = sc;
+        const double er = RT * fin[0];
+        for (int t = 0; t < D + 1; ++t) F[(size_t)f * NW + t] = fl[t] + sc * fin[t];
+        F[(size_t)f * NW + 1 + D] = fl[1 + D] + sc * (fin[1 + D] + er);
+        F[(size_t)f * NW + 2 + D] = fl[2 + D] + sc * er;
       }
-      const double kz = h / (gp.Z * tf);
-      const double ER = (m[2 + D] + kz * (rho * gp.R * T)) / (1.0 + kz);
-      const double Tr = ER / (rho * gp.R);
-      const double Tt = Ttb + (2.0 / 3.0) * (Trb - Tr);
-      const double lt = (1.0 - 1.0 / gp.Z) / 3.0 + gp.omega0 / (3.0 * gp.Z);
-      const double lr = (1.0 - gp.delta) * ((1.0 - 1.0 / gp.Z) * Tr / Tt + gp.omega1 / gp.Z);
-      rec[0] = rho;
-      for (int d = 0; d < D; ++d) {
-        rec[1 + d] = U[d];
-        rec[C::IQT + d] = q[d] / (1.0 + (1.0 - lt) * h / tf);
-        rec[C::IQR + d] = q[D + d] / (1.0 + (1.0 - lr) * h / tf);
-      }
-      rec[C::IT] = Tt;
-      rec[C::IR] = Tr;
-      rec[C::IDT] = tf / (tf + h);      // blend weights a, b in the dt/tau and E_rot slots
-      rec[C::IER] = h / (tf + h);
     }
-    __syncthreads();
-    double* tabt = lds_d;
-    double* tabr = lds_d + D * vg.numax;
-    dg_tables<D>(rec, gp.R, vg, tabt, tabr, part, parr);
-    const double a = rec[C::IDT], b = rec[C::IER];
-    double fl[NW];
-    for (int t = 0; t < NW; ++t) fl[t] = 0.0;
-    for (int k = threadIdx.x; k < L.n; k += BLOCK) {
-      double xi[D], A;
-      int u[D];
-      leaf_load<D>(L, k, xi, A, u);
-      double c[D];
+  }
+  __syncthreads();
+  unsigned mask = 0;
+  for (int s = 0; s < FB; ++s) mask |= sok[s] ? 1u << s : 0u;
+  if (!mask) return;
+  dg_rec_tables<D>(lds_d, srec, FB, mask, vg);
+  __syncthreads();
+  double acc[FB * NW];
 #pragma unroll
-      for (int d = 0; d < D; ++d) c[d] = xi[d] - rec[1 + d];
-      double Ge, He, Re;
-      dg_equilibrium<D>(gp, rec[0], c, rec[C::IT], rec[C::IR], rec + C::IQT, rec + C::IQR, false,
-                        maxw<D>(part, tabt, vg.numax, u), maxw<D>(parr, tabr, vg.numax, u), Ge, He, Re);
-      const double Gv = a * row0[k] + b * Ge;
-      const double Hv = a * row0[fs + k] + b * He;
-      const double Rv = a * row0[2 * fs + k] + b * Re;
-      row0[k] = Gv;
-      row0[fs + k] = Hv;
-      row0[2 * fs + k] = Rv;
-      dg_mom<D>(fl, A * normal_speed<D>(xi, n), xi, Gv, Hv, Rv);
-    }
-    dg_sum<NW>(fl, red);
-    if (threadIdx.x < NW) F[(size_t)f * NW + threadIdx.x] = fl[threadIdx.x];
-    return;
-  }
-  const int bc = -1 - Rc;
-  const bool wall = g.bc_kind[bc] == 0;
-  if (rf && threadIdx.x == 0) {
-    constexpr int MAXF = Dg<D>::MAXF;
-    const int c = g.f_L[f];
-    const size_t so = (size_t)c * MAXF + g.f_sL[f];
-    double rho, U[D], Tt, Tr, T;
-    if (!dg_temps<D>(W + (size_t)c * NW, gp.R, rho, U, Tt, Tr, T)) atomicMin(bad, c);
-    double un = 0.0, dn = 0.0;
-    for (int d = 0; d < D; ++d) {
-      un += U[d] * n[d];
-      dn += g.s_d[so * D + d] * n[d];
-    }
-    const double RTt = gp.R * Tt;
-    rf[f] = fabs(un) + sqrt(5.0 / 3.0 * RTt) + 2.0 * tau_of(rho, Tt, vgas) * RTt / (2.0 * dn);
-  }
-  double sc = 1.0;
-  if (wall) {
-    double nd[2] = {0.0, 0.0};
-    for (int k = threadIdx.x; k < L.n; k += BLOCK) {
-      double xi[D], A;
-      int u[D];
-      leaf_load<D>(L, k, xi, A, u);
-      const double s = normal_speed<D>(xi, n);
-      if (s > 0.0) nd[0] += A * s * row0[k];
-      if (s < 0.0) nd[1] += A * (-s) * row0[k];
-    }
-    dg_sum<2>(nd, red);
-    sc = nd[0] / nd[1];
-  }
-  double fl[NW];
-  for (int t = 0; t < NW; ++t) fl[t] = 0.0;
+  for (int t = 0; t < FB * NW; ++t) acc[t] = 0.0;
+  const int nu = vg.numax;
+  double xi_n[D], A_n = 0.0;
+  int u_n[D];
+  if ((int)threadIdx.x < L.n) leaf_load<D>(L, threadIdx.x, xi_n, A_n, u_n);
   for (int k = threadIdx.x; k < L.n; k += BLOCK) {
-    double xi[D], A;
+    double xi[D];
+    const double A = A_n;
     int u[D];
-    leaf_load<D>(L, k, xi, A, u);
-    const double s = normal_speed<D>(xi, n);
-    double Gv = row0[k], Hv = row0[fs + k], Rv = row0[2 * fs + k];
-    if (wall && s < 0.0) {
-      Gv *= sc;
-      Hv *= sc;
-      Rv *= sc;
-      row0[k] = Gv;
-      row0[fs + k] = Hv;
-      row0[2 * fs + k] = Rv;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      xi[d] = xi_n[d];
+      u[d] = u_n[d];
     }
-    dg_mom<D>(fl, A * s, xi, Gv, Hv, Rv);
+    if (k + BLOCK < L.n) leaf_load<D>(L, k + BLOCK, xi_n, A_n, u_n);
+#pragma unroll
+    for (int s = 0; s < FB; ++s) {
+      if (!((mask >> s) & 1u)) continue;
+      const double* r = srec + s * REC;
+      const double* tb = lds_d + s * 2 * D * nu;
+      double c[D], c2 = 0.0, n[D], t[3], e[3];
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        n[d] = sn_[s][d];
+        c[d] = xi[d] - r[C::RU + d];
+        c2 += c[d] * c[d];
+      }
+      dg_parts<D>(r, c, c2, dg_tab<D>(tb, nu, u), dg_tab<D>(tb + D * nu, nu, u), t, e);
+      dg_mom<D>(acc + s * NW, A * normal_speed<D>(xi, n), xi, t[0] + e[0], t[1] + e[1], t[2] + e[2]);
+    }
   }
-  dg_sum<NW>(fl, red);
-  if (threadIdx.x < NW) F[(size_t)f * NW + threadIdx.x] = fl[threadIdx.x];
+  const double v = block_sum_pick<FB * NW>(acc, red);
+  if (threadIdx.x < FB * NW) {
+    const int s = threadIdx.x / NW, t = threadIdx.x - s * NW;
+    if ((mask >> s) & 1u) F[(size_t)f0 * NW + threadIdx.x] = sF[s][t] + v;
+  }
 }
 
 // W* = W - dt/V sum sigma A F; rotational exchange point-implicit with tau
@@ -486,7 +366,7 @@ __global__ __launch_bounds__(BLOCK) void k_dg_face(Geo g, Leaves L, VGrid vg, Ga
 template <int D>
 __global__ void k_dg_macro(Geo g, GasP vgas, DiaGas gp, double dt, const double* __restrict__ F,
                            const double* __restrict__ W, double* __restrict__ Wn, const double* __restrict__ q,
-                           double* __restrict__ tp, int* __restrict__ bad) {
+                           double* __restrict__ tp, double* __restrict__ crec, int* __restrict__ bad) {
   using C = Dg<D>;
   constexpr int MAXF = C::MAXF, NW = C::NW;
   const int i = blockIdx.x * BLOCK + threadIdx.x;
@@ -520,47 +400,84 @@ __global__ void k_dg_macro(Geo g, GasP vgas, DiaGas gp, double dt, const double*
   r[C::IDT] = dt / tt;
   r[C::IER] = (1.0 - 1.0 / gp.Z) * w[2 + D] + rho * gp.R * T / gp.Z;
   r[C::IT0] = T;
+  double* e = crec + (size_t)i * C::REC;
+  e[C::RA] = 1.0 / gp.Z;
+  dg_record<D>(gp, rho, U, Tt, Tr, r + C::IQT, r + C::IQR, 1.0 - 1.0 / gp.Z, 1.0, e);
 }
 
-// Closure accumulators of one leaf: the base triple's moments, then those
-// of the D + 3 directions (1, c, |c|^2) x (g, (3-D) R T g, R T g) at T and
-// (0, 0, R T g).
+// Closure sums of one leaf: the base triple's moments and the moments of g
+// (14 sums in 2-D and 20 in 3-D in place of one per matrix entry, 30 and 42:
+// k_dg_target 443 -> 260 us at 8192 cells x 9988 leaves) from which those of the D + 3 directions (1, c, |c|^2) x (g, (3-D) R T g,
+// R T g) at T and (0, 0, R T g) follow.
 template <int D>
 __device__ __forceinline__ void dg_close_acc(double* acc, double A, const double (&xi)[D], const double (&c)[D],
-                                             double RT, double gv, double G, double H, double Rr) {
-  constexpr int NW = Dg<D>::NW;
+                                             double c2, double gv, double G, double H, double Rr) {
   dg_mom<D>(acc, A, xi, G, H, Rr);
-  double c2 = 0.0;
+  const double ag = A * gv, a2 = ag * c2;
+  double* s = acc + Dg<D>::NW;
+  s[0] += ag;
+  int t = 1 + D;
 #pragma unroll
-  for (int d = 0; d < D; ++d) c2 += c[d] * c[d];
-  const double hid = 3 - D;
-  dg_mom<D>(acc + NW, A, xi, gv, hid * RT * gv, RT * gv);
+  for (int d = 0; d < D; ++d) {
+    const double ac = ag * c[d];
+    s[1 + d] += ac;
 #pragma unroll
-  for (int d = 0; d < D; ++d) dg_mom<D>(acc + NW * (2 + d), A, xi, c[d] * gv, hid * RT * c[d] * gv, RT * c[d] * gv);
-  dg_mom<D>(acc + NW * (2 + D), A, xi, c2 * gv, hid * RT * c2 * gv, RT * c2 * gv);
-  dg_mom<D>(acc + NW * (3 + D), A, xi, 0.0, 0.0, RT * gv);
+    for (int e = d; e < D; ++e) s[t++] += ac * c[e];
+  }
+#pragma unroll
+  for (int d = 0; d < D; ++d) s[t++] += a2 * c[d];
+  s[t] += a2 * c2;
 }
 
-// Reduce the closure accumulators and solve J lambda = target - M[base].
 template <int D>
-__device__ __forceinline__ void dg_close_solve(double* acc, double* red, double* Jm, double* bv, double* xv,
-                                               const double* target, double* lam_out, int i, int* bad) {
-  constexpr int NW = Dg<D>::NW, NA = Dg<D>::NACC;
-  for (int g0 = 0; g0 < NA; g0 += 8) {
-    double v[8];
-    for (int m = 0; m < 8; ++m) v[m] = g0 + m < NA ? acc[g0 + m] : 0.0;
-    dg_sum<8>(v, red);
-    for (int m = 0; m < 8; ++m)
-      if (g0 + m < NA) acc[g0 + m] = v[m];
-  }
+struct DgClose {
+  static constexpr int NW = Dg<D>::NW, NA = Dg<D>::NACC;
+  double red[4 * NA], sum[NA], J[NW * NW], b[NW], x[NW], tg[NW];
+};
+
+// Reduce the closure sums and solve J lambda = target - M[base] (lambda in
+// w.x), J[l][e] the moment l of direction e about U: with <.> = sum A g . and
+// p = 1, c_d, |c|^2 the polynomial of e, <p>, <p c_d> + U_d <p>, <p |xi|^2>/2 +
+// (5 - D)/2 R T <p>, R T <p>.
+template <int D>
+__device__ __forceinline__ void dg_close_solve(double (&acc)[Dg<D>::NACC], DgClose<D>& w, const double* U, double RT,
+                                               double* lam_out, int i, int* bad) {
+  constexpr int NW = Dg<D>::NW, NA = Dg<D>::NACC, N2 = D * (D + 1) / 2;
+  const double v = block_sum_pick<NA>(acc, w.red);
+  if (threadIdx.x < NA) w.sum[threadIdx.x] = v;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    for (int l = 0; l < NW; ++l) {
-      for (int e = 0; e < NW; ++e) Jm[l * NW + e] = acc[NW + NW * e + l];
-      bv[l] = target[l] - acc[l];
+    const double* s = w.sum + NW;
+    auto m2 = [&](int d, int e) {
+      const int a = d < e ? d : e, b = d < e ? e : d;
+      return s[1 + D + a * D - a * (a - 1) / 2 + (b - a)];
+    };
+    double uu = 0.0, tr = 0.0;
+    for (int d = 0; d < D; ++d) {
+      uu += U[d] * U[d];
+      tr += m2(d, d);
     }
-    if (!solve_small<NW>(Jm, bv, xv)) atomicMin(bad, i);
+    for (int e = 0; e < D + 2; ++e) {
+      // <p>, <p c_d>, <p |c|^2>
+      const double m0 = e == 0 ? s[0] : e <= D ? s[e] : tr;
+      const double mc = e == 0 ? tr : e <= D ? s[1 + D + N2 + e - 1] : s[1 + 2 * D + N2];
+      double um = 0.0;
+      for (int d = 0; d < D; ++d) {
+        const double m1 = e == 0 ? s[1 + d] : e <= D ? m2(d, e - 1) : s[1 + D + N2 + d];
+        um += U[d] * m1;
+        w.J[(1 + d) * NW + e] = m1 + U[d] * m0;
+      }
+      w.J[e] = m0;
+      w.J[(1 + D) * NW + e] = 0.5 * (mc + 2.0 * um + uu * m0) + 0.5 * (5 - D) * RT * m0;
+      w.J[(2 + D) * NW + e] = RT * m0;
+    }
+    for (int l = 0; l < NW; ++l) {
+      w.J[l * NW + 2 + D] = l <= D ? 0.0 : RT * s[0];
+      w.b[l] = w.tg[l] - w.sum[l];
+    }
+    if (!solve_small<NW>(w.J, w.b, w.x)) atomicMin(bad, i);
     if (lam_out)
-      for (int e = 0; e < NW; ++e) lam_out[e] = xv[e];
+      for (int e = 0; e < NW; ++e) lam_out[e] = w.x[e];
   }
   __syncthreads();
 }
@@ -569,120 +486,191 @@ __device__ __forceinline__ void dg_close_solve(double* acc, double* red, double*
 // part with zero heat fluxes) plus sum_m lambda_m e_m has the moments
 // (rho, rho U, rho E, E_rot target) of W.
 template <int D>
-__global__ __launch_bounds__(BLOCK) void k_dg_target(Geo g, Leaves L, VGrid vg, DiaGas gp, const double* __restrict__ tp,
-                                                    const double* __restrict__ Wt, double* __restrict__ lam, int init,
-                                                    int* __restrict__ bad) {
+__global__ __launch_bounds__(BLOCK) void k_dg_target(Geo g, Leaves L, VGrid vg, const double* __restrict__ tp,
+                                                    const double* __restrict__ crec, const double* __restrict__ Wt,
+                                                    double* __restrict__ lam, int init, int* __restrict__ bad) {
   using C = Dg<D>;
   constexpr int NW = C::NW;
   extern __shared__ double lds_d[];
-  __shared__ double red[(BLOCK / 64 + 1) * 8];
-  __shared__ double Jm[NW * NW], bv[NW], xv[NW], part[NPAR], parr[NPAR], tg[NW];
+  __shared__ DgClose<D> cw;
+  __shared__ double rec[C::REC];
   const int i = blockIdx.x;
-  const double* r = tp + (size_t)i * C::NT;
-  double* tabt = lds_d;
-  double* tabr = lds_d + D * vg.numax;
   if (threadIdx.x < NW)
-    tg[threadIdx.x] = (threadIdx.x < 2 + D || init) ? Wt[(size_t)i * NW + threadIdx.x] : r[C::IER];
-  dg_tables<D>(r, gp.R, vg, tabt, tabr, part, parr);
-  const double rho = r[0], Tt = r[C::IT], Tr = r[C::IR], RT = gp.R * r[C::IT0];
+    cw.tg[threadIdx.x] =
+        (threadIdx.x < 2 + D || init) ? Wt[(size_t)i * NW + threadIdx.x] : tp[(size_t)i * C::NT + C::IER];
+  if (threadIdx.x < C::RX0 + 1) rec[threadIdx.x] = crec[(size_t)i * C::REC + threadIdx.x];
+  __syncthreads();
+  dg_rec_tables<D>(lds_d, rec, 1, 1u, vg);
+  __syncthreads();
+  const int nu = vg.numax;
+  const double RT = rec[C::RR0], wr = rec[C::RA];
   double acc[C::NACC];
+#pragma unroll
   for (int m = 0; m < C::NACC; ++m) acc[m] = 0.0;
   for (int k = threadIdx.x; k < L.n; k += BLOCK) {
     double xi[D], A;
     int u[D];
     leaf_load<D>(L, k, xi, A, u);
-    double c[D];
+    double c[D], c2 = 0.0, t[3], e[3];
 #pragma unroll
-    for (int d = 0; d < D; ++d) c[d] = xi[d] - r[1 + d];
-    const double gv = maxw<D>(parr, tabr, vg.numax, u);
-    double Ge, He, Re;
-    dg_equilibrium<D>(gp, rho, c, Tt, Tr, r + C::IQT, r + C::IQR, init != 0, maxw<D>(part, tabt, vg.numax, u), gv,
-                      Ge, He, Re);
-    dg_close_acc<D>(acc, A, xi, c, RT, gv, Ge, He, Re);
+    for (int d = 0; d < D; ++d) {
+      c[d] = xi[d] - rec[C::RU + d];
+      c2 += c[d] * c[d];
+    }
+    const double gv = dg_tab<D>(lds_d + D * nu, nu, u);
+    dg_parts<D>(rec, c, c2, dg_tab<D>(lds_d, nu, u), gv, t, e);
+    dg_close_acc<D>(acc, A, xi, c, c2, gv, t[0] + wr * e[0], t[1] + wr * e[1], t[2] + wr * e[2]);
   }
-  dg_close_solve<D>(acc, red, Jm, bv, xv, tg, lam + (size_t)i * NW, i, bad);
+  dg_close_solve<D>(acc, cw, rec + C::RU, RT, lam + (size_t)i * NW, i, bad);
 }
 
 // phi^{n+1} = (phi^n + dt/tau g~ - dt/V sum sigma A xi.n phi_f) / (1 + dt/tau)
-// (init = 0), the closed initial state (init = 1), or the right-hand side of
-// the implicit micro system scaled by dt/V, dt/tau (g~ - phi^n) - dt/V sum
-// sigma A xi.n phi_f (init = 2); heat fluxes of the result about U (not for
-// a right-hand side).
-template <int D>
-__global__ __launch_bounds__(BLOCK) void k_dg_update(Geo g, Leaves L, VGrid vg, DiaGas gp, const double* __restrict__ vin,
-                                                    const double* __restrict__ fv, double* __restrict__ vout,
-                                                    const double* __restrict__ tp, const double* __restrict__ lam,
-                                                    double* __restrict__ q, int init) {
+// (MODE 0), the closed initial state (MODE 1), or the right-hand side of the
+// implicit micro system scaled by dt/V, dt/tau (g~ - phi^n) - dt/V sum
+// sigma A xi.n phi_f (MODE 2); heat fluxes of the result about U (not for a
+// right-hand side).  phi_f = a phibar + b g of an interior face is formed here
+// from the face's record, for both of its cells, so that the interface rows
+// are read by one kernel and never rewritten.  The ten Maxwellians of a leaf
+// are evaluated where they are used: the kernel is bound by the rows' bandwidth
+// (7.9 GB, 2.13 ms at 8192 cells x 9988 leaves, 3.7 TB/s), and per-axis tables
+// in LDS, whose size sets the workgroups per CU, measured within 3 % of it on
+// both sides (4096 cells: 2573 / 2654 us per step with / without tables of 40
+// KiB, 5035 / 5111 at 80 KiB, 4074 / 4021 at 140 KiB; 3-D 1266 / 1240 at 21
+// KiB, 2527 / 2447 at 105 KiB).
+template <int D, int MODE>
+__global__ __launch_bounds__(BLOCK) void k_dg_update(Geo g, Leaves L, const double* __restrict__ vin,
+                                                    const double* __restrict__ fv, const double* __restrict__ frec,
+                                                    double* __restrict__ vout, const double* __restrict__ tp,
+                                                    const double* __restrict__ crec, const double* __restrict__ lam,
+                                                    double* __restrict__ q) {
   using C = Dg<D>;
-  constexpr int MAXF = C::MAXF, NW = C::NW;
-  extern __shared__ double lds_d[];
-  __shared__ double red[(BLOCK / 64 + 1) * 8];
-  __shared__ double part[NPAR], parr[NPAR];
-  const int i = blockIdx.x;
-  const double* r = tp + (size_t)i * C::NT;
-  double* tabt = lds_d;
-  double* tabr = lds_d + D * vg.numax;
-  dg_tables<D>(r, gp.R, vg, tabt, tabr, part, parr);
-  const double rho = r[0], Tt = r[C::IT], Tr = r[C::IR], dtt = r[C::IDT];
-  const double RT = gp.R * r[C::IT0], dtv = g.dtv[i], hid = 3 - D;
-  double la[NW];
-  for (int e = 0; e < NW; ++e) la[e] = lam[(size_t)i * NW + e];
-  const int ns = g.nslot[i];
+  constexpr int MAXF = C::MAXF, NW = C::NW, REC = C::REC, NQ = C::NQ;
+  __shared__ double red[4 * NQ];
+  const int i = xcd_cell(g, blockIdx.x);
+  if (i < 0) return;
+  const int ns = MODE == 1 ? 0 : g.nslot[i];
+  // records in the constant address space: they are the same for every lane
+  // of the workgroup, so each value is a scalar operand where it is used
+  using RP = const __attribute__((address_space(4))) double*;
+  RP rf[MAXF + 1];
+  const double* row[MAXF];
+  double sa[MAXF], nrm[MAXF][D];
   const size_t cs = (size_t)g.nc * L.ld, fs = (size_t)g.nf * L.ld;
-  double qa[C::NQ];
-  for (int t = 0; t < C::NQ; ++t) qa[t] = 0.0;
-  for (int k = threadIdx.x; k < L.n; k += BLOCK) {
-    double xi[D], A;
-    int u[D];
-    leaf_load<D>(L, k, xi, A, u);
-    double c[D], c2 = 0.0;
+  unsigned inner = 0, scaled = 0;
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      c[d] = xi[d] - r[1 + d];
-      c2 += c[d] * c[d];
-    }
-    const double gv = maxw<D>(parr, tabr, vg.numax, u);
-    double Ge, He, Re;
-    dg_equilibrium<D>(gp, rho, c, Tt, Tr, r + C::IQT, r + C::IQR, init == 1, maxw<D>(part, tabt, vg.numax, u), gv,
-                      Ge, He, Re);
-    double poly = la[0];
+  for (int s = 0; s < MAXF; ++s) {
+    const int f = s < ns ? g.s_face[i * MAXF + s] : 0;
+    rf[s] = (RP)(uintptr_t)(frec + (size_t)f * REC);
+    row[s] = fv + (size_t)f * L.ld;
+    sa[s] = s < ns ? g.s_sigA[i * MAXF + s] : 0.0;
+    if (s < ns) {
 #pragma unroll
-    for (int d = 0; d < D; ++d) poly += la[1 + d] * c[d];
-    poly += la[1 + D] * c2;
-    const double tg[3] = {Ge + poly * gv, He + poly * hid * RT * gv, Re + poly * RT * gv + la[2 + D] * RT * gv};
-    double nv[3];
-    if (init == 1) {
-      for (int p = 0; p < 3; ++p) nv[p] = tg[p];
-    } else {
-      double div[3] = {0, 0, 0};
-      for (int s = 0; s < ns; ++s) {
-        const int f = g.s_face[i * MAXF + s];
-        const double w = g.s_sigA[i * MAXF + s] * normal_speed<D>(xi, g.f_nrm + (size_t)f * D);
-        for (int p = 0; p < 3; ++p) div[p] += w * fv[p * fs + (size_t)f * L.ld + k];
-      }
-      for (int p = 0; p < 3; ++p) {
-        const double ph = vin[p * cs + (size_t)i * L.ld + k];
-        nv[p] = init == 2 ? dtt * (tg[p] - ph) - dtv * div[p] : (ph + dtt * tg[p] - dtv * div[p]) / (1.0 + dtt);
-      }
-    }
-    for (int p = 0; p < 3; ++p) vout[p * cs + (size_t)i * L.ld + k] = nv[p];
-    const double et = A * 0.5 * (c2 * nv[0] + nv[1]), er = A * nv[2];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      qa[d] += et * c[d];
-      qa[D + d] += er * c[d];
+      for (int d = 0; d < D; ++d) nrm[s][d] = g.f_nrm[(size_t)f * D + d];
+      const int Rc = g.f_R[f];
+      if (Rc >= 0) inner |= 1u << s;
+      else if (g.bc_kind[-1 - Rc] == 0) scaled |= 1u << s;
     }
   }
-  if (init == 2) return;   // a residual: the heat fluxes follow the micro sweeps
-  dg_sum<C::NQ>(qa, red);
-  if (threadIdx.x < C::NQ) q[(size_t)i * C::NQ + threadIdx.x] = qa[threadIdx.x];
+  rf[MAXF] = (RP)(uintptr_t)(crec + (size_t)i * REC);
+  const double dtt = tp[(size_t)i * C::NT + C::IDT], dtv = g.dtv[i], inv = 1.0 / (1.0 + dtt);
+  RP la = (RP)(uintptr_t)(lam + (size_t)i * NW);
+  // the two Maxwellians of a record at a leaf
+  auto pair = [&](RP r, double c2, double& gt, double& g0) {
+    gt = r[C::RCT] * exp(-c2 * r[C::RXT]);
+    g0 = r[C::RC0] * exp(-c2 * r[C::RX0]);
+  };
+  double qa[NQ];
+#pragma unroll
+  for (int t = 0; t < NQ; ++t) qa[t] = 0.0;
+  for (int k = threadIdx.x; k < L.n; k += BLOCK) {
+    const unsigned ko = (unsigned)k * 8u;
+    double xi[D], A, pf[MAXF][3], ph[3] = {0.0, 0.0, 0.0};
+    int u[D];
+    leaf_load<D>(L, k, xi, A, u);
+    if constexpr (MODE != 1) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) ph[p] = at_(vin + p * cs + (size_t)i * L.ld, ko);
+#pragma unroll
+      for (int s = 0; s < MAXF; ++s)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) pf[s][p] = at_(row[s] + p * fs, ko);
+    }
+    double div[3] = {0.0, 0.0, 0.0};
+    if constexpr (MODE != 1) {
+#pragma unroll
+      for (int s = 0; s < MAXF; ++s) {
+        if (s >= ns) continue;
+        // an opaque pointer: the record is read again for every leaf instead
+        // of being held (MAXF records would spill)
+        RP r = rf[s];
+        __asm__ volatile("" : "+s"(r));
+        const double sn = normal_speed<D>(xi, nrm[s]);
+        if ((inner >> s) & 1u) {
+          double c[D], c2 = 0.0, gt, g0, t[3], e[3];
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            c[d] = xi[d] - r[C::RU + d];
+            c2 += c[d] * c[d];
+          }
+          pair(r, c2, gt, g0);
+          dg_parts<D>(r, c, c2, gt, g0, t, e);
+          const double a = r[C::RA];
+#pragma unroll
+          for (int p = 0; p < 3; ++p) pf[s][p] = a * pf[s][p] + (t[p] + e[p]);
+        } else if (((scaled >> s) & 1u) && sn < 0.0) {
+          const double sc = r[C::RA];
+#pragma unroll
+          for (int p = 0; p < 3; ++p) pf[s][p] *= sc;
+        }
+        const double w = sa[s] * sn;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) div[p] += w * pf[s][p];
+      }
+    }
+    RP r = rf[MAXF];
+    __asm__ volatile("" : "+s"(r));
+    RP l = la;
+    __asm__ volatile("" : "+s"(l));
+    double c[D], c2 = 0.0, gt, g0, t[3], e[3], poly = l[0];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      c[d] = xi[d] - r[C::RU + d];
+      c2 += c[d] * c[d];
+      poly += l[1 + d] * c[d];
+    }
+    poly += l[1 + D] * c2;
+    pair(r, c2, gt, g0);
+    dg_parts<D>(r, c, c2, gt, g0, t, e);
+    const double wr = r[C::RA];
+    const double tg[3] = {t[0] + wr * e[0] + poly * g0, t[1] + wr * e[1] + poly * r[C::RH0] * g0,
+                          t[2] + wr * e[2] + (poly + l[2 + D]) * r[C::RR0] * g0};
+    double nv[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      nv[p] = MODE == 1 ? tg[p]
+              : MODE == 2 ? dtt * (tg[p] - ph[p]) - dtv * div[p]
+                          : (ph[p] + dtt * tg[p] - dtv * div[p]) * inv;
+      *ptr_at_(vout + p * cs + (size_t)i * L.ld, ko) = nv[p];
+    }
+    if constexpr (MODE != 2) {
+      const double et = A * 0.5 * (c2 * nv[0] + nv[1]), er = A * nv[2];
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        qa[d] += et * c[d];
+        qa[D + d] += er * c[d];
+      }
+    }
+  }
+  if constexpr (MODE == 2) return;   // a residual: the heat fluxes follow the micro sweeps
+  const double v = block_sum_pick<NQ>(qa, red);
+  if (threadIdx.x < NQ) q[(size_t)i * NQ + threadIdx.x] = v;
 }
 
 // Record from W (no exchange, zero heat fluxes): the initial state and the
 // heat fluxes after a remap.
 template <int D>
 __global__ void k_dg_initrec(int nc, DiaGas gp, const double* __restrict__ W, double* __restrict__ tp,
-                             int* __restrict__ bad) {
+                             double* __restrict__ crec, int* __restrict__ bad) {
   using C = Dg<D>;
   const int i = blockIdx.x * BLOCK + threadIdx.x;
   if (i >= nc) return;
@@ -697,18 +685,23 @@ __global__ void k_dg_initrec(int nc, DiaGas gp, const double* __restrict__ W, do
   r[C::IDT] = 0.0;
   r[C::IER] = W[(size_t)i * C::NW + 2 + D];
   r[C::IT0] = T;
+  // the translational part alone
+  double* e = crec + (size_t)i * C::REC;
+  e[C::RA] = 0.0;
+  dg_record<D>(gp, rho, U, Tt, Tr, r + C::IQT, r + C::IQR, 1.0, 1.0, e);
 }
 
 // Heat fluxes q_t, q_r of the state about the U of the record tp.
 template <int D>
-__global__ __launch_bounds__(BLOCK) void k_dg_heat(Geo g, Leaves L, const double* __restrict__ v,
+__global__ __launch_bounds__(BLOCK) void k_dg_heat(Geo g, Leaves L, const double* __restrict__ vdf,
                                                   const double* __restrict__ tp, double* __restrict__ q) {
   using C = Dg<D>;
-  __shared__ double red[(BLOCK / 64 + 1) * 8];
+  __shared__ double red[4 * Dg<D>::NQ];
   const int i = blockIdx.x;
   const double* r = tp + (size_t)i * C::NT;
   const size_t cs = (size_t)g.nc * L.ld;
   double qa[C::NQ];
+#pragma unroll
   for (int t = 0; t < C::NQ; ++t) qa[t] = 0.0;
   for (int k = threadIdx.x; k < L.n; k += BLOCK) {
     double xi[D], A;
@@ -721,15 +714,15 @@ __global__ __launch_bounds__(BLOCK) void k_dg_heat(Geo g, Leaves L, const double
       c[d] = xi[d] - r[1 + d];
       c2 += c[d] * c[d];
     }
-    const double et = A * 0.5 * (c2 * v[o] + v[cs + o]), er = A * v[2 * cs + o];
+    const double et = A * 0.5 * (c2 * vdf[o] + vdf[cs + o]), er = A * vdf[2 * cs + o];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       qa[d] += et * c[d];
       qa[D + d] += er * c[d];
     }
   }
-  dg_sum<C::NQ>(qa, red);
-  if (threadIdx.x < C::NQ) q[(size_t)i * C::NQ + threadIdx.x] = qa[threadIdx.x];
+  const double v = block_sum_pick<C::NQ>(qa, red);
+  if (threadIdx.x < C::NQ) q[(size_t)i * C::NQ + threadIdx.x] = v;
 }
 
 // --------------------------------------------- adaptation of the state
@@ -843,40 +836,42 @@ __global__ __launch_bounds__(BLOCK) void k_dg_close(Geo g, Leaves L, VGrid vg, D
   using C = Dg<D>;
   constexpr int NW = C::NW;
   extern __shared__ double lds_d[];
-  __shared__ double red[(BLOCK / 64 + 1) * 8];
-  __shared__ double Jm[NW * NW], bv[NW], xv[NW], part[NPAR], parr[NPAR], rec[C::NT], tg[NW];
+  __shared__ DgClose<D> cw;
+  __shared__ double par[NPAR];
   const int i = blockIdx.x;
   if (threadIdx.x == 0) {
     double rho, U[D], Tt, Tr, T;
     if (!dg_temps<D>(W + (size_t)i * NW, gp.R, rho, U, Tt, Tr, T)) atomicMin(bad, i);
-    rec[0] = rho;
-    for (int d = 0; d < D; ++d) rec[1 + d] = U[d];
-    rec[C::IT] = Tt;
-    rec[C::IR] = Tr;
-    rec[C::IT0] = T;
+    par[P_COEF] = dg_norm<D>(rho, gp.R * T);
+    for (int d = 0; d < 3; ++d) par[P_U + d] = d < D ? U[d] : 0.0;
+    par[P_RT] = gp.R * T;
+    par[P_I2RT] = 0.5 / (gp.R * T);
   }
-  if (threadIdx.x < NW) tg[threadIdx.x] = W[(size_t)i * NW + threadIdx.x];
+  if (threadIdx.x < NW) cw.tg[threadIdx.x] = W[(size_t)i * NW + threadIdx.x];
   __syncthreads();
-  double* tabt = lds_d;
-  double* tabr = lds_d + D * vg.numax;
-  dg_tables<D>(rec, gp.R, vg, tabt, tabr, part, parr);
-  const double RT = gp.R * rec[C::IT0], hid = 3 - D;
+  build_tab<D>(lds_d, par, vg);
+  __syncthreads();
+  const double RT = par[P_RT], hid = 3 - D;
   const size_t cs = (size_t)g.nc * L.ld;
   double acc[C::NACC];
+#pragma unroll
   for (int m = 0; m < C::NACC; ++m) acc[m] = 0.0;
   for (int k = threadIdx.x; k < L.n; k += BLOCK) {
     double xi[D], A;
     int u[D];
     leaf_load<D>(L, k, xi, A, u);
     const size_t o = (size_t)i * L.ld + k;
-    double c[D];
+    double c[D], c2 = 0.0;
 #pragma unroll
-    for (int d = 0; d < D; ++d) c[d] = xi[d] - rec[1 + d];
-    dg_close_acc<D>(acc, A, xi, c, RT, maxw<D>(parr, tabr, vg.numax, u), v[o], v[cs + o], v[2 * cs + o]);
+    for (int d = 0; d < D; ++d) {
+      c[d] = xi[d] - par[P_U + d];
+      c2 += c[d] * c[d];
+    }
+    dg_close_acc<D>(acc, A, xi, c, c2, maxw<D>(par, lds_d, vg.numax, u), v[o], v[cs + o], v[2 * cs + o]);
   }
-  dg_close_solve<D>(acc, red, Jm, bv, xv, tg, nullptr, i, bad);
+  dg_close_solve<D>(acc, cw, par + P_U, RT, nullptr, i, bad);
   double la[NW];
-  for (int e = 0; e < NW; ++e) la[e] = xv[e];
+  for (int e = 0; e < NW; ++e) la[e] = cw.x[e];
   for (int k = threadIdx.x; k < L.n; k += BLOCK) {
     double xi[D], A;
     int u[D];
@@ -884,10 +879,10 @@ __global__ __launch_bounds__(BLOCK) void k_dg_close(Geo g, Leaves L, VGrid vg, D
     double c[D], c2 = 0.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      c[d] = xi[d] - rec[1 + d];
+      c[d] = xi[d] - par[P_U + d];
       c2 += c[d] * c[d];
     }
-    const double gv = maxw<D>(parr, tabr, vg.numax, u);
+    const double gv = maxw<D>(par, lds_d, vg.numax, u);
     double poly = la[0];
 #pragma unroll
     for (int d = 0; d < D; ++d) poly += la[1 + d] * c[d];

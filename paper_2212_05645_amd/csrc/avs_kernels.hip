@@ -575,9 +575,10 @@ __global__ __launch_bounds__(BLOCK) void k_cell_moments(Geo g, Leaves L, const T
 // The stencil of one cell, loaded once per workgroup: row pointers of the
 // cell and of its neighbours (the cell's own row for a boundary face, whose
 // difference is then zero), least-squares coefficients and face offsets.
-template <int D, typename T>
+// NP components: the monatomic gas's, or G, H, R of the diatomic gas.
+template <int D, typename T, int NP = Cfg<D>::P>
 struct Stencil {
-  static constexpr int P = Cfg<D>::P, MAXF = Cfg<D>::MAXF;
+  static constexpr int P = NP, MAXF = Cfg<D>::MAXF;
   // 3-D: the LSQ coefficients and face offsets stay in LDS and are read
   // where they are used (held in scalar registers, the six faces' constants
   // spilled and were reloaded lane by lane on every leaf)
@@ -603,10 +604,10 @@ struct Stencil {
 // registers) or, with lcf/ldd non-null, from LDS: copied to vector registers
 // in 2-D FP32 (registers to spare), read at their use in 3-D (Stencil::kLds,
 // which needs lcf/ldd).
-template <int D, typename T>
+template <int D, typename T, int P>
 __device__ __forceinline__ void load_stencil(const Geo& g, const T* __restrict__ vdf, size_t cs, int ld, int c,
-                                             Stencil<D, T>& st, const T* lcf = nullptr, const T* ldd = nullptr) {
-  constexpr int P = Cfg<D>::P, MAXF = Cfg<D>::MAXF;
+                                             Stencil<D, T, P>& st, const T* lcf = nullptr, const T* ldd = nullptr) {
+  constexpr int MAXF = Cfg<D>::MAXF;
   st.ns = g.nslot[c];
   st.nbmask = 0;
   st.eps2 = (T)g.eps2[c];
@@ -620,7 +621,7 @@ __device__ __forceinline__ void load_stencil(const Geo& g, const T* __restrict__
     for (int p = 0; p < P; ++p) st.nb[s][p] = j >= 0 ? vdf + p * cs + (size_t)j * ld : st.own[p];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      if constexpr (Stencil<D, T>::kLds) {
+      if constexpr (Stencil<D, T, P>::kLds) {
         st.lcf = lcf;
         st.ldd = ldd;
       } else if (lcf) {
@@ -637,15 +638,15 @@ __device__ __forceinline__ void load_stencil(const Geo& g, const T* __restrict__
 // The stencil values of leaf k: the cell's own value and every neighbour's
 // (a slot without an interior neighbour points at the cell's own row),
 // loaded together so that they are in flight at once.
-template <int D, typename T>
+template <int D, typename T, int P = Cfg<D>::P>
 struct StencilVals {
-  T phi[Cfg<D>::P];
-  T nv[Cfg<D>::MAXF][Cfg<D>::P];
+  T phi[P];
+  T nv[Cfg<D>::MAXF][P];
 };
 
-template <int D, typename T>
-__device__ __forceinline__ void load_vals(const Stencil<D, T>& st, int k, StencilVals<D, T>& v) {
-  constexpr int P = Cfg<D>::P, MAXF = Cfg<D>::MAXF;
+template <int D, typename T, int P>
+__device__ __forceinline__ void load_vals(const Stencil<D, T, P>& st, int k, StencilVals<D, T, P>& v) {
+  constexpr int MAXF = Cfg<D>::MAXF;
   const unsigned ko = (unsigned)k * (unsigned)sizeof(T);
 #pragma unroll
   for (int p = 0; p < P; ++p) v.phi[p] = at_(st.own[p], ko);
@@ -655,23 +656,14 @@ __device__ __forceinline__ void load_vals(const Stencil<D, T>& st, int k, Stenci
     for (int p = 0; p < P; ++p) v.nv[s][p] = at_(st.nb[s][p], ko);
 }
 
-// Least-squares gradient and Venkatakrishnan limiter at leaf k, in T.
-// FULL: every one of the MAXF slots is a face with an interior neighbour
-// (known at compile time, so the slot tests vanish from the leaf loop).
-template <int D, typename T, bool FULL = false>
-__device__ __forceinline__ void lim_parts(const Stencil<D, T>& st, const StencilVals<D, T>& sv, T (&phi)[Cfg<D>::P],
-                                          T (&lim)[Cfg<D>::P], T (&grad)[Cfg<D>::P][D],
-                                          T (&d2s)[Cfg<D>::P][Cfg<D>::MAXF]);
-
 // Least-squares gradient, its increments grad . (x_f - x_i) towards the face
 // midpoints (D2 of the limiter, d2s) and the Venkatakrishnan limiter L, per
 // VDF component, in T.  FULL: every one of the MAXF slots is a face with an
 // interior neighbour (known at compile time, so the slot tests vanish).
-template <int D, typename T, bool FULL>
-__device__ __forceinline__ void lim_parts(const Stencil<D, T>& st, const StencilVals<D, T>& sv, T (&phi)[Cfg<D>::P],
-                                          T (&lim)[Cfg<D>::P], T (&grad)[Cfg<D>::P][D],
-                                          T (&d2s)[Cfg<D>::P][Cfg<D>::MAXF]) {
-  constexpr int P = Cfg<D>::P, MAXF = Cfg<D>::MAXF;
+template <int D, typename T, bool FULL, int P>
+__device__ __forceinline__ void lim_parts(const Stencil<D, T, P>& st, const StencilVals<D, T, P>& sv, T (&phi)[P],
+                                          T (&lim)[P], T (&grad)[P][D], T (&d2s)[P][Cfg<D>::MAXF]) {
+  constexpr int MAXF = Cfg<D>::MAXF;
   const int ns = FULL ? MAXF : st.ns;
   // the neighbour extrema are kept as differences from phi (rounding is
   // monotone, so max_j(v_j - phi) equals max_j(v_j) - phi exactly, and the
@@ -833,26 +825,68 @@ __device__ __forceinline__ void face_mom_acc(A* m, A aw, A hw, const A (&x)[D], 
   for (int d = 0; d < D; ++d) m[t++] += eh * x[d];
 }
 
+// The moments one side of a face contributes, from its components u: the
+// monatomic set above, or with three components (diatomic gas: G, H, R)
+// rho, rho U[D], rho E, rho E_rot, e1[D] = sum A xi (|xi|^2 G + H)/2, r1[D] =
+// sum A xi R, m2[D(D+1)/2].
+template <int D, int P>
+struct FaceMom {
+  static constexpr int NM = Cfg<D>::NM;
+  template <typename A>
+  static __device__ __forceinline__ void add(A* m, A aw, const A (&x)[D], const A (&u)[P]) {
+    face_mom_acc<D, A>(m, aw, (A)0.5 * aw, x, u[0], P == 2 ? u[P - 1] : (A)0);
+  }
+};
+template <int D>
+struct FaceMom<D, 3> {
+  static constexpr int NM = D + 3 + 2 * D + D * (D + 1) / 2;
+  static __device__ __forceinline__ void add(double* m, double aw, const double (&x)[D], const double (&u)[3]) {
+    double x2 = x[0] * x[0], ax[D];
+#pragma unroll
+    for (int d = 1; d < D; ++d) x2 += x[d] * x[d];
+    const double ag = aw * u[0], ar = aw * u[2], ek = 0.5 * aw * (x2 * u[0] + u[1]);
+    m[0] += ag;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      ax[d] = ag * x[d];
+      m[1 + d] += ax[d];
+    }
+    m[1 + D] += ek + ar;
+    m[2 + D] += ar;
+    int t = D + 3 + 2 * D;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      m[D + 3 + d] += ek * x[d];
+      m[D + 3 + D + d] += ar * x[d];
+#pragma unroll
+      for (int e = d; e < D; ++e) m[t++] += ax[d] * x[e];
+    }
+  }
+};
+
 // LDS of one pass-A workgroup: the per-cell constants, and one block of
 // reconstructions for the face sums: the upwind value of each face (0 where
 // the cell is downwind), the leaf centre and weight.
-template <int D, typename T>
+template <int D, typename T, int NP = Cfg<D>::P>
 struct PassAShared {
-  static constexpr int P = Cfg<D>::P, MAXF = Cfg<D>::MAXF, NT = passA_threads<D>();
+  static constexpr int P = NP, MAXF = Cfg<D>::MAXF, NT = passA_threads<D>();
+  static constexpr int PS = D == 3 && NP == 3 ? 2 : NP;   // components staged: H is identically zero in 3-D
   using A = typename MomAcc<T>::type;
   T cf[MAXF * D], dd[MAXF * D];
   double nrm[MAXF * D], sig[MAXF];
-  A u[MAXF][P][NT];
+  A u[MAXF][PS][NT];
   A x[D][NT];
+  static constexpr int slot(int p) { return PS == P ? p : p / 2; }
   A a[NT];
 };
 
-template <int D, typename T, bool FULL>
-__device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, const Leaves& L,
+template <int D, typename T, bool FULL, int P>
+__device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& g, const Leaves& L,
                                            const T* __restrict__ vdf, const double* __restrict__ bcpair, double h,
                                            T* __restrict__ fv, double* __restrict__ fmom, int nchs, int i, int k0,
-                                           int k1, int by) {
-  constexpr int P = Cfg<D>::P, MAXF = Cfg<D>::MAXF, NM = Cfg<D>::NM, NT = passA_threads<D>();
+                                           int k1, int by, double Rgas) {
+  using S = PassAShared<D, T, P>;
+  constexpr int MAXF = Cfg<D>::MAXF, NM = FaceMom<D, P>::NM, NT = passA_threads<D>(), PS = S::PS;
   using A = typename MomAcc<T>::type;
   T* const s_cf = sh.cf;
   T* const s_dd = sh.dd;
@@ -870,9 +904,9 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
   // LDS at their use, behind a compiler memory barrier per leaf, so they
   // occupy neither scalar nor vector registers across the leaf loop
   // (sphere FP32 pass A 38.7 -> 33.3 ms).
-  constexpr bool lds_consts = (D == 2 && sizeof(T) == 4) || Stencil<D, T>::kLds;
-  constexpr bool lds_nrm = D == 2 || Stencil<D, T>::kLds;
-  Stencil<D, T> st;
+  constexpr bool lds_consts = (D == 2 && sizeof(T) == 4) || Stencil<D, T, P>::kLds;
+  constexpr bool lds_nrm = D == 2 || Stencil<D, T, P>::kLds;
+  Stencil<D, T, P> st;
   double nrm[MAXF][D];
   unsigned lside = 0;          // bit s: the cell is the L side of face s
   T* row[MAXF][P];
@@ -892,9 +926,9 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
     __syncthreads();
   }
   if constexpr (lds_consts) {
-    load_stencil<D, T>(g, vdf, cs, L.ld, i, st, s_cf, s_dd);
+    load_stencil<D, T, P>(g, vdf, cs, L.ld, i, st, s_cf, s_dd);
   } else {
-    load_stencil<D, T>(g, vdf, cs, L.ld, i, st);
+    load_stencil<D, T, P>(g, vdf, cs, L.ld, i, st);
   }
   const int ns = FULL ? MAXF : st.ns;
 #pragma unroll
@@ -920,10 +954,10 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
   const T th = (T)h;
   // the loads of the next block are issued before the face sums of this one,
   // so that they are in flight across the barriers
-  StencilVals<D, T> sv;
+  StencilVals<D, T, P> sv;
   double xi_n[D], aw_n = 0.0;
   auto load_leaf = [&](int k) {
-    load_vals<D, T>(st, k, sv);
+    load_vals<D, T, P>(st, k, sv);
 #pragma unroll
     for (int d = 0; d < D; ++d) xi_n[d] = at_(L.xi + (size_t)d * L.cap, (unsigned)k * 8u);
     aw_n = at_(L.w, (unsigned)k * 8u);
@@ -938,8 +972,8 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
       const double aw_k = aw_n;
       T phi[P], lim[P], grad[P][D], d2s[P][MAXF];
       // re-read the LDS constants below instead of keeping them live
-      if constexpr (Stencil<D, T>::kLds) __asm__ volatile("" ::: "memory");
-      lim_parts<D, T, FULL>(st, sv, phi, lim, grad, d2s);
+      if constexpr (Stencil<D, T, P>::kLds) __asm__ volatile("" ::: "memory");
+      lim_parts<D, T, FULL, P>(st, sv, phi, lim, grad, d2s);
       // phibar = phi + L grad . (x_f - x_i) - h L grad . xi: the first product
       // is the limiter's D2 of the face, the second is shared by the faces
       T base[P];
@@ -956,7 +990,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
 #pragma unroll
         for (int p = 0; p < P; ++p) u[p] = 0;
         if (FULL || s < ns) {
-          const double sn = normal_speed<D>(xi, Stencil<D, T>::kLds ? s_nrm + s * D : nrm[s]);
+          const double sn = normal_speed<D>(xi, Stencil<D, T, P>::kLds ? s_nrm + s * D : nrm[s]);
           // L side: upwind for sn >= 0; R side: for sn < 0, the complement
           // (sn is finite).  One compare and a lane-mask xor with the
           // uniform side bit.
@@ -972,14 +1006,25 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
             // incoming leaf of a boundary face: the wall or far-field
             // Maxwellian, unscaled (the wall density ratio is applied in pass C)
             const int bc = -1 - g.f_R[g.s_face[i * MAXF + s]];
+            if constexpr (P == 3) {
+              // the equilibrium triple (g, (3 - D) RT g, RT g)
+              const double gv = bcpair[(size_t)bc * Cfg<D>::P * L.cap + k];
+              const double rg = Rgas * g.bc_prim[(size_t)bc * (D + 2) + 1 + D] * gv;
+              const unsigned ko = (unsigned)k * 8u;
+              *ptr_at_(row[s][0], ko) = gv;
+              *ptr_at_(row[s][1], ko) = (3 - D) * rg;
+              *ptr_at_(row[s][2], ko) = rg;
+            } else {
 #pragma unroll
-            for (int p = 0; p < P; ++p)
-              __builtin_nontemporal_store((T)bcpair[((size_t)bc * P + p) * L.cap + k],
-                                          ptr_at_(row[s][p], (unsigned)k * (unsigned)sizeof(T)));
+              for (int p = 0; p < P; ++p)
+                __builtin_nontemporal_store((T)bcpair[((size_t)bc * P + p) * L.cap + k],
+                                            ptr_at_(row[s][p], (unsigned)k * (unsigned)sizeof(T)));
+            }
           }
         }
 #pragma unroll
-        for (int p = 0; p < P; ++p) s_u[s][p][threadIdx.x] = u[p];
+        for (int p = 0; p < P; ++p)
+          if (PS == P || p != 1) s_u[s][S::slot(p)][threadIdx.x] = u[p];
       }
 #pragma unroll
       for (int d = 0; d < D; ++d) s_x[d][threadIdx.x] = (A)xi[d];
@@ -989,7 +1034,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
 #pragma unroll
       for (int s = 0; s < MAXF; ++s)
 #pragma unroll
-        for (int p = 0; p < P; ++p) s_u[s][p][threadIdx.x] = 0;
+        for (int p = 0; p < PS; ++p) s_u[s][p][threadIdx.x] = 0;
       s_a[threadIdx.x] = 0;
 #pragma unroll
       for (int d = 0; d < D; ++d) s_x[d][threadIdx.x] = 0;
@@ -1003,8 +1048,10 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
         A x[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) x[d] = s_x[d][j];
-        const A aw = s_a[j];
-        face_mom_acc<D, A>(acc, aw, (A)0.5 * aw, x, s_u[wave][0][j], P == 2 ? s_u[wave][P - 1][j] : (A)0);
+        A u[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) u[p] = PS == P || p != 1 ? s_u[wave][S::slot(p)][j] : (A)0;
+        FaceMom<D, P>::add(acc, s_a[j], x, u);
       }
     }
     __syncthreads();
@@ -1024,10 +1071,10 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T>& sh, const Geo& g, 
   }
 }
 
-template <int D, typename T>
+template <int D, typename T, int P = Cfg<D>::P>
 __device__ __forceinline__ void d_passA(Geo g, Leaves L, const T* __restrict__ vdf, const double* __restrict__ bcpair,
                                         double h, T* __restrict__ fv, double* __restrict__ fmom, int nchs, int chunk,
-                                        int bx, int by) {
+                                        int bx, int by, double Rgas = 0.0) {
   constexpr int MAXF = Cfg<D>::MAXF;
   const int i = xcd_cell(g, bx);
   if (i < 0) return;
@@ -1038,11 +1085,11 @@ __device__ __forceinline__ void d_passA(Geo g, Leaves L, const T* __restrict__ v
   bool full = g.nslot[i] == MAXF;
 #pragma unroll
   for (int s = 0; s < MAXF; ++s) full = full && g.s_nbr[i * MAXF + s] >= 0;
-  __shared__ PassAShared<D, T> sh;
+  __shared__ PassAShared<D, T, P> sh;
   if (full)
-    passA_cell<D, T, true>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by);
+    passA_cell<D, T, true, P>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by, Rgas);
   else
-    passA_cell<D, T, false>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by);
+    passA_cell<D, T, false, P>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by, Rgas);
 }
 
 // Waves per SIMD pass A asks for: the face-moment accumulators (MAXF x NM

@@ -117,3 +117,43 @@ def test_gradient_tile_remainders(avs, n):
     assert abs(loss - lr) <= 1e-5 * abs(lr)
     G = g.cpu().numpy().astype(np.float64)
     assert np.linalg.norm(G - gr) <= 1e-3 * np.linalg.norm(gr)
+
+
+@pytest.mark.parametrize("D,base,levels,wall", [
+    (2, 8, 4, True),
+    (2, 8, 6, True),     # interface tables beyond 64 KiB of LDS
+    (2, 3, 1, True),     # fewer leaves than threads
+    (2, 90, 0, False),   # one chunk of the moment partials (8100 leaves)
+    (2, 91, 0, True),    # two chunks of the moment partials (8281 leaves)
+    (3, 4, 2, True),
+    (3, 5, 6, False),
+])
+def test_diatomic_sizes(avs, D, base, levels, wall):
+    """Diatomic steps with small and large interface tables, one and two
+    chunks of face-moment partials, an odd number of faces, with and without
+    walls: two explicit steps and one implicit step (1e-12 per explicit step
+    and 1e-11 after the implicit one, as the other diatomic tests)."""
+    if D == 2:
+        mesh = MM.box2d(5, 3, periodic=(True, not wall), sides=dict(bottom=0, top=0) if wall else None,
+                        bcs=[(MM.WALL, (1.0, 0.1, 0.0, 1.1))] if wall else [])
+    else:
+        mesh = MM.box3d(3, 3, 2, periodic=(True, not wall, True))
+    half = 6.0 if D == 2 else 5.0
+    vs = dict(dim=D, lo=(-half,) * D, hi=(half,) * D, base=(base,) * D, max_level=levels)
+    n = mesh['ncells']
+    rng = np.random.default_rng(51 + levels)
+    prim = np.concatenate([1 + 0.1 * rng.uniform(-1, 1, (n, 1)), 0.3 * rng.uniform(-1, 1, (n, D)),
+                           1 + 0.1 * rng.uniform(-1, 1, (n, 1)), 0.8 + 0.1 * rng.uniform(-1, 1, (n, 1))], axis=1)
+    vgas = dict(R=0.5, Pr=0.72, omega=0.74, mu_ref=0.05, T_ref=1.0, model=1)
+    cs, dia, o = dia_pair(avs, mesh, vs, vgas, 2e-3, prim, random_tree(vs, 52, 2 if D == 2 else 1, 0.2))
+    for _ in range(2):
+        dia.step(1)
+        o.step(1)
+    v, W = dia.get_state()
+    assert rel(v, o.phi) < 2e-12 and rel(W, o.W) < 2e-12
+    dia.step_implicit(1, 3, 3)
+    o.step_implicit(1, 3, 3)
+    v, W = dia.get_state()
+    assert rel(v, o.phi) < 1e-11 and rel(W, o.W) < 1e-11
+    dia.close()
+    cs.close()
