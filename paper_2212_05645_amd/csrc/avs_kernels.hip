@@ -118,7 +118,7 @@ __device__ __forceinline__ void block_sum(double (&v)[N], double* red) {
 
 // Block total of each of N per-thread values, returned to thread t < N for
 // entry t (other threads get 0); the same association as block_sum.
-template <int N>
+template <int N, int NT = BLOCK>
 __device__ __forceinline__ double block_sum_pick(double (&v)[N], double* red) {
   int id;
   const double x = wave_totals<N>(v, id);
@@ -127,7 +127,11 @@ __device__ __forceinline__ double block_sum_pick(double (&v)[N], double* red) {
   if (id < N) red[w * N + id] = x;
   __syncthreads();
   const int t = threadIdx.x;
-  const double r = t < N ? (red[t] + red[N + t]) + (red[2 * N + t] + red[3 * N + t]) : 0.0;
+  double r = 0.0;
+  if (t < N)
+#pragma unroll
+    for (int q = 0; q < NT / 64; q += 4)
+      r += (red[q * N + t] + red[(q + 1) * N + t]) + (red[(q + 2) * N + t] + red[(q + 3) * N + t]);
   __syncthreads();
   return r;
 }
@@ -190,16 +194,16 @@ __device__ __forceinline__ void build_tab_r(R* tab, const double* par, const VGr
   }
 }
 
-template <int D, typename R>
-__device__ __forceinline__ R maxw_r(const R* par, const R* tab, int numax, const int (&u)[D]) {
+template <int D, typename R, typename RP = const R*>
+__device__ __forceinline__ R maxw_r(RP par, const R* tab, int numax, const int (&u)[D]) {
   R g = par[P_COEF];
 #pragma unroll
   for (int d = 0; d < D; ++d) g *= tab[d * numax + u[d]];
   return g;
 }
 
-template <int D, typename R>
-__device__ __forceinline__ void shakhov_r(const R* par, R g, const R (&xi)[D], R& G, R& H) {
+template <int D, typename R, typename RP = const R*>
+__device__ __forceinline__ void shakhov_r(RP par, R g, const R (&xi)[D], R& G, R& H) {
   R c2 = 0, cq = 0;
 #pragma unroll
   for (int d = 0; d < D; ++d) {
@@ -1972,14 +1976,22 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
                                         const double* __restrict__ lam, double* __restrict__ mom,
                                         double* __restrict__ qout, int bx) {
   constexpr int P = Cfg<D>::P, MAXF = Cfg<D>::MAXF, N = D + 2;
+  // FP64: the records are read in the constant address space, where they are
+  // scalar operands of the arithmetic (the same for every lane) and take no
+  // vector registers: 134 -> 104 of them, a wave more per SIMD, and no LDS
+  // reads (4096 cells x 256 leaves 31.2 -> 26.2 us, 8192 x 4991 658 -> 603, 3-D
+  // 7680 x 2500 163 -> 156; 32768 x 19678 10.1 -> 9.9 ms, bound by HBM: the
+  // same traffic without arithmetic takes 8.7).  FP32 would have to convert
+  // each value where it is used.
+  constexpr bool SREC = sizeof(T) == 8;
+  using RP = const __attribute__((address_space(4))) double*;
   extern __shared__ double lds_d[];
   T* lds = reinterpret_cast<T*>(lds_d);
-  __shared__ double red[4 * (N + D)];
+  __shared__ double red[(NT < BLOCK ? BLOCK : NT) / 64 * (N + D)];
   __shared__ double dpar[(MAXF + 1) * NPAR];
   __shared__ T spar[(MAXF + 1) * NPAR];
   __shared__ double snrm[MAXF][D];
   __shared__ T snrt[MAXF][D];
-  __shared__ int snbr[MAXF];
   __shared__ T ssa[MAXF], ssc[MAXF];
   __shared__ T slam[N];
   const int i = xcd_cell(g, bx);
@@ -1997,23 +2009,33 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
       v = tpar[(size_t)i * NPAR + m];
     }
     dpar[t] = v;
-    spar[t] = (T)v;
+    if constexpr (!SREC) spar[t] = (T)v;
   }
-  if (threadIdx.x < MAXF) {
+  // interior faces, and those with a wall's density ratio on incoming leaves
+  unsigned inner = 0, scaled = 0;
+  int face[MAXF];
+#pragma unroll
+  for (int s = 0; s < MAXF; ++s) {
+    face[s] = __builtin_amdgcn_readfirstlane(s < ns ? g.s_face[i * MAXF + s] : 0);
+    if (s < ns) {
+      const int Rc = g.f_R[face[s]];
+      if (Rc >= 0) inner |= 1u << s;
+      else if (g.bc_kind[-1 - Rc] == 0) scaled |= 1u << s;
+    }
+  }
+  if (!SREC && threadIdx.x < MAXF) {
     const int s = threadIdx.x;
     const int f = s < ns ? g.s_face[i * MAXF + s] : 0;
-    snbr[s] = s < ns ? g.s_nbr[i * MAXF + s] : -1;
     ssa[s] = s < ns ? (T)g.s_sigA[i * MAXF + s] : (T)0;
     // wall: density ratio of the incoming Maxwellian (first record slot of a
-    // boundary face); far field and interior faces: 1
-    const bool wall = s < ns && g.f_R[f] < 0 && g.bc_kind[-1 - g.f_R[f]] == 0;
-    ssc[s] = wall ? (T)fpar[(size_t)f * NPAR] : (T)1;
+    // boundary face)
+    ssc[s] = (scaled >> s) & 1u ? (T)fpar[(size_t)f * NPAR] : (T)1;
     for (int d = 0; d < D; ++d) {
       snrm[s][d] = g.f_nrm[(size_t)f * D + d];
       snrt[s][d] = (T)snrm[s][d];
     }
   }
-  if (threadIdx.x < N) slam[threadIdx.x] = (T)lam[(size_t)i * N + threadIdx.x];
+  if (!SREC && threadIdx.x < N) slam[threadIdx.x] = (T)lam[(size_t)i * N + threadIdx.x];
   // row pointers from global memory (scalar registers), so that every load
   // and store of the leaf loop is a scalar base plus one 32-bit lane offset
   const T* frow[MAXF][P];
@@ -2048,100 +2070,135 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
   __syncthreads();
 #pragma unroll
   for (int s = 0; s < MAXF; ++s) {
-    if (s < ns && snbr[s] >= 0) build_tab_r<D, T, NT>(lds + s * D * nu, dpar + s * NPAR, vg);
+    if ((inner >> s) & 1u) build_tab_r<D, T, NT>(lds + s * D * nu, dpar + s * NPAR, vg);
   }
   build_tab_r<D, T, NT>(lds + MAXF * D * nu, dpar + MAXF * NPAR, vg);
   __syncthreads();
   const T* tp = spar + MAXF * NPAR;
-  // the unrolled face loop in 3-D and FP32 (2-D FP64, bound by HBM, is no
-  // faster with it and fetches more)
-  bool full = (D == 3 || sizeof(T) == 4) && ns == MAXF;
-#pragma unroll
-  for (int q = 0; q < MAXF; ++q) full = full && snbr[q] >= 0;
-  const T dtt = tp[P_A], dtv = (T)g.dtv[i];
+  const T dtt = SREC ? (T)dpar[MAXF * NPAR + P_A] : tp[P_A], dtv = (T)g.dtv[i];
   const T inv = (T)1 / ((T)1 + dtt);
   double acc[N + D];
 #pragma unroll
   for (int m = 0; m < N + D; ++m) acc[m] = 0.0;
 
-  auto process = [&](int k, const LeafIn<D, T>& x) {
+  // FP64: a leaf's fluxes and target from scalar records
+  auto process_s = [&](int k, const LeafIn<D, T>& x) {
+    double div[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) div[p] = 0.0;
+#pragma unroll
+    for (int s = 0; s < MAXF; ++s) {
+      if (s >= ns) continue;
+      // opaque: the record is read again for every leaf, not held (all the
+      // faces' records together would spill)
+      int f = face[s];
+      __asm__ volatile("" : "+s"(f));
+      RP r = (RP)(uintptr_t)fpar + (size_t)f * NPAR;
+      RP nr = (RP)(uintptr_t)g.f_nrm + (size_t)f * D;
+      double n[D], pf[P];
+#pragma unroll
+      for (int d = 0; d < D; ++d) n[d] = nr[d];
+#pragma unroll
+      for (int p = 0; p < P; ++p) pf[p] = x.row[s][p];
+      const double sw = normal_speed<D>(x.xi, n);
+      if ((inner >> s) & 1u) {
+        const double gv = maxw_r<D, double, RP>(r, lds_d + s * D * nu, nu, x.u);
+        double G, H;
+        shakhov_r<D, double, RP>(r, gv, x.xi, G, H);
+        pf[0] = r[P_A] * pf[0] + r[P_B] * G;
+        if (P == 2) pf[P - 1] = r[P_A] * pf[P - 1] + r[P_B] * H;
+      } else if (((scaled >> s) & 1u) && sw < 0.0) {
+        const double sc = r[0];
+#pragma unroll
+        for (int p = 0; p < P; ++p) pf[p] = sc * pf[p];
+      }
+      const double w = ((RP)(uintptr_t)g.s_sigA)[(size_t)i * MAXF + s] * sw;
+#pragma unroll
+      for (int p = 0; p < P; ++p) div[p] += w * pf[p];
+    }
+    int ic = __builtin_amdgcn_readfirstlane(i);
+    __asm__ volatile("" : "+s"(ic));
+    RP r = (RP)(uintptr_t)tpar + (size_t)ic * NPAR;
+    RP la = (RP)(uintptr_t)lam + (size_t)ic * N;
+    const double gv = maxw_r<D, double, RP>(r, lds_d + MAXF * D * nu, nu, x.u);
+    double G, H, c[D], c2 = 0.0, poly = la[0], xi2 = 0.0;
+    shakhov_r<D, double, RP>(r, gv, x.xi, G, H);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      c[d] = x.xi[d] - r[P_U + d];
+      c2 += c[d] * c[d];
+      xi2 += x.xi[d] * x.xi[d];
+      poly += la[1 + d] * c[d];
+    }
+    poly += la[D + 1] * c2;
+    const double tgt[2] = {G + poly * gv, H + poly * r[P_RT] * gv};
+    double nv[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      nv[p] = RES ? dtt * (tgt[p] - x.phi[p]) - dtv * div[p] : (x.phi[p] + dtt * tgt[p] - dtv * div[p]) * inv;
+      *ptr_at_(orow[p], (unsigned)k * 8u) = nv[p];
+    }
+    if constexpr (RES) return;
+    const double Hn = P == 2 ? nv[P - 1] : 0.0;
+    mom_acc<D>(acc, x.A, x.xi, xi2, nv[0], Hn);
+    const double e = 0.5 * x.A * (c2 * nv[0] + Hn);
+#pragma unroll
+    for (int d = 0; d < D; ++d) acc[N + d] += e * c[d];
+  };
+  // FP32: from the records in LDS
+  auto process_v = [&](int k, const LeafIn<D, T>& x) {
     T xr[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) xr[d] = (T)x.xi[d];
     T div[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) div[p] = 0;
-    if (full) {
-      // every slot an interior face: the face loop unrolled, rows taken by
-      // static index.  The empty asm with a memory clobber makes each face
-      // read its record from LDS where it is used; without it the compiler
-      // keeps all the faces' records live across the leaf loop (168-256
-      // VGPRs).
+    // faces unrolled, rows taken by static index; FULL: every slot an interior
+    // face, without the tests (3-D 6.2 ms, 6.35 with them; triangles, which
+    // have an empty slot, 129 -> 125 us against a loop over the faces).  The
+    // empty asm with a memory clobber makes each face read its record from LDS
+    // where it is used; without it the compiler keeps all the faces' records
+    // live across the leaf loop (168-256 VGPRs).
+    auto faces = [&](auto full_) {
+      constexpr bool FULL = decltype(full_)::value;
 #pragma unroll
       for (int s = 0; s < MAXF; ++s) {
+        if (!FULL && s >= ns) continue;
         __asm__ volatile("" ::: "memory");
         T pf[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) pf[p] = x.row[s][p];
-        const T* par = spar + s * NPAR;
-        const T gv = maxw_r<D, T>(par, lds + s * D * nu, nu, x.u);
-        T G, H;
-        shakhov_r<D, T>(par, gv, xr, G, H);
-        pf[0] = par[P_A] * pf[0] + par[P_B] * G;
-        if (P == 2) pf[P - 1] = par[P_A] * pf[P - 1] + par[P_B] * H;
-        T sw;
-        if constexpr (sizeof(T) == 8) {
-          sw = normal_speed<D>(x.xi, snrm[s]);
-        } else {
+        T sw;     // xi . n, the flux weight
+        if (FULL || ((inner >> s) & 1u)) {
+          const T* par = spar + s * NPAR;
+          const T gv = maxw_r<D, T>(par, lds + s * D * nu, nu, x.u);
+          T G, H;
+          shakhov_r<D, T>(par, gv, xr, G, H);
+          pf[0] = par[P_A] * pf[0] + par[P_B] * G;
+          if (P == 2) pf[P - 1] = par[P_A] * pf[P - 1] + par[P_B] * H;
+          // no side is chosen here, so the weight is formed in T (both cells
+          // of the face form the same value: the flux stays antisymmetric)
           sw = xr[0] * snrt[s][0];
 #pragma unroll
           for (int d = 1; d < D; ++d) sw += xr[d] * snrt[s][d];
+        } else {
+          // boundary face: the incoming side is taken in FP64, as in pass A
+          const double sn = normal_speed<D>(x.xi, snrm[s]);
+          if (((scaled >> s) & 1u) && sn < 0.0) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) pf[p] = ssc[s] * pf[p];
+          }
+          sw = (T)sn;
         }
         const T w = ssa[s] * sw;
 #pragma unroll
         for (int p = 0; p < P; ++p) div[p] += w * pf[p];
       }
-    } else
-    // one face at a time: its record is read from LDS inside the loop, so
-    // only one face's parameters are live in registers
-#pragma unroll 1
-    for (int s = 0; s < ns; ++s) {
-      // static indices only (a dynamic index would move the rows to scratch memory)
-      T pf[P];
-#pragma unroll
-      for (int q = 0; q < MAXF; ++q)
-#pragma unroll
-        for (int p = 0; p < P; ++p) pf[p] = q == s ? x.row[q][p] : (q == 0 ? (T)0 : pf[p]);
-      T sw;     // xi . n, the flux weight
-      if (snbr[s] >= 0) {
-        const T* par = spar + s * NPAR;
-        const T gv = maxw_r<D, T>(par, lds + s * D * nu, nu, x.u);
-        T G, H;
-        shakhov_r<D, T>(par, gv, xr, G, H);
-        pf[0] = par[P_A] * pf[0] + par[P_B] * G;
-        if (P == 2) pf[P - 1] = par[P_A] * pf[P - 1] + par[P_B] * H;
-        // no side is chosen here, so the weight is formed in T (both cells
-        // of the face form the same value: the flux stays antisymmetric)
-        if constexpr (sizeof(T) == 8) {
-          sw = normal_speed<D>(x.xi, snrm[s]);
-        } else {
-          sw = xr[0] * snrt[s][0];
-#pragma unroll
-          for (int d = 1; d < D; ++d) sw += xr[d] * snrt[s][d];
-        }
-      } else {
-        // boundary face: the incoming side is taken in FP64, as in pass A
-        const double sn = normal_speed<D>(x.xi, snrm[s]);
-        if (sn < 0.0) {
-#pragma unroll
-          for (int p = 0; p < P; ++p) pf[p] = ssc[s] * pf[p];
-        }
-        sw = (T)sn;
-      }
-      const T w = ssa[s] * sw;
-#pragma unroll
-      for (int p = 0; p < P; ++p) div[p] += w * pf[p];
-    }
+    };
+    if (inner == (1u << MAXF) - 1u)
+      faces(std::true_type{});
+    else
+      faces(std::false_type{});
     // closed Shakhov target
     const T gv = maxw_r<D, T>(tp, lds + MAXF * D * nu, nu, x.u);
     T G, H;
@@ -2182,6 +2239,10 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
     for (int d = 0; d < D; ++d) acc[N + d] += e * cd[d];
   };
 
+  auto process = [&](int k, const LeafIn<D, T>& x) {
+    if constexpr (SREC) process_s(k, x);
+    else process_v(k, x);
+  };
   if constexpr (!TWO) {
     for (int k = threadIdx.x; k < L.n; k += NT) {
       if (!EARLY || k != (int)threadIdx.x) load(k, x0);
@@ -2205,11 +2266,10 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
     if (m < N) mom[(size_t)i * N + m] = v;
     else if (m < N + D) qout[(size_t)i * D + m - N] = v;
   } else {
-    block_sum<N + D>(acc, red);
-    if (threadIdx.x == 0) {
-      for (int m = 0; m < N; ++m) mom[(size_t)i * N + m] = acc[m];
-      for (int d = 0; d < D; ++d) qout[(size_t)i * D + d] = acc[N + d];
-    }
+    const int t = threadIdx.x;
+    const double v = block_sum_pick<N + D, NT>(acc, red);
+    if (t < N) mom[(size_t)i * N + t] = v;
+    else if (t < N + D) qout[(size_t)i * D + t - N] = v;
   }
 }
 
