@@ -422,11 +422,22 @@ avs_status launch_init_vdf(avs_ctx* ctx, bool close = true) {
   return AVS_OK;
 }
 
+// Cells per workgroup of the moments pass: 4 measured best of 1, 2, 4 and 8
+// (the 36 864-cell FP32 sphere 1845 / 1124 / 810 / 851 us), from the cell
+// count at which the groups fill the chip (one cell / four: 1024 cells x 4000
+// leaves FP64 15.6 / 15.7 us, 16000 FP32 45.8 / 50; 1536 cells 30.9 / 25.3 and
+// 73 / 59; 144 cells x 256 leaves 6.5 / 7.0).
+constexpr int MOM_GROUP = 4, MOM_GROUP_CELLS = 1280;
 template <int D, typename T>
 avs_status launch_moments(avs_ctx* ctx) {
   ProfScope ps(ctx, K_MOMENTS);
-  k_cell_moments<D, T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->geo, ctx->leaves(ctx->lcur), (const T*)ctx->vdf[ctx->cur],
-                                                          ctx->W, ctx->mom, ctx->q);
+  const Leaves L = ctx->leaves(ctx->lcur);
+  const T* v = (const T*)ctx->vdf[ctx->cur];
+  if (ctx->nc >= MOM_GROUP_CELLS)
+    k_cell_moments<D, T, MOM_GROUP><<<(ctx->nc + MOM_GROUP - 1) / MOM_GROUP, BLOCK, 0, ctx->stream>>>(ctx->geo, L, v, ctx->W,
+                                                                                                  ctx->mom, ctx->q);
+  else
+    k_cell_moments<D, T, 1><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->geo, L, v, ctx->W, ctx->mom, ctx->q);
   CKL();
   return AVS_OK;
 }
@@ -675,13 +686,7 @@ avs_status launch_step_implicit(avs_ctx* ctx, int n_macro, int n_micro, T* dphi,
   }
   std::swap(ctx->W, ctx->Wn);
   ctx->cur ^= 1;
-  {
-    ProfScope ps(ctx, K_MOMENTS);
-    k_cell_moments<D, T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->geo, L, (const T*)ctx->vdf[ctx->cur], ctx->W, ctx->mom,
-                                                            ctx->q);
-    CKL();
-  }
-  return AVS_OK;
+  return launch_moments<D, T>(ctx);
 }
 
 template <int D>

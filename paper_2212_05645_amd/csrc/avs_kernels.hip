@@ -540,39 +540,54 @@ __device__ __forceinline__ void state_mom_acc(double* acc, const double (&xi)[D]
   for (int d = 0; d < D; ++d) acc[N + d] += e * c[d];
 }
 
-template <int D, typename T>
+// CB cells per workgroup: a leaf (its centre and weight, 3 to 8 times the
+// bytes of the state it weights) is loaded once for all of them.
+template <int D, typename T, int CB>
 __device__ __forceinline__ void d_cell_moments(Geo g, Leaves L, const T* __restrict__ vdf,
                                                const double* __restrict__ W, double* __restrict__ mom,
                                                double* __restrict__ q, int bx) {
-  constexpr int N = D + 2;
-  __shared__ double red[4 * (N + D)];
-  const int i = bx;
+  constexpr int N = D + 2, P = Cfg<D>::P, NQ = N + D;
+  __shared__ double red[4 * CB * NQ];
+  const int i0 = bx * CB;
   const size_t cs = (size_t)g.nc * L.ld;
-  double U[D];
+  double U[CB][D], acc[CB * NQ];
+  const T* row[CB];
 #pragma unroll
-  for (int d = 0; d < D; ++d) U[d] = W[(size_t)i * N + 1 + d] / W[(size_t)i * N];
-  double acc[N + D];
+  for (int b = 0; b < CB; ++b) {
+    const int i = min(i0 + b, g.nc - 1);
+    row[b] = vdf + (size_t)i * L.ld;
 #pragma unroll
-  for (int m = 0; m < N + D; ++m) acc[m] = 0.0;
+    for (int d = 0; d < D; ++d) U[b][d] = W[(size_t)i * N + 1 + d] / W[(size_t)i * N];
+  }
+#pragma unroll
+  for (int m = 0; m < CB * NQ; ++m) acc[m] = 0.0;
   for (int k = threadIdx.x; k < L.n; k += BLOCK) {
     double xi[D], A;
     int u[D];
     leaf_load<D>(L, k, xi, A, u);
-    const double G = ld_(vdf + (size_t)i * L.ld + k);
-    const double H = (D == 2) ? ld_(vdf + cs + (size_t)i * L.ld + k) : 0.0;
-    state_mom_acc<D>(acc, xi, A, U, G, H);
+    T v[CB][P];
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+#pragma unroll
+      for (int p = 0; p < P; ++p) v[b][p] = at_(row[b] + p * cs, (unsigned)k * (unsigned)sizeof(T));
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+      state_mom_acc<D>(acc + b * NQ, xi, A, U[b], (double)v[b][0], P == 2 ? (double)v[b][P - 1] : 0.0);
   }
-  block_sum<N + D>(acc, red);
-  if (threadIdx.x == 0) {
-    for (int m = 0; m < N; ++m) mom[(size_t)i * N + m] = acc[m];
-    for (int d = 0; d < D; ++d) q[(size_t)i * D + d] = acc[N + d];
+  const double x = block_sum_pick<CB * NQ>(acc, red);
+  if (threadIdx.x < CB * NQ) {
+    const int b = threadIdx.x / NQ, m = threadIdx.x - b * NQ, i = i0 + b;
+    if (i < g.nc) {
+      if (m < N) mom[(size_t)i * N + m] = x;
+      else q[(size_t)i * D + m - N] = x;
+    }
   }
 }
 
-template <int D, typename T>
+template <int D, typename T, int CB>
 __global__ __launch_bounds__(BLOCK) void k_cell_moments(Geo g, Leaves L, const T* __restrict__ vdf,
                              const double* __restrict__ W, double* __restrict__ mom, double* __restrict__ q) {
-  d_cell_moments<D, T>(g, L, vdf, W, mom, q, blockIdx.x);
+  d_cell_moments<D, T, CB>(g, L, vdf, W, mom, q, blockIdx.x);
 }
 
 // ------------------------------------------------- limited gradient (S2-S3)
@@ -3037,7 +3052,7 @@ __global__ __launch_bounds__(BLOCK) void kb_cell_moments(const RemapArgs<T>* __r
                                                          const int* __restrict__ off, int ncase) {
   const int c = find_case(off, ncase, blockIdx.x);
   const RemapArgs<T>* a = args + c;
-  d_cell_moments<D, T>(global_geo(a->g), global_leaves(a->Ln), gptr(a->vout), gptr(a->W), gptr(a->mom), gptr(a->q),
+  d_cell_moments<D, T, 1>(global_geo(a->g), global_leaves(a->Ln), gptr(a->vout), gptr(a->W), gptr(a->mom), gptr(a->q),
                        blockIdx.x - off[c]);
 }
 
