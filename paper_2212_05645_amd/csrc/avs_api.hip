@@ -763,19 +763,19 @@ avs_status launch_remap(avs_ctx* ctx, int correction) {
   }
   const Leaves Lo = ctx->leaves(ctx->lcur);
   const Leaves Ln = ctx->leaves(ctx->lcur ^ 1);
+  const T* vin = (const T*)ctx->vdf[ctx->cur];
   T* vout = (T*)ctx->vdf[ctx->cur ^ 1];
-  {
+  if (correction == 0) {
     ProfScope ps(ctx, K_REMAP_GATHER);
-    k_remap_gather<D, T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->geo, Lo, Ln, ctx->pkind, ctx->psrc,
-                                                            (const T*)ctx->vdf[ctx->cur], vout, ctx->momp);
+    k_remap_gather<D, T><<<ctx->nc, BLOCK, 0, ctx->stream>>>(ctx->geo, Lo, Ln, ctx->pkind, ctx->psrc, vin, vout);
     CKL();
-  }
-  if (correction > 0) {
-    // the correction also leaves the moments and heat flux of the new state
+  } else {
+    // also leaves the moments and heat flux of the new state
     // (remap_leaves_moments)
     ProfScope ps(ctx, K_REMAP_CORRECT);
     k_remap_correct<D, T><<<ctx->nc, BLOCK, (size_t)2 * D * ctx->vg.numax * sizeof(double), ctx->stream>>>(
-        ctx->geo, Ln, ctx->vg, ctx->gas, correction, ctx->W, ctx->momp, vout, ctx->bad, ctx->mom, ctx->q);
+        ctx->geo, Lo, Ln, ctx->vg, ctx->gas, correction, ctx->pkind, ctx->psrc, ctx->W, vin, vout, ctx->bad, ctx->mom,
+        ctx->q);
     CKL();
   }
   return AVS_OK;
@@ -2504,7 +2504,6 @@ avs_status batch_remap_launch(avs_batch* b, int correction) {
     a.psrc = c->psrc;
     a.vin = (const T*)c->vdf[c->cur];
     a.vout = (T*)c->vdf[c->cur ^ 1];
-    a.momp = c->momp;
     a.W = c->W;
     a.mom = c->mom;
     a.q = c->q;
@@ -2515,8 +2514,8 @@ avs_status batch_remap_launch(avs_batch* b, int correction) {
     a.nbl = (a.Ln.n + BLOCK - 1) / BLOCK;
     args[i] = a;
     numax = std::max(numax, c->vg.numax);
-    // the correction kernel forms the moments of the new state itself
-    const int cnt[BR_N] = {c->nc, correction > 0 ? c->nc : 0, c->nbc > 0 ? a.nbl * c->nbc : 0, c->n_bnd,
+    // the correction kernel gathers by itself and forms the moments of the new state
+    const int cnt[BR_N] = {correction > 0 ? 0 : c->nc, correction > 0 ? c->nc : 0, c->nbc > 0 ? a.nbl * c->nbc : 0, c->n_bnd,
                            remap_leaves_moments(correction) ? 0 : c->nc};
     for (int k = 0; k < BR_N; ++k) off[k * (n + 1) + i + 1] = off[k * (n + 1) + i] + cnt[k];
   }

@@ -2584,84 +2584,91 @@ __global__ void k_scatter(Leaves L, const int8_t* __restrict__ eff, const int* _
 }
 
 // ------------------------------------------------------- remap (Sec. 3.2)
-// Gather the new rows (copy or pairwise mean of 2^D brothers) and the
-// moments W' of the result.
-template <int D, typename T>
-__device__ __forceinline__ void d_remap_gather(Geo g, Leaves Lo, Leaves Ln, const int* __restrict__ kind,
-                                               const int* __restrict__ src, const T* __restrict__ vin,
-                                               T* __restrict__ vout, double* __restrict__ momp, int bx) {
+// The value of a new leaf: its source's (copied or split leaf), or the
+// pairwise mean of its 2^D children, whose values follow the source's.
+template <int D, typename T, int P>
+__device__ __forceinline__ void gather_merge(const T* const (&row)[P], int k, bool merged, T (&v)[P]) {
 #pragma clang fp contract(off)
-  constexpr int P = Cfg<D>::P, N = D + 2;
-  __shared__ double red[4 * N];
-  const int i = bx;
-  const size_t cso = (size_t)g.nc * Lo.ld, csn = (size_t)g.nc * Ln.ld;
-  double acc[N];
-  for (int m = 0; m < N; ++m) acc[m] = 0.0;
-  // four leaves per thread in flight: the source indices and leaf data of
-  // the group first, then every leaf's first source value, and only then
-  // the other children of merged leaves, the stores and the sums (a leaf at
-  // a time made each row read wait on its index load).  The sums keep the
-  // order of one leaf after another; a slot past the end re-reads the last
-  // leaf and is dropped.
-  constexpr int U = 4;
+  if (!merged) return;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const T* r = row[p] + k;
+    if (D == 2) {
+      v[p] = ((v[p] + r[1]) + (r[2] + r[3])) * (T)0.25;
+    } else {
+      v[p] = (((v[p] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]))) * (T)0.125;
+    }
+  }
+}
+
+// f(j, value) for this thread's new leaves, four of them in flight: the source
+// indices of the group first, then every leaf's first source value, and only
+// then the other children of merged leaves and f (a leaf at a time made each
+// row read wait on its index load).  A slot past the end re-reads the last
+// leaf and is dropped.
+template <int D, typename T, typename F>
+__device__ __forceinline__ void gather_leaves(const Geo& g, const Leaves& Lo, const Leaves& Ln,
+                                              const int* __restrict__ kind, const int* __restrict__ src,
+                                              const T* __restrict__ vin, int i, F f) {
+  constexpr int P = Cfg<D>::P, U = 4;
+  const T* row[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) row[p] = vin + (p * (size_t)g.nc + i) * Lo.ld;
   for (int j0 = threadIdx.x; j0 < Ln.n; j0 += U * BLOCK) {
     int kk[U];
     bool mg[U];
-    double xi[U][D], A[U];
     T v[U][P];
 #pragma unroll
     for (int t = 0; t < U; ++t) {
       const int j = min(j0 + t * BLOCK, Ln.n - 1);
       kk[t] = src[j];
       mg[t] = kind[j] == 2;
-      int u[D];
-      leaf_load<D>(Ln, j, xi[t], A[t], u);
     }
 #pragma unroll
     for (int t = 0; t < U; ++t)
 #pragma unroll
-      for (int p = 0; p < P; ++p) v[t][p] = vin[p * cso + (size_t)i * Lo.ld + kk[t]];
+      for (int p = 0; p < P; ++p) v[t][p] = row[p][kk[t]];
 #pragma unroll
     for (int t = 0; t < U; ++t) {
       const int j = j0 + t * BLOCK;
       if (j >= Ln.n) break;
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        if (mg[t]) {
-          const T* r = vin + p * cso + (size_t)i * Lo.ld + kk[t];
-          if (D == 2) {
-            v[t][p] = ((v[t][p] + r[1]) + (r[2] + r[3])) * (T)0.25;
-          } else {
-            v[t][p] = (((v[t][p] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]))) * (T)0.125;
-          }
-        }
-        vout[p * csn + (size_t)i * Ln.ld + j] = v[t][p];
-      }
-      double xi2 = 0.0;
-      for (int d = 0; d < D; ++d) xi2 += xi[t][d] * xi[t][d];
-      mom_acc<D>(acc, A[t], xi[t], xi2, (double)v[t][0], P == 2 ? (double)v[t][P - 1] : 0.0);
+      gather_merge<D, T, P>(row, kk[t], mg[t], v[t]);
+      f(j, v[t]);
     }
   }
-  block_sum<N>(acc, red);
-  if (threadIdx.x == 0)
-    for (int m = 0; m < N; ++m) momp[(size_t)i * N + m] = acc[m];
+}
+
+template <int D, typename T>
+__device__ __forceinline__ void d_remap_gather(Geo g, Leaves Lo, Leaves Ln, const int* __restrict__ kind,
+                                               const int* __restrict__ src, const T* __restrict__ vin,
+                                               T* __restrict__ vout, int bx) {
+  constexpr int P = Cfg<D>::P;
+  const int i = bx;
+  gather_leaves<D, T>(g, Lo, Ln, kind, src, vin, i, [&](int j, const T (&v)[P]) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) vout[(p * (size_t)g.nc + i) * Ln.ld + j] = v[p];
+  });
 }
 
 template <int D, typename T>
 __global__ __launch_bounds__(BLOCK) void k_remap_gather(Geo g, Leaves Lo, Leaves Ln, const int* __restrict__ kind,
-                             const int* __restrict__ src, const T* __restrict__ vin, T* __restrict__ vout,
-                             double* __restrict__ momp) {
-  d_remap_gather<D, T>(g, Lo, Ln, kind, src, vin, vout, momp, blockIdx.x);
+                             const int* __restrict__ src, const T* __restrict__ vin, T* __restrict__ vout) {
+  d_remap_gather<D, T>(g, Lo, Ln, kind, src, vin, vout, blockIdx.x);
 }
 
-// Conservation correction of Sec. 3.3: f = f' + g_eq(W) - g_eq(W'), then
-// (mode 2) the closure that restores M[f] = W.  In place on the new rows.
-// With mom non-null, also the moments and heat flux of the corrected rows
-// (those of d_cell_moments: same leaf order per thread, same sums).
+// Gather with the conservation correction of Sec. 3.3: f = f' + g_eq(W) -
+// g_eq(W') with W' the moments of the gathered values f', then (mode 2) the
+// closure that restores M[f] = W; also the moments and heat flux of the result
+// (those of d_cell_moments: same leaf order per thread, same sums).  The old
+// rows are gathered twice, for W' and for the result, instead of being stored
+// in between: bound by memory, and the second reading finds most of a row in
+// the caches (8192 cells x 4991 leaves FP64: 518 us, 729 as a gather and a
+// correction in place).
 template <int D, typename T>
-__device__ __forceinline__ void d_remap_correct(Geo g, Leaves L, VGrid vg, GasP gas, int mode,
-                                                const double* __restrict__ W, const double* __restrict__ momp,
-                                                T* __restrict__ vdf, int* __restrict__ bad, double* __restrict__ mom,
+__device__ __forceinline__ void d_remap_correct(Geo g, Leaves Lo, Leaves L, VGrid vg, GasP gas, int mode,
+                                                const int* __restrict__ kind, const int* __restrict__ src,
+                                                const double* __restrict__ W, const T* __restrict__ vin,
+                                                T* __restrict__ vout, int* __restrict__ bad, double* __restrict__ mom,
                                                 double* __restrict__ q, int bx) {
   constexpr int P = Cfg<D>::P, N = D + 2, NS = Cfg<D>::NS;
   extern __shared__ double lds[];
@@ -2669,14 +2676,31 @@ __device__ __forceinline__ void d_remap_correct(Geo g, Leaves L, VGrid vg, GasP 
   double* tabB = lds + D * vg.numax;
   __shared__ double red[4 * (2 * N + NS)];
   __shared__ double parA[NPAR], parB[NPAR];
-  __shared__ double lam[N];
+  __shared__ double lam[N], sw[N];
   __shared__ ClosureWork<D> cw;
   const int i = bx;
+  {
+    double acc[N];
+#pragma unroll
+    for (int m = 0; m < N; ++m) acc[m] = 0.0;
+    gather_leaves<D, T>(g, Lo, L, kind, src, vin, i, [&](int j, const T (&v)[P]) {
+#pragma clang fp contract(off)
+      double xi[D], A, xi2 = 0.0;
+      int u[D];
+      leaf_load<D>(L, j, xi, A, u);
+#pragma unroll
+      for (int d = 0; d < D; ++d) xi2 += xi[d] * xi[d];
+      mom_acc<D>(acc, A, xi, xi2, (double)v[0], P == 2 ? (double)v[P - 1] : 0.0);
+    });
+    const double x = block_sum_pick<N>(acc, red);
+    if (threadIdx.x < N) sw[threadIdx.x] = x;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     double rho, U[D], T_;
     if (!prim_from_W<D>(W + (size_t)i * N, gas, rho, U, T_)) atomicMin(bad, i);
     eq_record<D>(parA, rho, U, T_, nullptr, gas);
-    if (!prim_from_W<D>(momp + (size_t)i * N, gas, rho, U, T_)) atomicMin(bad, i);
+    if (!prim_from_W<D>(sw, gas, rho, U, T_)) atomicMin(bad, i);
     eq_record<D>(parB, rho, U, T_, nullptr, gas);
   }
   __syncthreads();
@@ -2704,7 +2728,7 @@ __device__ __forceinline__ void d_remap_correct(Geo g, Leaves L, VGrid vg, GasP 
       gram_to_J<D>(cw.S, parA, cw.J);
 #pragma unroll
       for (int m = 0; m < N; ++m)
-        cw.b[m] = W[(size_t)i * N + m] - (momp[(size_t)i * N + m] + acc[m] - acc[N + m]);
+        cw.b[m] = W[(size_t)i * N + m] - (sw[m] + acc[m] - acc[N + m]);
       if (!solve_small<N>(cw.J, cw.b, cw.x)) { atomicMin(bad, i); for (int m = 0; m < N; ++m) cw.x[m] = 0.0; }
       for (int m = 0; m < N; ++m) lam[m] = cw.x[m];
     }
@@ -2712,14 +2736,13 @@ __device__ __forceinline__ void d_remap_correct(Geo g, Leaves L, VGrid vg, GasP 
     lam[threadIdx.x] = 0.0;
   }
   __syncthreads();
-  const size_t cs = (size_t)g.nc * L.ld;
   double U[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) U[d] = W[(size_t)i * N + 1 + d] / W[(size_t)i * N];
   double macc[N + D];
 #pragma unroll
   for (int m = 0; m < N + D; ++m) macc[m] = 0.0;
-  for (int k = threadIdx.x; k < L.n; k += BLOCK) {
+  gather_leaves<D, T>(g, Lo, L, kind, src, vin, i, [&](int k, const T (&v)[P]) {
     double xi[D], A;
     int u[D];
     leaf_load<D>(L, k, xi, A, u);
@@ -2731,30 +2754,27 @@ __device__ __forceinline__ void d_remap_correct(Geo g, Leaves L, VGrid vg, GasP 
       poly += lam[1 + d] * c;
     }
     poly += lam[D + 1] * c2;
-    T* r = vdf + (size_t)i * L.ld + k;
-    const T G = (T)(ld_(r) + (ga - gb) + poly * ga);
+    T* r = vout + (size_t)i * L.ld + k;
+    const T G = (T)((double)v[0] + (ga - gb) + poly * ga);
     r[0] = G;
     T H = 0;
     if (P == 2) {
-      H = (T)(ld_(r + cs) + (parA[P_RT] * ga - parB[P_RT] * gb) + poly * parA[P_RT] * ga);
-      r[cs] = H;
+      H = (T)((double)v[P - 1] + (parA[P_RT] * ga - parB[P_RT] * gb) + poly * parA[P_RT] * ga);
+      r[(size_t)g.nc * L.ld] = H;
     }
-    if (mom) state_mom_acc<D>(macc, xi, A, U, (double)G, (double)H);
-  }
-  if (mom) {
-    block_sum<N + D>(macc, red);
-    if (threadIdx.x == 0) {
-      for (int m = 0; m < N; ++m) mom[(size_t)i * N + m] = macc[m];
-      for (int d = 0; d < D; ++d) q[(size_t)i * D + d] = macc[N + d];
-    }
-  }
+    state_mom_acc<D>(macc, xi, A, U, (double)G, (double)H);
+  });
+  const double x = block_sum_pick<N + D>(macc, red);
+  if (threadIdx.x < N) mom[(size_t)i * N + threadIdx.x] = x;
+  else if (threadIdx.x < N + D) q[(size_t)i * D + threadIdx.x - N] = x;
 }
 
 template <int D, typename T>
-__global__ __launch_bounds__(BLOCK) void k_remap_correct(Geo g, Leaves L, VGrid vg, GasP gas, int mode,
-                             const double* __restrict__ W, const double* __restrict__ momp, T* __restrict__ vdf,
-                             int* __restrict__ bad, double* __restrict__ mom, double* __restrict__ q) {
-  d_remap_correct<D, T>(g, L, vg, gas, mode, W, momp, vdf, bad, mom, q, blockIdx.x);
+__global__ __launch_bounds__(BLOCK) void k_remap_correct(Geo g, Leaves Lo, Leaves Ln, VGrid vg, GasP gas, int mode,
+                             const int* __restrict__ kind, const int* __restrict__ src, const double* __restrict__ W,
+                             const T* __restrict__ vin, T* __restrict__ vout, int* __restrict__ bad,
+                             double* __restrict__ mom, double* __restrict__ q) {
+  d_remap_correct<D, T>(g, Lo, Ln, vg, gas, mode, kind, src, W, vin, vout, bad, mom, q, blockIdx.x);
 }
 
 // -------------------------------------------------- residual, totals, fields
@@ -2998,7 +3018,6 @@ struct RemapArgs {
   const int* psrc;
   const T* vin;
   T* vout;
-  double* momp;
   const double* W;
   double* mom;
   double* q;
@@ -3017,7 +3036,7 @@ __global__ __launch_bounds__(BLOCK) void kb_remap_gather(const RemapArgs<T>* __r
   const int c = find_case(off, ncase, blockIdx.x);
   const RemapArgs<T>* a = args + c;
   d_remap_gather<D, T>(global_geo(a->g), global_leaves(a->Lo), global_leaves(a->Ln), gptr(a->pkind), gptr(a->psrc),
-                       gptr(a->vin), gptr(a->vout), gptr(a->momp), blockIdx.x - off[c]);
+                       gptr(a->vin), gptr(a->vout), blockIdx.x - off[c]);
 }
 
 template <int D, typename T>
@@ -3025,8 +3044,9 @@ __global__ __launch_bounds__(BLOCK) void kb_remap_correct(const RemapArgs<T>* __
                                                           const int* __restrict__ off, int ncase, int mode) {
   const int c = find_case(off, ncase, blockIdx.x);
   const RemapArgs<T>* a = args + c;
-  d_remap_correct<D, T>(global_geo(a->g), global_leaves(a->Ln), a->vg, a->gas, mode, gptr(a->W), gptr(a->momp),
-                        gptr(a->vout), gptr(a->bad), gptr(a->mom), gptr(a->q), blockIdx.x - off[c]);
+  d_remap_correct<D, T>(global_geo(a->g), global_leaves(a->Lo), global_leaves(a->Ln), a->vg, a->gas, mode,
+                        gptr(a->pkind), gptr(a->psrc), gptr(a->W), gptr(a->vin), gptr(a->vout), gptr(a->bad),
+                        gptr(a->mom), gptr(a->q), blockIdx.x - off[c]);
 }
 
 template <int D, typename T>
