@@ -663,27 +663,27 @@ struct StencilVals {
   T nv[Cfg<D>::MAXF][P];
 };
 
-template <int D, typename T, int P>
+template <int D, typename T, int P, int MS = Cfg<D>::MAXF>
 __device__ __forceinline__ void load_vals(const Stencil<D, T, P>& st, int k, StencilVals<D, T, P>& v) {
-  constexpr int MAXF = Cfg<D>::MAXF;
   const unsigned ko = (unsigned)k * (unsigned)sizeof(T);
 #pragma unroll
   for (int p = 0; p < P; ++p) v.phi[p] = at_(st.own[p], ko);
 #pragma unroll
-  for (int s = 0; s < MAXF; ++s)
+  for (int s = 0; s < MS; ++s)
 #pragma unroll
     for (int p = 0; p < P; ++p) v.nv[s][p] = at_(st.nb[s][p], ko);
 }
 
 // Least-squares gradient, its increments grad . (x_f - x_i) towards the face
 // midpoints (D2 of the limiter, d2s) and the Venkatakrishnan limiter L, per
-// VDF component, in T.  FULL: every one of the MAXF slots is a face with an
-// interior neighbour (known at compile time, so the slot tests vanish).
-template <int D, typename T, bool FULL, int P>
+// VDF component, in T.  NF > 0: the cell has NF faces, all with an interior
+// neighbour (known at compile time, so the slot tests vanish).
+template <int D, typename T, int NF, int P>
 __device__ __forceinline__ void lim_parts(const Stencil<D, T, P>& st, const StencilVals<D, T, P>& sv, T (&phi)[P],
                                           T (&lim)[P], T (&grad)[P][D], T (&d2s)[P][Cfg<D>::MAXF]) {
-  constexpr int MAXF = Cfg<D>::MAXF;
-  const int ns = FULL ? MAXF : st.ns;
+  constexpr bool FULL = NF > 0;
+  constexpr int MS = FULL ? NF : Cfg<D>::MAXF;
+  const int ns = FULL ? NF : st.ns;
   // the neighbour extrema are kept as differences from phi (rounding is
   // monotone, so max_j(v_j - phi) equals max_j(v_j) - phi exactly, and the
   // differences, being arithmetic results, need no NaN canonicalisation)
@@ -698,7 +698,7 @@ __device__ __forceinline__ void lim_parts(const Stencil<D, T, P>& st, const Sten
   }
   const auto& nv = sv.nv;
 #pragma unroll
-  for (int s = 0; s < MAXF; ++s) {
+  for (int s = 0; s < MS; ++s) {
     if (FULL || (st.nbmask & (1u << s))) {
 #pragma unroll
       for (int p = 0; p < P; ++p) {
@@ -733,7 +733,7 @@ __device__ __forceinline__ void lim_parts(const Stencil<D, T, P>& st, const Sten
     const T up0 = dmax[p], dn0 = -dmin[p];
     T ap = 0, an = 0;                    // largest D2 and largest -D2
 #pragma unroll
-    for (int s = 0; s < MAXF; ++s) {
+    for (int s = 0; s < MS; ++s) {
       T d2 = 0;
 #pragma unroll
       for (int d = 0; d < D; ++d) d2 += grad[p][d] * st.DD(s, d);
@@ -774,7 +774,7 @@ __device__ __forceinline__ void lim_parts(const Stencil<D, T, P>& st, const Sten
         Nm = 1;
         Dm = 0;                                        // running minimum, starts at +inf
 #pragma unroll
-        for (int s = 0; s < MAXF; ++s) {
+        for (int s = 0; s < MS; ++s) {
           if (FULL || s < ns) {
             psi(fabs(d2s[p][s]) * inv, d2s[p][s] > (T)0 ? up : dn, Nn, Dd);
             if ((FULL && s == 0) || Nn * Dm < Nm * Dd) {
@@ -899,13 +899,15 @@ struct PassAShared {
   A a[NT];
 };
 
-template <int D, typename T, bool FULL, int P>
+template <int D, typename T, int NF, int P>
 __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& g, const Leaves& L,
                                            const T* __restrict__ vdf, const double* __restrict__ bcpair, double h,
                                            T* __restrict__ fv, double* __restrict__ fmom, int nchs, int i, int k0,
                                            int k1, int by, double Rgas) {
   using S = PassAShared<D, T, P>;
   constexpr int MAXF = Cfg<D>::MAXF, NM = FaceMom<D, P>::NM, NT = passA_threads<D>(), PS = S::PS;
+  constexpr bool FULL = NF > 0;
+  constexpr int MS = FULL ? NF : MAXF;
   using A = typename MomAcc<T>::type;
   T* const s_cf = sh.cf;
   T* const s_dd = sh.dd;
@@ -949,9 +951,9 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& 
   } else {
     load_stencil<D, T, P>(g, vdf, cs, L.ld, i, st);
   }
-  const int ns = FULL ? MAXF : st.ns;
+  const int ns = FULL ? NF : st.ns;
 #pragma unroll
-  for (int s = 0; s < MAXF; ++s) {
+  for (int s = 0; s < MS; ++s) {
     const int f = (FULL || s < ns) ? g.s_face[i * MAXF + s] : 0;
     if constexpr (lds_nrm) {
       if (s_sig[s] > 0.0) lside |= 1u << s;
@@ -976,7 +978,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& 
   StencilVals<D, T, P> sv;
   double xi_n[D], aw_n = 0.0;
   auto load_leaf = [&](int k) {
-    load_vals<D, T, P>(st, k, sv);
+    load_vals<D, T, P, MS>(st, k, sv);
 #pragma unroll
     for (int d = 0; d < D; ++d) xi_n[d] = at_(L.xi + (size_t)d * L.cap, (unsigned)k * 8u);
     aw_n = at_(L.w, (unsigned)k * 8u);
@@ -992,7 +994,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& 
       T phi[P], lim[P], grad[P][D], d2s[P][MAXF];
       // re-read the LDS constants below instead of keeping them live
       if constexpr (Stencil<D, T, P>::kLds) __asm__ volatile("" ::: "memory");
-      lim_parts<D, T, FULL, P>(st, sv, phi, lim, grad, d2s);
+      lim_parts<D, T, NF, P>(st, sv, phi, lim, grad, d2s);
       // phibar = phi + L grad . (x_f - x_i) - h L grad . xi: the first product
       // is the limiter's D2 of the face, the second is shared by the faces
       T base[P];
@@ -1004,7 +1006,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& 
         base[p] = phi[p] - th * lim[p] * gx;
       }
 #pragma unroll
-      for (int s = 0; s < MAXF; ++s) {
+      for (int s = 0; s < MS; ++s) {
         A u[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) u[p] = 0;
@@ -1051,7 +1053,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& 
       if (k + NT < k1) load_leaf(k + NT);
     } else {
 #pragma unroll
-      for (int s = 0; s < MAXF; ++s)
+      for (int s = 0; s < MS; ++s)
 #pragma unroll
         for (int p = 0; p < PS; ++p) s_u[s][p][threadIdx.x] = 0;
       s_a[threadIdx.x] = 0;
@@ -1060,7 +1062,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& 
     }
     __syncthreads();
     // the face of this wave: moments of its upwind values over the block
-    if (FULL || wave < ns) {
+    if (NF == MAXF || wave < ns) {
 #pragma unroll
       for (int q = 0; q < NT / 64; ++q) {
         const int j = q * 64 + lane;
@@ -1076,7 +1078,7 @@ __device__ __forceinline__ void passA_cell(PassAShared<D, T, P>& sh, const Geo& 
     __syncthreads();
   }
   // one partial per (face, side, chunk): the wave's lanes added in FP64
-  if (FULL || wave < ns) {
+  if (NF == MAXF || wave < ns) {
     double tot[NM];
 #pragma unroll
     for (int t = 0; t < NM; ++t) tot[t] = (double)acc[t];
@@ -1098,17 +1100,31 @@ __device__ __forceinline__ void d_passA(Geo g, Leaves L, const T* __restrict__ v
   const int i = xcd_cell(g, bx);
   if (i < 0) return;
   const int k0 = by * chunk, k1 = min(L.n, k0 + chunk);
-  // a cell whose every slot is a face with an interior neighbour takes the
-  // specialised loop (no slot tests); others (boundary cells, cells with
-  // fewer faces) the general one
-  bool full = g.nslot[i] == MAXF;
+  // a cell whose faces all have an interior neighbour takes a specialised loop
+  // (no slot tests): with every slot a face, and in 2-D FP32 with three
+  // (triangles: 11 880 cells x 1252 leaves 160 -> 140 us; in FP64 the third
+  // loop's code costs quadrilaterals with few leaves 36 -> 38 us at 4096 x 256,
+  // and with three components a wave per SIMD, 1.95 -> 2.35 ms); others
+  // (boundary cells) the general one
+  const int ns = g.nslot[i];
+  bool inner = true;
 #pragma unroll
-  for (int s = 0; s < MAXF; ++s) full = full && g.s_nbr[i * MAXF + s] >= 0;
+  for (int s = 0; s < MAXF; ++s) {
+    const int j = g.s_nbr[i * MAXF + s];      // loaded beside ns, not after it
+    inner = inner & ((s >= ns) | (j >= 0));
+  }
   __shared__ PassAShared<D, T, P> sh;
-  if (full)
-    passA_cell<D, T, true, P>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by, Rgas);
-  else
-    passA_cell<D, T, false, P>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by, Rgas);
+  if (inner && ns == MAXF) {
+    passA_cell<D, T, MAXF, P>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by, Rgas);
+    return;
+  }
+  if constexpr (D == 2 && sizeof(T) == 4) {
+    if (inner && ns == 3) {
+      passA_cell<D, T, 3, P>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by, Rgas);
+      return;
+    }
+  }
+  passA_cell<D, T, 0, P>(sh, g, L, vdf, bcpair, h, fv, fmom, nchs, i, k0, k1, by, Rgas);
 }
 
 // Waves per SIMD pass A asks for: the face-moment accumulators (MAXF x NM

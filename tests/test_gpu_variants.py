@@ -181,3 +181,22 @@ def test_moment_groups(avs, shape, prec):
     ref = np.einsum('ik,ikd->id', e, c)
     assert np.max(np.abs(q - ref)) < 1e-12 * np.max(np.einsum('ik,ikd->id', e, np.abs(c)))
     cs.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_triangles_inner_and_boundary(avs, prec):
+    """Cells with three interior faces and with one or two walls: two explicit
+    steps (FP64 1e-12 per step; FP32 1e-5 of the field, as the other step
+    tests)."""
+    mesh = MM.tri_box(5, 4, 71, sides=dict(left=0, right=0, bottom=0, top=0), bcs=[(MM.WALL, (1.0, 0.1, 0.0, 1.1))])
+    vs = dict(dim=2, lo=(-6, -6), hi=(6, 6), base=(8, 8), max_level=2)
+    prim = F.perturbed_uniform(mesh['ncells'], 2, 72, amp=0.1, uamp=0.3)
+    cs, o = make_pair(avs, mesh, vs, GAS, 0.5 * F._cfl_dt(mesh, 0.5, (6.0, 6.0)), prim, tree=random_tree(vs, 73, 2),
+                      noise=0.02, seed=74, precision=prec)
+    cs.step(2)
+    o.step(2)
+    v, W = cs.get_state()
+    if prec:
+        assert fieldrel(W, o.W) < 1e-5 and fieldrel(v, o.phi) < 1e-5
+    else:
+        assert rel(v, o.phi) < 2e-12 and rel(W, o.W) < 2e-12
