@@ -531,7 +531,7 @@ avs_status launch_interfaces(avs_ctx* ctx) {
                                                             ctx->fmom, ctx->nchs, chunk);
     CKL();
   }
-  if (ctx->nf > 0 && lane_form<D, T>(nu)) {
+  if (face_lane_form<D, T>(ctx->nf, nu)) {
     ProfScope ps(ctx, K_FACE_EQFLUX);
     const int shares = face_shares<D, T>(ctx), groups = (ctx->nf + 63) / 64;
     double* part = (double*)ctx->vdf[ctx->cur ^ 1];
@@ -946,9 +946,10 @@ avs_status batch_upload(avs_batch* b) {
     const int fb = c->D == 2 ? face_batch<2>() : face_batch<3>();
     const bool lanes = c->D == 2 ? lane_form<2, T>(c->vg.numax) : lane_form<3, T>(c->vg.numax);
     const bool wavec = c->D == 2 ? passC_wave_form<2, T>(nl, c->vg.numax) : passC_wave_form<3, T>(nl, c->vg.numax);
+    const bool flanes = c->D == 2 ? face_lane_form<2, T>(c->nf, c->vg.numax) : face_lane_form<3, T>(c->nf, c->vg.numax);
     const int fg = (c->nf + 63) / 64;
-    const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), lanes ? 0 : (c->nf + fb - 1) / fb,
-                           lanes ? fg * args[i].fshares : 0, lanes && args[i].fshares > 1 ? fg : 0,
+    const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), flanes ? 0 : (c->nf + fb - 1) / fb,
+                           flanes ? fg * args[i].fshares : 0, flanes && args[i].fshares > 1 ? fg : 0,
                            lanes ? 0 : (c->nc + BLOCK - 1) / BLOCK, lanes ? 0 : c->nc, lanes ? (c->nc + 63) / 64 * args[i].shares : 0,
                            lanes && args[i].shares > 1 ? (c->nc + 63) / 64 : 0, wavec ? 0 : gx, wavec ? gx : 0};
     for (int k = 0; k < BK_N; ++k) off[k * (n + 1) + i + 1] = off[k * (n + 1) + i] + cnt[k];

@@ -1535,6 +1535,19 @@ inline int lane_shares(int count, int nleaf, int numax, int nacc, int64_t most) 
   return best;
 }
 
+// The interface stage takes the lane form from FACE_LANES faces on: with fewer
+// the groups (or their leaf shares, each of which builds the tables again)
+// leave most of the chip idle, and a workgroup per four faces is done sooner.
+// Four faces / lanes, us: 312 faces x 300 leaves FP64 11.9 / 14.3; 1590 x 1500
+// FP32 14.8 / 33.5 (256 table entries); 2100 x 700 3-D 15.0 / 21.7; 5200 x 300
+// 22.1 / 15.3; 10 400 x 1500 39.7 / 35.2; 12 300 x 1500 3-D 57.5 / 37.1.  Alone
+// the forms cross between 2600 (300 leaves) and some 10 000 faces (1500); many
+// cases in one launch fill the chip with groups of fewer, and take the same
+// form as the case alone.
+constexpr int FACE_LANES = 1536;
+template <int D, typename R>
+inline bool face_lane_form(int nf, int numax) { return nf >= FACE_LANES && lane_form<D, R>(numax); }
+
 // Tables of the 64 lanes' Maxwellians from their records spar[NPAR][64]:
 // tab[d][u][lane] = exp(-(x_u - U_d)^2 / 2RT).
 template <int D, typename R>

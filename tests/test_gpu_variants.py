@@ -66,6 +66,10 @@ def test_repeated_colour_turns(avs, nx, ny, diatomic):
     (3, 3, 40, 0, 0),     # and first with four
     (3, 3, 38, 0, 1),
     (3, 3, 40, 0, 1),
+    (27, 27, 5, 1, 0),    # 1485 faces: a workgroup per four faces
+    (27, 28, 5, 1, 0),    # 1539 faces: a lane per face, three in the last group
+    (45, 23, 8, 0, 1),
+    (33, 33, 72, 0, 0),   # faces in leaf shares with the largest tables
 ])
 def test_lane_groups(avs, nx, ny, base, levels, prec):
     """A lane per cell and per face: group remainders, leaf shares, both
