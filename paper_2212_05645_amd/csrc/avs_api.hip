@@ -458,20 +458,27 @@ avs_status launch_bc_tables(avs_ctx* ctx) {
   return AVS_OK;
 }
 
-// Leaf shares of a context's 64-lane target.  The partial sums go into the
-// next state's buffer, which pass C fills after them.
+// Leaf shares of a context's 64-lane target, 0 where a workgroup per cell is
+// taken instead.  The partial sums go into the next state's buffer, which pass
+// C fills after them.
 template <int D, typename T>
 int target_shares(const avs_ctx* ctx) {
   constexpr int nacc = D + 2 + Cfg<D>::NS;
+  const int n = ctx->nleaf[ctx->lcur], nu = ctx->vg.numax;
+  if (!lane_form<D, T>(nu)) return 0;
   const int64_t most = (int64_t)(ctx->vdf_buf_bytes / (round_up(ctx->nc, 64) * nacc * sizeof(double)));
-  return lane_shares<D, T>(ctx->nc, ctx->nleaf[ctx->lcur], ctx->vg.numax, nacc, most);
+  const int s = lane_shares<D, T>(ctx->nc, n, nu, nacc, most);
+  return lane_work_pays(s, D, n, nu) ? s : 0;
 }
 
 // The same for the interface stage.
 template <int D, typename T>
 int face_shares(const avs_ctx* ctx) {
-  const int64_t most = (int64_t)(ctx->vdf_buf_bytes / (round_up(std::max(ctx->nf, 1), 64) * (D + 2) * sizeof(double)));
-  return lane_shares<D, T>(ctx->nf, ctx->nleaf[ctx->lcur], ctx->vg.numax, D + 2, most);
+  const int n = ctx->nleaf[ctx->lcur], nu = ctx->vg.numax;
+  if (ctx->nf < FACE_LANES || !lane_form<D, T>(nu)) return 0;
+  const int64_t most = (int64_t)(ctx->vdf_buf_bytes / (round_up(ctx->nf, 64) * (D + 2) * sizeof(double)));
+  const int s = lane_shares<D, T>(ctx->nf, n, nu, D + 2, most);
+  return lane_work_pays(s, D, n, nu) ? s : 0;
 }
 
 // W^{n+1} from the fluxes F, the target records and the closure's lambda.
@@ -479,9 +486,8 @@ template <int D, typename T>
 avs_status launch_target(avs_ctx* ctx) {
   const Leaves L = ctx->leaves(ctx->lcur);
   const int nu = ctx->vg.numax;
-  if (lane_form<D, T>(nu)) {
+  if (const int shares = target_shares<D, T>(ctx)) {
     ProfScope ps(ctx, K_TARGET);
-    const int shares = target_shares<D, T>(ctx);
     double* part = (double*)ctx->vdf[ctx->cur ^ 1];
     k_target_lanes<D, T><<<dim3((ctx->nc + 63) / 64, shares), LANE_BLOCK, lane_lds<D, T>(nu, D + 2 + Cfg<D>::NS),
                            ctx->stream>>>(ctx->geo, L, ctx->vg, ctx->gas, ctx->dt, ctx->F, ctx->W, ctx->Wn, ctx->q,
@@ -531,9 +537,9 @@ avs_status launch_interfaces(avs_ctx* ctx) {
                                                             ctx->fmom, ctx->nchs, chunk);
     CKL();
   }
-  if (face_lane_form<D, T>(ctx->nf, nu)) {
+  if (const int shares = face_shares<D, T>(ctx)) {
     ProfScope ps(ctx, K_FACE_EQFLUX);
-    const int shares = face_shares<D, T>(ctx), groups = (ctx->nf + 63) / 64;
+    const int groups = (ctx->nf + 63) / 64;
     double* part = (double*)ctx->vdf[ctx->cur ^ 1];
     k_face_lanes<D, T><<<dim3(groups, shares), LANE_BLOCK, lane_face_lds<D, T>(nu), ctx->stream>>>(
         ctx->geo, L, ctx->vg, ctx->gas, ctx->h, ctx->bden, ctx->bfin, ctx->fmom, ctx->nchs, nch, ctx->fpar, ctx->F, part,
@@ -944,9 +950,8 @@ avs_status batch_upload(avs_batch* b) {
     const int nl = c->nleaf[c->lcur];
     const int gx = (int)round_up(c->nc, 8);
     const int fb = c->D == 2 ? face_batch<2>() : face_batch<3>();
-    const bool lanes = c->D == 2 ? lane_form<2, T>(c->vg.numax) : lane_form<3, T>(c->vg.numax);
+    const bool lanes = args[i].shares > 0, flanes = args[i].fshares > 0;
     const bool wavec = c->D == 2 ? passC_wave_form<2, T>(nl, c->vg.numax) : passC_wave_form<3, T>(nl, c->vg.numax);
-    const bool flanes = c->D == 2 ? face_lane_form<2, T>(c->nf, c->vg.numax) : face_lane_form<3, T>(c->nf, c->vg.numax);
     const int fg = (c->nf + 63) / 64;
     const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), flanes ? 0 : (c->nf + fb - 1) / fb,
                            flanes ? fg * args[i].fshares : 0, flanes && args[i].fshares > 1 ? fg : 0,

@@ -1535,18 +1535,24 @@ inline int lane_shares(int count, int nleaf, int numax, int nacc, int64_t most) 
   return best;
 }
 
-// The interface stage takes the lane form from FACE_LANES faces on: with fewer
-// the groups (or their leaf shares, each of which builds the tables again)
-// leave most of the chip idle, and a workgroup per four faces is done sooner.
-// Four faces / lanes, us: 312 faces x 300 leaves FP64 11.9 / 14.3; 1590 x 1500
-// FP32 14.8 / 33.5 (256 table entries); 2100 x 700 3-D 15.0 / 21.7; 5200 x 300
-// 22.1 / 15.3; 10 400 x 1500 39.7 / 35.2; 12 300 x 1500 3-D 57.5 / 37.1.  Alone
-// the forms cross between 2600 (300 leaves) and some 10 000 faces (1500); many
-// cases in one launch fill the chip with groups of fewer, and take the same
-// form as the case alone.
+// The lane form pays while the shares' tables and reductions, each share's
+// anew, stay within twice the leaves' own work; beyond (few groups, fine
+// velocity grids) a workgroup per cell or per four faces does less, alone or
+// among other cases in one launch, which takes the form of the case alone.
+// Five batched cases of 646 to 1334 cells x 2212 leaves FP32 (16 shares, 256
+// table entries): lanes 94 + 79 us, workgroups 74 + 56; 2574 cells x 4404
+// leaves FP64 3-D (6 shares, 64 entries): 43 against 75.
+inline bool lane_work_pays(int shares, int D, int nleaf, int numax) {
+  return (int64_t)shares * (D * numax + 640) <= 2 * ((int64_t)nleaf + 640);
+}
+
+// The interface stage takes it from FACE_LANES faces on: with fewer most of the
+// chip idles, and a workgroup per four faces is done sooner.  Four faces /
+// lanes, us: 312 faces x 300 leaves FP64 11.9 / 14.3; 2100 x 700 3-D 15.0 /
+// 21.7; 5200 x 300 22.1 / 15.3; 10 400 x 1500 39.7 / 35.2; 12 300 x 1500 3-D
+// 57.5 / 37.1.  Alone the forms cross between 2600 faces (300 leaves) and some
+// 10 000 (1500); many cases in one launch fill the chip with groups of fewer.
 constexpr int FACE_LANES = 1536;
-template <int D, typename R>
-inline bool face_lane_form(int nf, int numax) { return nf >= FACE_LANES && lane_form<D, R>(numax); }
 
 // Tables of the 64 lanes' Maxwellians from their records spar[NPAR][64]:
 // tab[d][u][lane] = exp(-(x_u - U_d)^2 / 2RT).

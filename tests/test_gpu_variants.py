@@ -57,7 +57,7 @@ def test_repeated_colour_turns(avs, nx, ny, diatomic):
     (9, 7, 8, 2, 0),      # one lane short of a group of 64 cells
     (8, 8, 8, 2, 0),      # exactly one group
     (13, 5, 8, 2, 0),     # one cell in the second group
-    (3, 2, 72, 0, 0),     # largest tables of the 64-lane form, leaves in several shares
+    (3, 2, 72, 0, 0),     # largest tables of the 64-lane form: its work rule, a workgroup per cell
     (3, 2, 73, 0, 0),     # just beyond: a workgroup per cell
     (5, 4, 16, 3, 1),     # FP32
     (3, 3, 5, 0, 0),      # fewer leaves than lanes
@@ -69,7 +69,7 @@ def test_repeated_colour_turns(avs, nx, ny, diatomic):
     (27, 27, 5, 1, 0),    # 1485 faces: a workgroup per four faces
     (27, 28, 5, 1, 0),    # 1539 faces: a lane per face, three in the last group
     (45, 23, 8, 0, 1),
-    (33, 33, 72, 0, 0),   # faces in leaf shares with the largest tables
+    (33, 33, 40, 0, 0),   # 2211 faces, tables of 80 entries
 ])
 def test_lane_groups(avs, nx, ny, base, levels, prec):
     """A lane per cell and per face: group remainders, leaf shares, both
@@ -98,6 +98,22 @@ def test_lane_groups_3d(avs, prec):
     prim = F.perturbed_uniform(mesh['ncells'], 3, 31, amp=0.1, uamp=0.3)
     cs, o = make_pair(avs, mesh, vs, GAS, F._cfl_dt(mesh, 0.5, (5.0,) * 3), prim, tree=random_tree(vs, 32, 2),
                       noise=0.02, seed=33, precision=prec)
+    cs.step(1)
+    o.step(1)
+    v, W = cs.get_state()
+    tol = 1e-5 if prec else 1e-12
+    assert fieldrel(v, o.phi) < tol and fieldrel(W, o.W) < tol
+
+
+@pytest.mark.parametrize("shape,prec", [((5, 3, 5), 0), ((8, 8, 9), 0), ((8, 8, 9), 1)])
+def test_leaf_shares(avs, shape, prec):
+    """Few groups and many leaves on small tables: the leaves of the target
+    (75 cells) and of both the target and the interface stage (1728 faces)
+    split over workgroups whose sums a closing launch adds."""
+    mesh = MM.box3d(*shape)
+    vs = dict(dim=3, lo=(-5.0,) * 3, hi=(5.0,) * 3, base=(18, 18, 18), max_level=0)
+    prim = F.perturbed_uniform(mesh['ncells'], 3, 81, amp=0.1, uamp=0.3)
+    cs, o = make_pair(avs, mesh, vs, GAS, F._cfl_dt(mesh, 0.5, (5.0,) * 3), prim, noise=0.02, seed=83, precision=prec)
     cs.step(1)
     o.step(1)
     v, W = cs.get_state()
