@@ -84,6 +84,7 @@ struct avs_ctx {
   int lcur = 0;
   int nleaf[2] = {0, 0};
   int ld[2] = {0, 0};
+  StepForms forms;        // of the current leaf count (step_forms)
 
   double *W, *Wn, *q, *mom, *tpar, *lam, *fpar, *F, *bden, *bfin, *bcpair, *momp, *res, *tot;
   double* fmom;           // face-moment partials of pass A: [nf+1][2 sides][nchs chunks][NM]
@@ -458,27 +459,21 @@ avs_status launch_bc_tables(avs_ctx* ctx) {
   return AVS_OK;
 }
 
-// Leaf shares of a context's 64-lane target, 0 where a workgroup per cell is
-// taken instead.  The partial sums go into the next state's buffer, which pass
-// C fills after them.
+// The forms of a context's step, chosen anew when its leaf count changes.  The
+// shares' partial sums go into the next state's buffer, which pass C fills
+// after them.
 template <int D, typename T>
-int target_shares(const avs_ctx* ctx) {
-  constexpr int nacc = D + 2 + Cfg<D>::NS;
+const StepForms& step_forms(avs_ctx* ctx) {
+  StepForms& f = ctx->forms;
   const int n = ctx->nleaf[ctx->lcur], nu = ctx->vg.numax;
-  if (!lane_form<D, T>(nu)) return 0;
-  const int64_t most = (int64_t)(ctx->vdf_buf_bytes / (round_up(ctx->nc, 64) * nacc * sizeof(double)));
-  const int s = lane_shares<D, T>(ctx->nc, n, nu, nacc, most);
-  return lane_work_pays(s, D, n, nu) ? s : 0;
-}
-
-// The same for the interface stage.
-template <int D, typename T>
-int face_shares(const avs_ctx* ctx) {
-  const int n = ctx->nleaf[ctx->lcur], nu = ctx->vg.numax;
-  if (ctx->nf < FACE_LANES || !lane_form<D, T>(nu)) return 0;
-  const int64_t most = (int64_t)(ctx->vdf_buf_bytes / (round_up(ctx->nf, 64) * (D + 2) * sizeof(double)));
-  const int s = lane_shares<D, T>(ctx->nf, n, nu, D + 2, most);
-  return lane_work_pays(s, D, n, nu) ? s : 0;
+  if (f.nleaf == n) return f;
+  const auto room = [&](int count, int nacc) {
+    return (int64_t)(ctx->vdf_buf_bytes / (round_up(count, 64) * nacc * sizeof(double)));
+  };
+  f.nleaf = n;
+  f.target = lane_shares<D, T>(TARGET_COST, ctx->nc, n, nu, room(ctx->nc, D + 2 + Cfg<D>::NS));
+  f.face = lane_shares<D, T>(FACE_COST, ctx->nf, n, nu, room(ctx->nf, D + 2));
+  return f;
 }
 
 // W^{n+1} from the fluxes F, the target records and the closure's lambda.
@@ -486,7 +481,7 @@ template <int D, typename T>
 avs_status launch_target(avs_ctx* ctx) {
   const Leaves L = ctx->leaves(ctx->lcur);
   const int nu = ctx->vg.numax;
-  if (const int shares = target_shares<D, T>(ctx)) {
+  if (const int shares = step_forms<D, T>(ctx).target) {
     ProfScope ps(ctx, K_TARGET);
     double* part = (double*)ctx->vdf[ctx->cur ^ 1];
     k_target_lanes<D, T><<<dim3((ctx->nc + 63) / 64, shares), LANE_BLOCK, lane_lds<D, T>(nu, D + 2 + Cfg<D>::NS),
@@ -537,7 +532,7 @@ avs_status launch_interfaces(avs_ctx* ctx) {
                                                             ctx->fmom, ctx->nchs, chunk);
     CKL();
   }
-  if (const int shares = face_shares<D, T>(ctx)) {
+  if (const int shares = step_forms<D, T>(ctx).face) {
     ProfScope ps(ctx, K_FACE_EQFLUX);
     const int groups = (ctx->nf + 63) / 64;
     double* part = (double*)ctx->vdf[ctx->cur ^ 1];
@@ -928,8 +923,9 @@ CaseArgs<T> case_args(avs_ctx* c, int flip, int chunk) {
   a.nchs = c->nchs;
   a.chunk = chunk;
   a.gx = (int)round_up(c->nc, 8);
-  a.fshares = c->D == 2 ? face_shares<2, T>(c) : face_shares<3, T>(c);
-  a.shares = c->D == 2 ? target_shares<2, T>(c) : target_shares<3, T>(c);
+  const StepForms& f = c->D == 2 ? step_forms<2, T>(c) : step_forms<3, T>(c);
+  a.fshares = f.face;
+  a.shares = f.target;
   return a;
 }
 

@@ -1,0 +1,113 @@
+// Which form the target and the interface stage of a step take: a lane per
+// cell or face (k_target_lanes, k_face_lanes), its leaves in one or more
+// shares, or a workgroup per cell (k_target) or per four faces (k_face_eq).
+// Functions of the sizes alone, so that a case takes the same form, and the
+// same order of summation, alone and in a batch.  Plain C++.
+#pragma once
+
+#include <cstddef>
+#include <cstdint>
+
+namespace avs {
+
+constexpr int LANE_WAVES = 16;              // waves of a 64-lane workgroup
+constexpr size_t LANE_LDS = 144 * 1024;     // its tables' room, of 160 KiB per CU
+constexpr int LANE_SHARES = 16;             // most leaf shares
+
+template <int D, typename R>
+constexpr size_t lane_tab_bytes(int numax) { return (size_t)D * numax * 64 * sizeof(R); }
+
+// True when the 64-lane form's tables fit (numax up to 144 in FP64 2-D, 288
+// in FP32 2-D, 192 in FP32 3-D).
+template <int D, typename R>
+inline bool lane_form(int numax) { return lane_tab_bytes<D, R>(numax) <= LANE_LDS; }
+
+// Dynamic LDS: the tables, later the waves' partial sums (nacc doubles per
+// lane from half of the waves).
+template <int D, typename R>
+inline size_t lane_lds(int numax, int nacc) {
+  const size_t t = lane_tab_bytes<D, R>(numax), r = (size_t)(LANE_WAVES / 2) * nacc * 64 * sizeof(double);
+  return t > r ? t : r;
+}
+
+// What a stage costs, us on a chip of 256 CUs; the costs of a leaf and of a
+// table entry are per 1000 of them.
+struct StageCost {
+  int per;                          // cells or faces of a workgroup of the workgroup form
+  double base, round, leaf, lat;    // workgroup form: launches and serial part, a workgroup in its CU's
+                                    // turn, a leaf of one of its cells or faces, a leaf of the longest chain
+  double lround, lleaf;             // 64-lane form: a workgroup in its CU's turn, a leaf
+};
+constexpr StageCost TARGET_COST = {1, 10.7, 0.94, 0.34, 0.25, 4.5, 21.5};
+constexpr StageCost FACE_COST = {4, 3.9, 1.9, 0.17, 0.9, 3.5, 13.4};
+constexpr double GROUP_TAB = 2.1, LANE_TAB = 17.0;       // a workgroup's exponential tables
+constexpr double CLOSE_BASE = 2.4, CLOSE_SHARE = 0.4;    // the launch that adds several shares
+constexpr double SHARED_WORK = 3.0;                      // weight of the work beside the time alone
+constexpr double LANE_MARGIN = 3.0;                      // what the lanes have to gain
+
+// Cost of a stage of `count` cells or faces in the 64-lane form with `shares`
+// leaf shares, in the workgroup form for 0: its time alone, whole turns of the
+// CUs, and its work, the same turns without rounding up.
+inline double stage_cost(const StageCost& c, int D, int count, int nleaf, int numax, int shares) {
+  if (shares == 0) {
+    const int64_t n = ((int64_t)count + c.per - 1) / c.per;
+    const double one = c.round + c.leaf * c.per * nleaf / 1000;
+    return c.base + (double)((n + 255) / 256) * one + (c.lat * nleaf + GROUP_TAB * D * numax) / 1000 +
+           SHARED_WORK * one * (double)n / 256;
+  }
+  const int64_t n = ((int64_t)count + 63) / 64 * shares;
+  const double one = c.lround + (c.lleaf * nleaf / shares + LANE_TAB * D * numax) / 1000;
+  return LANE_MARGIN + ((double)((n + 255) / 256) + SHARED_WORK * (double)n / 256) * one +
+         (shares > 1 ? CLOSE_BASE + CLOSE_SHARE * shares : 0.0);
+}
+
+// Leaf shares of the 64-lane form for `count` cells or faces, 0 where the
+// workgroup form is taken: the one of least cost.  The lanes do less work per
+// leaf, but a launch has only ceil(count / 64) groups of them: with few groups
+// most CUs idle and each wave walks a sixteenth of the leaves, so the leaves are
+// split over `shares` workgroups per group, each with tables of its own, whose
+// sums another launch adds.
+// The constants are a least-squares fit to a sweep of whole steps, 508 sizes x
+// 9 forms of either stage (32 to 36 864 cells, 76 to 19 972 leaves, 20 to 288
+// table entries, 2-D and 3-D, FP64 and FP32).  Whole steps, us, workgroup form /
+// lanes with 1, 2, 4 and 8 shares:
+//   target     600 cells x 1498 leaves, 256 entries, FP32     66 /  95  83  76  73
+//             3584 x 1498, 256, FP32                         161 / 174 162 157 170
+//             7000 x 1498, 256, FP32                         286 / 283 272 286 309
+//            16384 x 256, 32, FP64                           362 / 295 303 315 337
+//   interface 1836 faces x 1498, 256, FP32                    73 /  93  87  83  82
+//             7232 x 1498, 256, FP32                         161 / 166 162 175 201
+//            14100 x 1498, 256, FP32                         285 / 273 287 313 349
+//            33024 x 256, 32, FP64                           361 / 301 314 330 369
+// A case takes the same form in a batch, where other cases use what it leaves
+// idle and only its work counts, which is mostly the lanes' smaller one: so the
+// work counts beside the time.  The weight is a compromise.  Steps of 147 single
+// cases and of 19 FP32 batches (400 to 7000 cells, 300 to 16 000 leaves, sizes
+// drawn at random) against a rule for full chips, the lanes wherever their
+// tables fit and the shares' tables stay within twice the leaves' work: with
+// weight 0 the single cases are 4 % faster and the batches 12 % slower on
+// average, with 2 3.5 and 8 %, with 3 2.4 and 6 %, with 6 1 and 3 %, with 9 no
+// faster and 2 % faster.  With 3 none of the single cases is more than 5 %
+// slower than by that rule, and those it had made up to half as slow again (75
+// to 900 cells x 1500 leaves) are back at the workgroup form.
+// At most `most` shares (the partial sums' room; one share needs none).
+template <int D, typename R>
+inline int lane_shares(const StageCost& c, int count, int nleaf, int numax, int64_t most) {
+  int best = 0;
+  if (!lane_form<D, R>(numax)) return best;
+  double least = stage_cost(c, D, count, nleaf, numax, 0);
+  for (int s = 1; s <= LANE_SHARES && (s == 1 || s <= most); ++s) {
+    const double t = stage_cost(c, D, count, nleaf, numax, s);
+    if (t < least) { least = t; best = s; }
+  }
+  return best;
+}
+
+// What a step of a case with nleaf leaves takes: leaf shares of the target and
+// of the interface stage.
+struct StepForms {
+  int nleaf = -1;
+  int target = 0, face = 0;
+};
+
+}  // namespace avs

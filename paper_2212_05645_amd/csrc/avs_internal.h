@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "avs_forms.h"
+
 namespace avs {
 
 constexpr int BLOCK = 256;       // threads per workgroup (4 wave64)

@@ -1483,76 +1483,16 @@ __global__ __launch_bounds__(BLOCK) void k_target(Geo g, Leaves L, VGrid vg, con
 // kernel) -> 15 us, 11 880 x 1252 FP32 134 + 7 -> 42 us, 2574 x 4404 FP64
 // 3-D 66 + 8 -> 41 us, 36 864 x 19 972 FP32 3-D 1.81 -> 1.24 ms (bound by
 // VALU issue: about 54 instructions per cell and leaf against 71).
-// The tables of 64 lanes have to fit the LDS: lane_form is the rule.
-constexpr int LANE_WAVES = 16;
+// avs_forms.h chooses between the two.
 constexpr int LANE_BLOCK = 64 * LANE_WAVES;
-constexpr size_t LANE_LDS = 144 * 1024;     // of 160 KiB per CU
 
-template <int D, typename R>
-constexpr size_t lane_tab_bytes(int numax) { return (size_t)D * numax * 64 * sizeof(R); }
-
-// True when the 64-lane form's tables fit (numax up to 144 in FP64 2-D, 288
-// in FP32 2-D, 192 in FP32 3-D).
-template <int D, typename R>
-inline bool lane_form(int numax) { return lane_tab_bytes<D, R>(numax) <= LANE_LDS; }
-
-// Dynamic LDS: the tables, later the waves' partial sums (nacc doubles per
-// lane from half of the waves).
-template <int D, typename R>
-inline size_t lane_lds(int numax, int nacc) {
-  const size_t t = lane_tab_bytes<D, R>(numax), r = (size_t)(LANE_WAVES / 2) * nacc * 64 * sizeof(double);
-  return t > r ? t : r;
-}
-
-// The interface stage's: the faces' raw moments wait in the same place.
+// The interface stage's dynamic LDS: the faces' raw moments wait in the place
+// of the tables and sums.
 template <int D, typename R>
 inline size_t lane_face_lds(int numax) {
   const size_t t = lane_lds<D, R>(numax, D + 2), m = (size_t)Cfg<D>::NM * 64 * sizeof(double);
   return t > m ? t : m;
 }
-
-// Leaf shares: a launch has ceil(n / 64) groups of lanes, each able to fill a
-// CU (or, with small tables, half of one).  When those do not fill the 256
-// CUs evenly the leaves are split over several workgroups per group, whose
-// sums a finishing kernel adds.  The number of shares is the one of least
-// estimated time, rounds of workgroups times the work of one in leaves: its
-// leaves, its tables (an exponential costs about what a leaf does) and 640
-// leaves' worth of reduction and latency; the finishing launch counts 1500.
-// (Sphere, 36 864 cells x 19 972 leaves, FP32: 576 groups are 2.25 rounds.
-// 2574 cells x 4404 leaves, FP64: 41 groups of 256 CUs.)
-// At most `most` shares (the partial sums' room).
-template <int D, typename R>
-inline int lane_shares(int count, int nleaf, int numax, int nacc, int64_t most) {
-  const int groups = (count + 63) / 64;
-  const int64_t per_cu = lane_lds<D, R>(numax, nacc) + 12 * 1024 <= 80 * 1024 ? 2 : 1, slots = 256 * per_cu;
-  int best = 1;
-  int64_t cost = INT64_MAX;
-  for (int s = 1; s <= 16 && s <= most; ++s) {
-    const int64_t rounds = ((int64_t)groups * s + slots - 1) / slots;
-    const int64_t c = rounds * per_cu * ((nleaf + s - 1) / s + D * numax + 640) + (s > 1 ? 1500 : 0);
-    if (c < cost) { cost = c; best = s; }
-  }
-  return best;
-}
-
-// The lane form pays while the shares' tables and reductions, each share's
-// anew, stay within twice the leaves' own work; beyond (few groups, fine
-// velocity grids) a workgroup per cell or per four faces does less, alone or
-// among other cases in one launch, which takes the form of the case alone.
-// Five batched cases of 646 to 1334 cells x 2212 leaves FP32 (16 shares, 256
-// table entries): lanes 94 + 79 us, workgroups 74 + 56; 2574 cells x 4404
-// leaves FP64 3-D (6 shares, 64 entries): 43 against 75.
-inline bool lane_work_pays(int shares, int D, int nleaf, int numax) {
-  return (int64_t)shares * (D * numax + 640) <= 2 * ((int64_t)nleaf + 640);
-}
-
-// The interface stage takes it from FACE_LANES faces on: with fewer most of the
-// chip idles, and a workgroup per four faces is done sooner.  Four faces /
-// lanes, us: 312 faces x 300 leaves FP64 11.9 / 14.3; 2100 x 700 3-D 15.0 /
-// 21.7; 5200 x 300 22.1 / 15.3; 10 400 x 1500 39.7 / 35.2; 12 300 x 1500 3-D
-// 57.5 / 37.1.  Alone the forms cross between 2600 faces (300 leaves) and some
-// 10 000 (1500); many cases in one launch fill the chip with groups of fewer.
-constexpr int FACE_LANES = 1536;
 
 // Tables of the 64 lanes' Maxwellians from their records spar[NPAR][64]:
 // tab[d][u][lane] = exp(-(x_u - U_d)^2 / 2RT).
