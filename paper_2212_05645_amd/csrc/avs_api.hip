@@ -473,6 +473,7 @@ const StepForms& step_forms(avs_ctx* ctx) {
   f.nleaf = n;
   f.target = lane_shares<D, T>(TARGET_COST, ctx->nc, n, nu, room(ctx->nc, D + 2 + Cfg<D>::NS));
   f.face = lane_shares<D, T>(FACE_COST, ctx->nf, n, nu, room(ctx->nf, D + 2));
+  f.wave = passC_wave_form<D, T>(ctx->nc, n, nu);
   return f;
 }
 
@@ -566,8 +567,9 @@ avs_status launch_step(avs_ctx* ctx, bool last_residual) {
   if (avs_status st = launch_target<D, T>(ctx)) return st;
   {
     ProfScope ps(ctx, K_PASSC);
+    static_assert(MAXF == 2 * D, "passC_tab");
     const size_t shm = passC_tab<D, T>(nu);
-    if (passC_wave_form<D, T>(L.n, nu))
+    if (step_forms<D, T>(ctx).wave)
       k_passC<D, T, 64><<<(unsigned)round_up(ctx->nc, 8), 64, shm, ctx->stream>>>(
           ctx->geo, L, ctx->vg, vin, (const T*)ctx->fv, vout, ctx->fpar, ctx->tpar, ctx->lam, ctx->mom, ctx->q);
     else
@@ -947,7 +949,7 @@ avs_status batch_upload(avs_batch* b) {
     const int gx = (int)round_up(c->nc, 8);
     const int fb = c->D == 2 ? face_batch<2>() : face_batch<3>();
     const bool lanes = args[i].shares > 0, flanes = args[i].fshares > 0;
-    const bool wavec = c->D == 2 ? passC_wave_form<2, T>(nl, c->vg.numax) : passC_wave_form<3, T>(nl, c->vg.numax);
+    const bool wavec = c->forms.wave;      // (chosen by case_args)
     const int fg = (c->nf + 63) / 64;
     const int cnt[BK_N] = {gx * ((nl + ch - 1) / ch), flanes ? 0 : (c->nf + fb - 1) / fb,
                            flanes ? fg * args[i].fshares : 0, flanes && args[i].fshares > 1 ? fg : 0,

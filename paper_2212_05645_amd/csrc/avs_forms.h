@@ -103,11 +103,40 @@ inline int lane_shares(const StageCost& c, int count, int nleaf, int numax, int6
   return best;
 }
 
+// Exponential tables of a cell in pass C: one per face and the cell's own, of
+// at most MAXF = 2 D faces.
+template <int D, typename T>
+constexpr size_t passC_tab(int numax) { return (size_t)(2 * D + 1) * D * numax * sizeof(T); }
+constexpr size_t PASSC_WAVE_TAB = 12 * 1024;
+
+// One wave per cell in pass C instead of four, where the leaves are few, the
+// tables small enough for many such workgroups in a CU's LDS, and the cells
+// many: a cell's leaves then take four times as long (11 us per 1000 of them),
+// which costs more than the set-ups of four cells at once save unless every CU
+// has several cells to turn to.  What is saved per turn of 256 cells shrinks
+// with the leaves and the tables; least-squares fit to 790 steps in both forms
+// (64 to 12 000 cells, 64 to 1536 leaves, 1.3 to 12 KiB of tables), whose
+// better form the rule misses by 0.2 % of a step on average.  Whole steps, us,
+// four waves / one:
+//   FP32 2-D, 798 leaves, 5 KiB    144 cells 47 / 54   1500 73 /  79   3584 112 / 110    12 000 268 / 253
+//   FP64 2-D, 298 leaves, 5 KiB    144       41 / 44   1500 66 /  64   3584  99 /  88    12 000 244 / 208
+//   FP32 3-D, 1492 leaves, 5 KiB    75       64 / 85   1080 105 / 126  5760 306 / 320
+//   FP64 3-D, 148 leaves, 3 KiB     75       42 / 45   1080  62 /  63  5760 177 / 164
+template <int D, typename T>
+inline bool passC_wave_form(int nc, int nleaf, int numax) {
+  const size_t tab = passC_tab<D, T>(numax);
+  if (tab > PASSC_WAVE_TAB || nleaf > 1536) return false;
+  const double l = nleaf / 1000.0, t = tab / 10240.0, turns = nc / 256.0;
+  return sizeof(T) == 4 ? turns * (0.62 + 0.20 * l - 0.46 * t - 0.30 * l * t) > 0.6 + 11.0 * l
+                        : turns * (0.94 - 0.25 * l - 0.36 * l * t) > 0.6 + 13.2 * l;
+}
+
 // What a step of a case with nleaf leaves takes: leaf shares of the target and
-// of the interface stage.
+// of the interface stage, one wave per cell in pass C.
 struct StepForms {
   int nleaf = -1;
   int target = 0, face = 0;
+  bool wave = false;
 };
 
 }  // namespace avs

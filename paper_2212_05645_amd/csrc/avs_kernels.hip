@@ -2263,20 +2263,6 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
   }
 }
 
-// One wave per cell where the leaves are few and the cell's tables small
-// enough for many such workgroups in a CU's LDS.  Measured, four waves / one:
-// 4096 cells x 256 leaves FP64 (2.5 KiB of tables) 53 / 32 us; 11 880 x 1252
-// FP32 (5 KiB) 157 / 128; 3840 x 1200 FP32 3-D (5.3 KiB) 79 / 71, x 2400
-// 115 / 115; 4608 x 300 FP32 (10 KiB) 44 / 37, x 600 53 / 52, x 1200 66 / 79.
-template <int D, typename T>
-constexpr size_t passC_tab(int numax) { return (size_t)(Cfg<D>::MAXF + 1) * D * numax * sizeof(T); }
-constexpr size_t PASSC_WAVE_TAB = 12 * 1024;
-template <int D, typename T>
-inline bool passC_wave_form(int nleaf, int numax) {
-  const size_t tab = passC_tab<D, T>(numax);
-  return (tab <= 6 * 1024 && nleaf <= 1536) || (tab <= PASSC_WAVE_TAB && nleaf <= 512);
-}
-
 template <int D, typename T, int NT>
 __global__ __launch_bounds__(NT, (waves_hint<D, T>())) void k_passC(Geo g, Leaves L, VGrid vg, const T* __restrict__ vin,
                                                      const T* __restrict__ fv, T* __restrict__ vout,

@@ -1,5 +1,6 @@
 """The library's rules of a step's forms (csrc/avs_forms.h), compiled for the
-host: leaf shares of the 64-lane target and interface stage."""
+host: leaf shares of the 64-lane target and interface stage, waves per cell in
+pass C."""
 import ctypes as C
 import functools
 import os
@@ -22,6 +23,10 @@ extern "C" int shares(int dim, int fp32, int count, int nleaf, int numax, int fa
 extern "C" double cost(int dim, int count, int nleaf, int numax, int face, int shares) {
   const StageCost& c = face ? FACE_COST : TARGET_COST;
   return stage_cost(c, dim, count, nleaf, numax, shares);
+}
+extern "C" int wave(int dim, int fp32, int nc, int nleaf, int numax) {
+  return BY_TYPE((passC_wave_form<2, double>(nc, nleaf, numax)), (passC_wave_form<2, float>(nc, nleaf, numax)),
+                 (passC_wave_form<3, double>(nc, nleaf, numax)), (passC_wave_form<3, float>(nc, nleaf, numax)));
 }
 extern "C" int form(int dim, int fp32, int numax) {
   return BY_TYPE((lane_form<2, double>(numax)), (lane_form<2, float>(numax)), (lane_form<3, double>(numax)),
@@ -56,3 +61,8 @@ def cost(dim, count, nleaf, numax, face, nshares):
 def form(dim, fp32, numax):
     return bool(lib().form(dim, fp32, numax))
 
+
+
+def wave(dim, fp32, nc, nleaf, numax):
+    """One wave per cell in pass C."""
+    return bool(lib().wave(dim, fp32, nc, nleaf, numax))

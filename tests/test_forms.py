@@ -93,3 +93,38 @@ def test_shares_respect_every_limit():
                                 s = forms.shares(dim, fp32, count, nleaf, numax, face, most)
                                 assert 0 <= s <= min(max(1, most), 16)
                                 assert s == 0 or forms.form(dim, fp32, numax)
+
+
+# Whole explicit steps, us, with four waves per cell in pass C and with one:
+# (dim, fp32, cells, leaves, table entries, four, one)
+PASSC = [
+    (2, 1, 64, 1530, 120, 54, 69),
+    (2, 1, 64, 1198, 128, 50, 62),
+    (2, 1, 144, 795, 120, 47, 55),
+    (2, 1, 12000, 76, 32, 125, 102),
+    (2, 1, 7000, 148, 32, 86, 74),
+    (2, 1, 7000, 507, 72, 125, 114),
+    (2, 0, 64, 1200, 72, 54, 69),
+    (2, 0, 144, 796, 64, 50, 58),
+    (2, 0, 64, 300, 72, 40, 44),
+    (2, 0, 12000, 76, 32, 181, 136),
+    (2, 0, 3584, 76, 64, 72, 59),
+    (2, 0, 7000, 298, 64, 155, 135),
+    (3, 1, 75, 1513, 72, 64, 86),
+    (3, 1, 75, 1184, 64, 61, 77),
+    (3, 1, 1080, 1492, 64, 105, 126),
+    (3, 1, 5760, 64, 16, 120, 104),
+    (3, 1, 2574, 288, 16, 86, 82),
+    (3, 0, 75, 1532, 24, 72, 96),
+    (3, 0, 75, 468, 48, 52, 61),
+    (3, 0, 288, 300, 24, 51, 54),
+    (3, 0, 5760, 64, 16, 159, 139),
+    (3, 0, 2574, 288, 16, 113, 109),
+]
+
+
+@pytest.mark.parametrize("dim,fp32,nc,nleaf,numax,four,one", PASSC)
+def test_pass_c_takes_the_faster_measured_form(dim, fp32, nc, nleaf, numax, four, one):
+    """By more than the 1 us and 2 % that two runs may differ by."""
+    us = one if forms.wave(dim, fp32, nc, nleaf, numax) else four
+    assert us <= min(four, one) + 1.0 + 0.02 * four
