@@ -128,3 +128,9 @@ def test_pass_c_takes_the_faster_measured_form(dim, fp32, nc, nleaf, numax, four
     """By more than the 1 us and 2 % that two runs may differ by."""
     us = one if forms.wave(dim, fp32, nc, nleaf, numax) else four
     assert us <= min(four, one) + 1.0 + 0.02 * four
+
+
+def test_the_gpu_tests_sizes_are_in_the_forms_they_are_for():
+    import test_gpu_forms as G
+    for name, prec in G.ALONE + [(n, prec) for names, prec in G.BATCHED for n in names]:
+        G.build(name, prec)
