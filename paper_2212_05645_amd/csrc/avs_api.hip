@@ -1622,7 +1622,7 @@ size_t dia_layout(const avs_ctx* c, int64_t max_leaves, avs_dia* d, char* base) 
   Carver cv{base};
   // rows for at most max_leaves leaves
   const size_t nc = c->nc, nf = c->nf, cap = (size_t)round_up(max_leaves, 64);
-  const size_t D = c->D, NW = D + 3, NQ = 2 * D, NT = 6 + 3 * D;
+  const size_t D = c->D, NW = D + 3, NQ = 2 * D, NT = D == 2 ? Dg<2>::NT : Dg<3>::NT;
   for (int t = 0; t < 2; ++t) {
     double* p = cv.take<double>(3 * nc * cap);
     if (d) d->v[t] = p;

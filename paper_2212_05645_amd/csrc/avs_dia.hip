@@ -25,9 +25,8 @@ template <int D>
 struct Dg {
   static constexpr int NW = D + 3;           // rho, rho U, rho E, rho E_rot
   static constexpr int NQ = 2 * D;           // q_t, q_r
-  // record: rho, U[D], T_t, T_r, q_t[D], q_r[D], dt/tau, E_rot target, T
-  static constexpr int IT = 1 + D, IR = 2 + D, IQT = 3 + D, IQR = 3 + 2 * D, IDT = 3 + 3 * D, IER = 4 + 3 * D,
-                       IT0 = 5 + 3 * D, NT = 6 + 3 * D;
+  // target record of a cell: U[D], dt/tau, E_rot target
+  static constexpr int IDT = D, IER = D + 1, NT = D + 2;
   static constexpr int MAXF = Cfg<D>::MAXF;
   // closure sums: the base triple's moments, then sum A g (1, c_d, c_d c_e (d <= e), |c|^2 c_d, |c|^4)
   static constexpr int NACC = NW + 2 + 2 * D + D * (D + 1) / 2;
@@ -392,17 +391,13 @@ __global__ void k_dg_macro(Geo g, GasP vgas, DiaGas gp, double dt, const double*
   for (int m = 0; m < NW; ++m) Wn[(size_t)i * NW + m] = w[m];
   dg_temps<D>(w, gp.R, rho, U, Tt, Tr, T);
   double* r = tp + (size_t)i * C::NT;
-  r[0] = rho;
-  for (int d = 0; d < D; ++d) r[1 + d] = U[d];
-  r[C::IT] = Tt;
-  r[C::IR] = Tr;
-  for (int d = 0; d < C::NQ; ++d) r[C::IQT + d] = q[(size_t)i * C::NQ + d];
+  for (int d = 0; d < D; ++d) r[d] = U[d];
   r[C::IDT] = dt / tt;
   r[C::IER] = (1.0 - 1.0 / gp.Z) * w[2 + D] + rho * gp.R * T / gp.Z;
-  r[C::IT0] = T;
+  const double* qi = q + (size_t)i * C::NQ;
   double* e = crec + (size_t)i * C::REC;
   e[C::RA] = 1.0 / gp.Z;
-  dg_record<D>(gp, rho, U, Tt, Tr, r + C::IQT, r + C::IQR, 1.0 - 1.0 / gp.Z, 1.0, e);
+  dg_record<D>(gp, rho, U, Tt, Tr, qi, qi + D, 1.0 - 1.0 / gp.Z, 1.0, e);
 }
 
 // Closure sums of one leaf: the base triple's moments and the moments of g
@@ -677,18 +672,14 @@ __global__ void k_dg_initrec(int nc, DiaGas gp, const double* __restrict__ W, do
   double rho, U[D], Tt, Tr, T;
   if (!dg_temps<D>(W + (size_t)i * C::NW, gp.R, rho, U, Tt, Tr, T)) atomicMin(bad, i);
   double* r = tp + (size_t)i * C::NT;
-  r[0] = rho;
-  for (int d = 0; d < D; ++d) r[1 + d] = U[d];
-  r[C::IT] = Tt;
-  r[C::IR] = Tr;
-  for (int d = 0; d < C::NQ; ++d) r[C::IQT + d] = 0.0;
+  for (int d = 0; d < D; ++d) r[d] = U[d];
   r[C::IDT] = 0.0;
   r[C::IER] = W[(size_t)i * C::NW + 2 + D];
-  r[C::IT0] = T;
   // the translational part alone
+  const double q0[C::NQ] = {};
   double* e = crec + (size_t)i * C::REC;
   e[C::RA] = 0.0;
-  dg_record<D>(gp, rho, U, Tt, Tr, r + C::IQT, r + C::IQR, 1.0, 1.0, e);
+  dg_record<D>(gp, rho, U, Tt, Tr, q0, q0 + D, 1.0, 1.0, e);
 }
 
 // Heat fluxes q_t, q_r of the state about the U of the record tp.
@@ -711,7 +702,7 @@ __global__ __launch_bounds__(BLOCK) void k_dg_heat(Geo g, Leaves L, const double
     double c[D], c2 = 0.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      c[d] = xi[d] - r[1 + d];
+      c[d] = xi[d] - r[d];
       c2 += c[d] * c[d];
     }
     const double et = A * 0.5 * (c2 * vdf[o] + vdf[cs + o]), er = A * vdf[2 * cs + o];
