@@ -118,7 +118,7 @@ __device__ __forceinline__ void block_sum(double (&v)[N], double* red) {
 
 // Block total of each of N per-thread values, returned to thread t < N for
 // entry t (other threads get 0); the same association as block_sum.
-template <int N, int NT = BLOCK>
+template <int N>
 __device__ __forceinline__ double block_sum_pick(double (&v)[N], double* red) {
   int id;
   const double x = wave_totals<N>(v, id);
@@ -127,11 +127,7 @@ __device__ __forceinline__ double block_sum_pick(double (&v)[N], double* red) {
   if (id < N) red[w * N + id] = x;
   __syncthreads();
   const int t = threadIdx.x;
-  double r = 0.0;
-  if (t < N)
-#pragma unroll
-    for (int q = 0; q < NT / 64; q += 4)
-      r += (red[q * N + t] + red[(q + 1) * N + t]) + (red[(q + 2) * N + t] + red[(q + 3) * N + t]);
+  const double r = t < N ? (red[t] + red[N + t]) + (red[2 * N + t] + red[3 * N + t]) : 0.0;
   __syncthreads();
   return r;
 }
@@ -1977,7 +1973,7 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
   using RP = const __attribute__((address_space(4))) double*;
   extern __shared__ double lds_d[];
   T* lds = reinterpret_cast<T*>(lds_d);
-  __shared__ double red[(NT < BLOCK ? BLOCK : NT) / 64 * (N + D)];
+  __shared__ double red[BLOCK / 64 * (N + D)];
   __shared__ double dpar[(MAXF + 1) * NPAR];
   __shared__ T spar[(MAXF + 1) * NPAR];
   __shared__ double snrm[MAXF][D];
@@ -2257,7 +2253,7 @@ __device__ __forceinline__ void d_passC(Geo g, Leaves L, VGrid vg, const T* __re
     else if (m < N + D) qout[(size_t)i * D + m - N] = v;
   } else {
     const int t = threadIdx.x;
-    const double v = block_sum_pick<N + D, NT>(acc, red);
+    const double v = block_sum_pick<N + D>(acc, red);
     if (t < N) mom[(size_t)i * N + t] = v;
     else if (t < N + D) qout[(size_t)i * D + t - N] = v;
   }
