@@ -374,7 +374,7 @@ int32_t avs_profile_read(avs_ctx *ctx, int32_t nmax, char *names_host, double *m
  * one bucket at a time, then whether pass C keeps one or two leaves' loads
  * in flight; each candidate is timed on two steps computed into the spare
  * buffers and not taken, so the members' state is the same afterwards
- * (their implicit-predictor and remap scratch is overwritten).  chunk_host
+ * (their implicit-predictor scratch is overwritten).  chunk_host
  * (or NULL) receives five ints: the four chunks and the pass-C choice (0/1).
  * avs_batch_check waits and reports a non-physical state in any member. */
 typedef struct avs_batch avs_batch;

@@ -86,7 +86,7 @@ struct avs_ctx {
   int ld[2] = {0, 0};
   StepForms forms;        // of the current leaf count (step_forms)
 
-  double *W, *Wn, *q, *mom, *tpar, *lam, *fpar, *F, *bden, *bfin, *bcpair, *momp, *res, *tot;
+  double *W, *Wn, *q, *mom, *tpar, *lam, *fpar, *F, *bden, *bfin, *bcpair, *res, *tot;
   double* fmom;           // face-moment partials of pass A: [nf+1][2 sides][nchs chunks][NM]
   int nchs;               // chunk stride of fmom: ceil(capacity / CHUNK_MIN)
   double *cc, *crit_part, *Mk, *probe_cc, *probe_prim;
@@ -269,7 +269,6 @@ void carve(avs_ctx& x, Carver& c) {
   x.bden = c.take<double>(nf + 1);
   x.bfin = c.take<double>((nf + 1) * N);
   x.bcpair = c.take<double>((size_t)(x.nbc + 1) * x.P * cap);
-  x.momp = c.take<double>(nc * N);
   x.res = c.take<double>(N);
   x.tot = c.take<double>(N);
   x.cc = c.take<double>(nc * N);
@@ -1032,14 +1031,15 @@ avs_status batch_launch(avs_batch* b, int nsteps) {
 
 // One step of every case computed into the spare buffers without taking it
 // (the state W, phi^n stays where it is); the heat flux and moments that
-// pass C overwrites are saved in each case's implicit-predictor and remap
-// scratch and put back.  Used to time tile choices on the cases' own state.
+// pass C overwrites are saved in each case's implicit-predictor scratch (irhs
+// and prow, both larger) and put back.  Used to time tile choices on the cases'
+// own state.
 avs_status batch_dry_step(avs_batch* b) {
   avs_ctx* ctx = nullptr;
   const bool f64 = b->prec == AVS_FP64;
   for (avs_ctx* c : b->cases) {
     CK(hipMemcpyAsync(c->irhs, c->q, sizeof(double) * c->nc * c->D, hipMemcpyDeviceToDevice, b->stream));
-    CK(hipMemcpyAsync(c->momp, c->mom, sizeof(double) * c->nc * (c->D + 2), hipMemcpyDeviceToDevice, b->stream));
+    CK(hipMemcpyAsync(c->prow, c->mom, sizeof(double) * c->nc * (c->D + 2), hipMemcpyDeviceToDevice, b->stream));
   }
   avs_status st = f64 ? batch_upload<double>(b) : batch_upload<float>(b);
   if (st) return st;
@@ -1048,7 +1048,7 @@ avs_status batch_dry_step(avs_batch* b) {
   if (st) return st;
   for (avs_ctx* c : b->cases) {
     CK(hipMemcpyAsync(c->q, c->irhs, sizeof(double) * c->nc * c->D, hipMemcpyDeviceToDevice, b->stream));
-    CK(hipMemcpyAsync(c->mom, c->momp, sizeof(double) * c->nc * (c->D + 2), hipMemcpyDeviceToDevice, b->stream));
+    CK(hipMemcpyAsync(c->mom, c->prow, sizeof(double) * c->nc * (c->D + 2), hipMemcpyDeviceToDevice, b->stream));
   }
   return AVS_OK;
 }
