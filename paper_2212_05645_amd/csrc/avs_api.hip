@@ -470,8 +470,8 @@ const StepForms& step_forms(avs_ctx* ctx) {
     return (int64_t)(ctx->vdf_buf_bytes / (round_up(count, 64) * nacc * sizeof(double)));
   };
   f.nleaf = n;
-  f.target = lane_shares<D, T>(TARGET_COST, ctx->nc, n, nu, room(ctx->nc, D + 2 + Cfg<D>::NS));
-  f.face = lane_shares<D, T>(FACE_COST, ctx->nf, n, nu, room(ctx->nf, D + 2));
+  f.target = lane_shares<D, T>(target_cost<D>(), ctx->nc, n, nu, room(ctx->nc, D + 2 + Cfg<D>::NS));
+  f.face = lane_shares<D, T>(face_cost<T>(), ctx->nf, n, nu, room(ctx->nf, D + 2));
   f.wave = passC_wave_form<D, T>(ctx->nc, n, nu);
   return f;
 }

@@ -38,10 +38,16 @@ struct StageCost {
                                     // turn, a leaf of one of its cells or faces, a leaf of the longest chain
   double lround, lleaf;             // 64-lane form: a workgroup in its CU's turn, a leaf
 };
-constexpr StageCost TARGET_COST = {1, 10.7, 0.94, 0.34, 0.25, 4.5, 21.5};
-constexpr StageCost FACE_COST = {4, 3.9, 1.9, 0.17, 0.9, 3.5, 13.4};
-constexpr double GROUP_TAB = 2.1, LANE_TAB = 17.0;       // a workgroup's exponential tables
-constexpr double CLOSE_BASE = 2.4, CLOSE_SHARE = 0.4;    // the launch that adds several shares
+constexpr StageCost TARGET_COST[2] = {{1, 10.5, 0.90, 0.35, 0.45, 4.2, 22.0},     // 2-D
+                                      {1, 13.0, 1.20, 0.48, 0.10, 5.0, 24.4}};    // 3-D
+constexpr StageCost FACE_COST[2] = {{4, 3.8, 2.40, 0.26, 0.45, 3.8, 16.8},        // FP64
+                                    {4, 5.0, 1.85, 0.21, 0.60, 4.2, 13.8}};       // FP32
+template <int D>
+constexpr const StageCost& target_cost() { return TARGET_COST[D - 2]; }
+template <typename R>
+constexpr const StageCost& face_cost() { return FACE_COST[sizeof(R) == 4]; }
+constexpr double GROUP_TAB = 3.7, LANE_TAB = 16.5;       // a workgroup's exponential tables
+constexpr double CLOSE_BASE = 3.3, CLOSE_SHARE = 0.4;    // the launch that adds several shares
 constexpr double SHARED_WORK = 3.0;                      // weight of the work beside the time alone
 constexpr double LANE_MARGIN = 3.0;                      // what the lanes have to gain
 
@@ -69,8 +75,9 @@ inline double stage_cost(const StageCost& c, int D, int count, int nleaf, int nu
 // sums another launch adds.
 // The constants are a least-squares fit to a sweep of whole steps, 508 sizes x
 // 9 forms of either stage (32 to 36 864 cells, 76 to 19 972 leaves, 20 to 288
-// table entries, 2-D and 3-D, FP64 and FP32).  Whole steps, us, workgroup form /
-// lanes with 1, 2, 4 and 8 shares:
+// table entries, 2-D and 3-D, FP64 and FP32), and to the stages' own times at 85
+// of the larger sizes x 4 forms.  Whole steps, us, workgroup form / lanes with 1,
+// 2, 4 and 8 shares:
 //   target     600 cells x 1498 leaves, 256 entries, FP32     66 /  95  83  76  73
 //             3584 x 1498, 256, FP32                         161 / 174 162 157 170
 //             7000 x 1498, 256, FP32                         286 / 283 272 286 309
@@ -85,11 +92,11 @@ inline double stage_cost(const StageCost& c, int D, int count, int nleaf, int nu
 // cases and of 19 FP32 batches (400 to 7000 cells, 300 to 16 000 leaves, sizes
 // drawn at random) against a rule for full chips, the lanes wherever their
 // tables fit and the shares' tables stay within twice the leaves' work: with
-// weight 0 the single cases are 4 % faster and the batches 12 % slower on
-// average, with 2 3.5 and 8 %, with 3 2.4 and 6 %, with 6 1 and 3 %, with 9 no
-// faster and 2 % faster.  With 3 none of the single cases is more than 5 %
-// slower than by that rule, and those it had made up to half as slow again (75
-// to 900 cells x 1500 leaves) are back at the workgroup form.
+// weight 0 the single cases are 4.3 % faster and the batches 10.5 % slower on
+// average, with 1 4.1 and 7.7 %, with 3 3.0 and 6.0 %, with 6 1.4 and 3.9 %.
+// With 3 none of the single cases is more than 5 % slower than by that rule, and
+// those it had made up to half as slow again (75 to 900 cells x 1500 leaves) are
+// back at the workgroup form; the largest cases take the faster form as by it.
 // At most `most` shares (the partial sums' room; one share needs none).
 template <int D, typename R>
 inline int lane_shares(const StageCost& c, int count, int nleaf, int numax, int64_t most) {

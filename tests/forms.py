@@ -15,14 +15,16 @@ SRC = """
 using namespace avs;
 #define BY_TYPE(expr2d, expr2f, expr3d, expr3f) \
   (dim == 2 ? (fp32 ? expr2f : expr2d) : (fp32 ? expr3f : expr3d))
+static const StageCost& stage(int dim, int fp32, int face) {
+  return face ? (fp32 ? face_cost<float>() : face_cost<double>()) : dim == 2 ? target_cost<2>() : target_cost<3>();
+}
 extern "C" int shares(int dim, int fp32, int count, int nleaf, int numax, int face, int64_t most) {
-  const StageCost& c = face ? FACE_COST : TARGET_COST;
+  const StageCost& c = stage(dim, fp32, face);
   return BY_TYPE((lane_shares<2, double>(c, count, nleaf, numax, most)), (lane_shares<2, float>(c, count, nleaf, numax, most)),
                  (lane_shares<3, double>(c, count, nleaf, numax, most)), (lane_shares<3, float>(c, count, nleaf, numax, most)));
 }
-extern "C" double cost(int dim, int count, int nleaf, int numax, int face, int shares) {
-  const StageCost& c = face ? FACE_COST : TARGET_COST;
-  return stage_cost(c, dim, count, nleaf, numax, shares);
+extern "C" double cost(int dim, int fp32, int count, int nleaf, int numax, int face, int shares) {
+  return stage_cost(stage(dim, fp32, face), dim, count, nleaf, numax, shares);
 }
 extern "C" int wave(int dim, int fp32, int nc, int nleaf, int numax) {
   return BY_TYPE((passC_wave_form<2, double>(nc, nleaf, numax)), (passC_wave_form<2, float>(nc, nleaf, numax)),
@@ -43,7 +45,7 @@ def lib():
         subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fPIC", "-shared", f"-I{CSRC}", src, "-o", so], check=True)
         h = C.CDLL(so)
     h.shares.argtypes = [C.c_int] * 6 + [C.c_int64]
-    h.cost.argtypes, h.cost.restype = [C.c_int] * 6, C.c_double
+    h.cost.argtypes, h.cost.restype = [C.c_int] * 7, C.c_double
     return h
 
 
@@ -53,9 +55,9 @@ def shares(dim, fp32, count, nleaf, numax, face, most=1 << 40):
     return lib().shares(dim, fp32, count, nleaf, numax, face, most)
 
 
-def cost(dim, count, nleaf, numax, face, nshares):
+def cost(dim, fp32, count, nleaf, numax, face, nshares):
     """The rule's cost of the lane form, of the workgroup form for 0 shares."""
-    return lib().cost(dim, count, nleaf, numax, face, nshares)
+    return lib().cost(dim, fp32, count, nleaf, numax, face, nshares)
 
 
 def form(dim, fp32, numax):

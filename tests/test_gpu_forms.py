@@ -40,8 +40,8 @@ SIZES = {
     "cells_65": ((13, 5), 5, 1, 0.3, "one", "group", False),
     # split leaves
     "split_2d": ((35, 31), 32, 0, 0.0, "several", "several", False),
-    "split_target_2d": ((17, 19), 18, 0, 0.0, "several", "group", False),
-    "split_3d": ((8, 8, 9), 9, 0, 0.0, "several", "several", False),
+    "split_target_2d": ((20, 21), 20, 0, 0.0, "several", "group", False),
+    "split_3d": ((9, 9, 9), 11, 0, 0.0, "several", "several", False),
     # pass C with one wave per cell: fewer leaves than lanes, one leaf per
     # lane, and two rounds of both load schemes
     "wave_2d": ((27, 28), 5, 1, 0.3, "one", "one", True),
@@ -74,7 +74,7 @@ def build(name, prec):
 
 
 ALONE = [
-    ("cells_63", 0), ("cells_64", 0), ("cells_65", 0), ("cells_65", 1),
+    ("cells_63", 0), ("cells_64", 0), ("cells_65", 0),
     ("limit_2d_fp64", 0), ("limit_2d_fp32", 1), ("limit_3d_fp64", 0), ("limit_3d_fp32", 1), ("beyond_2d_fp64", 0),
     ("split_2d", 0), ("split_2d", 1), ("split_target_2d", 0), ("split_3d", 0), ("split_3d", 1),
     ("wave_2d", 0), ("wave_2d", 1), ("wave_64_2d", 0), ("wave_3_2d", 0), ("wave_3_2d", 1), ("wave_3d", 0), ("wave_3d", 1)]
