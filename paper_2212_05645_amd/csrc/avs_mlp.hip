@@ -43,9 +43,10 @@ constexpr int G_W1 = 0, G_B1 = G_W1 + NINP * NH, G_W2 = G_B1 + NH, G_B2 = G_W2 +
 // so that 16 rows fall on different banks.  (Element by element, an operand
 // was four 2-byte reads; with 4 waves per tile.  Gradient of 8192 rows 40 ->
 // 18 us, logits of 19 678 rows 25 -> 7.6 us; both bound by the latency of one
-// tile.)  H2 takes H1's place (a wave
-// reads and writes its own 16 rows only) except in training, where W2 takes
-// W2T's place once the forward pass is through with it.
+// tile.)  H2 takes H1's place, except in training, where W2 takes W2T's place
+// once the forward pass is through with it.  Two waves share each slab of 16
+// rows (and write half of its columns each), all waves W2T: either overlay needs
+// the barrier between the last read of the old values and the first write.
 constexpr int SNI = NINP + 4, SNH = NH + 4, SNO = NOUTP + 4, STL = TILE + 4;   // padded rows
 constexpr int L_T1 = 0, L_T2 = L_T1 + NH * SNI, L_T3 = L_T2 + NH * SNH, L_X = L_T3 + NOUTP * SNH,
               L_H = L_X + TILE * SNI, L_FWD = L_H + TILE * SNH;
@@ -194,8 +195,8 @@ __global__ __launch_bounds__(MPB) void k_mlp_tile(int n, const uint16_t* __restr
     }
   }
   __syncthreads();
-  // H2 = bf16(relu(H1 W2 + b2)); the wave's rows of H1 are read before any of
-  // H2 is written
+  // H2 = bf16(relu(H1 W2 + b2)); the barrier: H2's rows are H1's, which another
+  // wave reads too, and W2T, which all of them read, is replaced
   {
     f4 acc[NT];
 #pragma unroll
