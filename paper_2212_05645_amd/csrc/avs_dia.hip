@@ -527,7 +527,7 @@ __global__ __launch_bounds__(BLOCK) void k_dg_target(Geo g, Leaves L, VGrid vg, 
 // from the face's record, for both of its cells, so that the interface rows
 // are read by one kernel and never rewritten.  The ten Maxwellians of a leaf
 // are evaluated where they are used: the kernel is bound by the rows' bandwidth
-// (7.9 GB, 2.13 ms at 8192 cells x 9988 leaves, 3.7 TB/s), and per-axis tables
+// (7.9 GB, 1.85 ms at 8192 cells x 9988 leaves, 4.3 TB/s), and per-axis tables
 // in LDS, whose size sets the workgroups per CU, measured within 3 % of it on
 // both sides (4096 cells: 2573 / 2654 us per step with / without tables of 40
 // KiB, 5035 / 5111 at 80 KiB, 4074 / 4021 at 140 KiB; 3-D 1266 / 1240 at 21
