@@ -54,28 +54,29 @@ def test_repeated_colour_turns(avs, nx, ny, diatomic):
 
 
 @pytest.mark.parametrize("nx,ny,base,levels,prec", [
-    (9, 7, 8, 2, 0),      # one lane short of a group of 64 cells
-    (8, 8, 8, 2, 0),      # exactly one group
-    (13, 5, 8, 2, 0),     # one cell in the second group
-    (3, 2, 72, 0, 0),     # largest tables of the 64-lane form: its work rule, a workgroup per cell
-    (3, 2, 73, 0, 0),     # just beyond: a workgroup per cell
+    (9, 7, 8, 2, 0),      # 63, 64 and 65 cells
+    (8, 8, 8, 2, 0),
+    (13, 5, 8, 2, 0),
+    (3, 2, 72, 0, 0),     # the largest tables that the lanes would take,
+    (3, 2, 73, 0, 0),     # and beyond: a workgroup per cell (few cells)
     (5, 4, 16, 3, 1),     # FP32
     (3, 3, 5, 0, 0),      # fewer leaves than lanes
     (3, 3, 8, 0, 0),      # one leaf per lane
-    (3, 3, 38, 0, 0),     # pass C: last sizes with one wave per cell
-    (3, 3, 40, 0, 0),     # and first with four
+    (3, 3, 38, 0, 0),     # both sides of pass C's 6 KiB of tables, four waves per cell
+    (3, 3, 40, 0, 0),
     (3, 3, 38, 0, 1),
     (3, 3, 40, 0, 1),
-    (27, 27, 5, 1, 0),    # 1485 faces: a workgroup per four faces
-    (27, 28, 5, 1, 0),    # 1539 faces: a lane per face, three in the last group
+    (27, 27, 5, 1, 0),    # 1485 faces: a lane per face, 13 in the last group
+    (27, 28, 5, 1, 0),    # 1539 faces: three in the last group
     (45, 23, 8, 0, 1),
     (33, 33, 40, 0, 0),   # 2211 faces, tables of 80 entries
 ])
 def test_lane_groups(avs, nx, ny, base, levels, prec):
-    """A lane per cell and per face: group remainders, leaf shares, both
-    sides of the table limit; one or four waves per cell in pass C; two
-    explicit steps with walls (FP64 to 1e-12 per step as the other step
-    tests; FP32 1e-5 of the field)."""
+    """Small and ragged sizes in whatever forms the rules give them (the forms
+    themselves are held by test_gpu_forms): a lane or a workgroup per cell and
+    per face, one or four waves per cell in pass C; two explicit steps with
+    walls (FP64 to 1e-12 per step as the other step tests; FP32 1e-5 of the
+    field)."""
     mesh = MM.box2d(nx, ny, periodic=(True, False), sides=dict(bottom=0, top=0),
                     bcs=[(MM.WALL, (1.0, 0.1, 0.0, 1.1))])
     vs = dict(dim=2, lo=(-6, -6), hi=(6, 6), base=(base, base), max_level=levels)
@@ -107,9 +108,8 @@ def test_lane_groups_3d(avs, prec):
 
 @pytest.mark.parametrize("shape,prec", [((5, 3, 5), 0), ((8, 8, 9), 0), ((8, 8, 9), 1)])
 def test_leaf_shares(avs, shape, prec):
-    """Few groups and many leaves on small tables: the leaves of the target
-    (75 cells) and of both the target and the interface stage (1728 faces)
-    split over workgroups whose sums a closing launch adds."""
+    """Few cells and many leaves on small tables, where the rules weigh split
+    leaves against a workgroup per cell and per four faces."""
     mesh = MM.box3d(*shape)
     vs = dict(dim=3, lo=(-5.0,) * 3, hi=(5.0,) * 3, base=(18, 18, 18), max_level=0)
     prim = F.perturbed_uniform(mesh['ncells'], 3, 81, amp=0.1, uamp=0.3)
